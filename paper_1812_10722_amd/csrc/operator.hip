@@ -311,6 +311,111 @@ k_far(const Chunk* __restrict__ chunks, const Box* __restrict__ boxes,
     }
 }
 
+// ------------------------------------------------------------------------------- direct sums
+// FP64 sums of one or two wavelengths over direct ranges alone, every kernel value formed on the
+// fly: a dense product on a mesh whose factors do not fit the device.  Bound by the FP64 vector
+// units: about 19 operations per far-rule node and 10 per pair (about 88 at K = 4).
+// One workgroup per chunk, one target per lane; DW waves take tiles of DT panels of each range in
+// turn.  A panel's record, centroid and densities are the same for the whole wave, so they come
+// by scalar loads and enter the arithmetic from scalar registers: no LDS, barrier or vector load
+// in the loop, and up to 32 waves stay resident per CU (k_far, with 29 KB of LDS per one-wave
+// workgroup, holds five).  Each tile's partial joins a compensated sum; the waves' sums are added
+// (compensated) through LDS after the own-surface ranges and at the end.
+// 111392 panels, one wavelength, K = 4: 41 ms (k_far: 232 ms), 0.30 T pairs/s; the operations
+// above take 28 ms at the FP64 vector peak.
+constexpr int DW = 16;  // waves per workgroup
+constexpr int DT = 16;  // panels per partial
+
+// FP64 inverse square root: the hardware estimate (relative error below 2^-22) and one third-order
+// step, y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2: its truncation, 5 e^3 / 16 < 2^-64, is below
+// the rounding, as after two Newton steps, in five operations instead of eight.
+__device__ __forceinline__ double rsqrt_cubic(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
+}
+
+template <int K, int CPT>
+__global__ void __launch_bounds__(64 * DW)
+k_direct64(const Chunk* __restrict__ chunks, const int32_t* __restrict__ p2p_off,
+           const Range* __restrict__ p2p_rng, const int32_t* __restrict__ p2p_self,
+           const double* __restrict__ cen, const double* __restrict__ src,
+           const double* __restrict__ dens, double* __restrict__ out_self,
+           double* __restrict__ out_all) {
+    constexpr int NC = 2 * CPT, RS = 4 + 4 * K;
+    static_assert(NC <= DW, "one wave per column adds the waves' sums");
+    __shared__ double red[NC][DW][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Chunk C = chunks[blockIdx.x];
+    const int i = C.start + lane;
+    const bool valid = i < C.end;
+    const int it = valid ? i : C.start;
+    const double x0 = cen[3 * it], x1 = cen[3 * it + 1], x2 = cen[3 * it + 2];
+    double hi[NC], lo[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) hi[c] = lo[c] = 0.0;
+    // adds panel j (uniform); SELF: the lane whose target it is adds nothing
+    auto panel = [&](int j, double (&part)[NC], auto self) {
+        const double* r = src + static_cast<size_t>(j) * RS;
+        const double* dj = dens + static_cast<size_t>(j) * NC;
+        const double dx = x0 - cen[3 * static_cast<size_t>(j)];
+        const double dy = x1 - cen[3 * static_cast<size_t>(j) + 1];
+        const double dz = x2 - cen[3 * static_cast<size_t>(j) + 2];
+        const double s = r[0] * dx + r[1] * dy + r[2] * dz;  // height above the plane
+        double sv = 0.0, sk = 0.0;
+#pragma unroll
+        for (int g = 0; g < K; ++g) {
+            const double ex = dx - r[4 + 4 * g], ey = dy - r[5 + 4 * g], ez = dz - r[6 + 4 * g];
+            const double ri = rsqrt_cubic(ex * ex + ey * ey + ez * ez);
+            const double t = r[7 + 4 * g] * ri;
+            sv += t;
+            sk += t * ri * ri;
+        }
+        double kk = s * sk;
+        if constexpr (decltype(self)::value) {
+            sv = j == i ? 0.0 : sv;
+            kk = j == i ? 0.0 : kk;
+        }
+#pragma unroll
+        for (int c = 0; c < CPT; ++c) {
+            part[c] += kk * dj[c];
+            part[CPT + c] += sv * dj[CPT + c];
+        }
+    };
+    const int p_beg = p2p_off[blockIdx.x], p_end = p2p_off[blockIdx.x + 1];
+    const int p_mid = p_beg + p2p_self[blockIdx.x];
+    for (int phase = 0; phase < 2; ++phase) {
+        const int pa = phase == 0 ? p_beg : p_mid, pb = phase == 0 ? p_mid : p_end;
+        for (int e = pa; e < pb; ++e) {
+            const Range R = p2p_rng[e];
+            for (int p0 = R.start + wave * DT; p0 < R.end; p0 += DW * DT) {
+                const int p1 = min(p0 + DT, R.end);
+                double part[NC];
+#pragma unroll
+                for (int c = 0; c < NC; ++c) part[c] = 0.0;
+                if (p0 < C.end && p1 > C.start)
+                    for (int j = p0; j < p1; ++j) panel(j, part, std::true_type{});
+                else
+                    for (int j = p0; j < p1; ++j) panel(j, part, std::false_type{});
+#pragma unroll
+                for (int c = 0; c < NC; ++c) two_sum_add(hi[c], lo[c], part[c]);
+            }
+        }
+        double* o = phase == 0 ? out_self : out_all;
+        if (o == nullptr) continue;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) red[c][wave][lane] = hi[c] + lo[c];
+        __syncthreads();
+        if (wave < NC) {
+            double h = 0.0, l = 0.0;
+            for (int w = 0; w < DW; ++w) two_sum_add(h, l, red[wave][w][lane]);
+            if (valid) o[static_cast<size_t>(i) * NC + wave] = h + l;
+        }
+        __syncthreads();
+    }
+}
+
 // ------------------------------------------------------------------------------- far field, MFMA
 // Far-field sums on matrix cores, FP32 or FP64.  For a chunk of 64 targets every interaction is
 // a small dense product: an expansion is (64 x terms) . (terms x columns) of Taylor
@@ -2034,6 +2139,34 @@ void launch_far_cpt(Geometry& g, int pad, const T* dens, const T* mom, double* o
     }
 }
 
+// Direct sums on the fly (k_direct64), when the geometry has no expansions and the product one or
+// two wavelengths in FP64; false otherwise (k_far: its workgroups share the kernel values among
+// more columns than this kernel's registers hold).
+bool launch_direct(Geometry& g, const Cols& c, const double* dens, double* os, double* oa,
+                   hipStream_t s) {
+    if (g.n_m2p > 0 || c.pad != c.cpt || c.cpt > 4) return false;
+    auto launch = [&](auto k, auto cpt) {
+        hipLaunchKernelGGL((k_direct64<decltype(k)::value, decltype(cpt)::value>), dim3(g.n_chunks),
+                           dim3(64 * DW), 0, s, g.chunks.p, g.p2p_off.p, g.p2p_rng.p, g.p2p_self.p,
+                           g.cen.p, g.src64.p, dens, os, oa);
+        LSPR_HIP(hipGetLastError());
+    };
+    auto width = [&](auto k) {
+        if (c.cpt == 2) launch(k, std::integral_constant<int, 2>{});
+        else launch(k, std::integral_constant<int, 4>{});
+    };
+    switch (g.K) {
+        case 1: width(std::integral_constant<int, 1>{}); return true;
+        case 3: width(std::integral_constant<int, 3>{}); return true;
+        case 4: width(std::integral_constant<int, 4>{}); return true;
+        case 7: width(std::integral_constant<int, 7>{}); return true;
+        default: return false;
+    }
+}
+bool launch_direct(Geometry&, const Cols&, const float*, double*, double*, hipStream_t) {
+    return false;
+}
+
 template <class T>
 void apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* oa,
                  hipStream_t s) {
@@ -2086,7 +2219,7 @@ void apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* 
             LSPR_REQUIRE(tiles_of<T>(g) != nullptr || (g.n_m2p == 0 && g.n_p2p == 0),
                          LSPR_E_INVALID, "matrix-core tiles were not built");
             launch_far_tiles<T>(g, c.pad, dens, mom, os, oa, s);
-        } else {
+        } else if (!launch_direct(g, c, dens, os, oa, s)) {
             switch (c.cpt) {
                 case 2: launch_far_cpt<T, 2>(g, c.pad, dens, mom, os, oa, s); break;
                 case 4: launch_far_cpt<T, 4>(g, c.pad, dens, mom, os, oa, s); break;

@@ -1,0 +1,67 @@
+"""GPU kernels chosen by size, width or precision, at the sizes where the choice or the kernel's
+edges can go wrong, against the oracle's dense matrix.
+
+Tolerance of the FP64 products: a row sums N products of kernel values and densities, each
+within a few units of 1.1e-16 of the oracle's; N <= 4096 of them in any order differ by at most
+N x 1.1e-16 x a few = 2e-12 of the largest row in the worst case and by its square root in
+practice, so 1e-12 of the largest entry holds with room.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from lspr_inputs import merge_surfaces, octasphere, perturbed_ellipsoid, place_at_gap
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    from paper_1812_10722_amd import lspr
+    assert torch.cuda.is_available()
+    return lspr
+
+
+def _surfaces(nu, nu_blobs=()):
+    out = [octasphere(nu, 8.0)]
+    rng = np.random.default_rng(nu)
+    for k, nb in enumerate(nu_blobs):
+        bv, bt = perturbed_ellipsoid(nb, (1.5, 4.0, 1.5), rng)
+        out.append((place_at_gap(bv, [0.1, 0.2, 1.0 - 2.0 * k], 8.0, 0.8), bt))
+    return out
+
+
+def _system(surfs, ncol, seed, **rules):
+    """x, permittivities and the oracle's products for ncol columns."""
+    v, t, sid = merge_surfaces(surfs)
+    V, K = oracle.dense_operators(v, t, **rules)
+    normal = oracle.panel_geometry(v, t)["normal"]
+    rng = np.random.default_rng(seed)
+    x = rng.standard_normal((ncol, 2 * len(t))) + 1j * rng.standard_normal((ncol, 2 * len(t)))
+    em = 1.7 + 0.05 * rng.random(ncol) + 0.01j * rng.random(ncol)
+    es = np.concatenate([(-3.0 + rng.random((ncol, 1)) + 0.3j),
+                         2.0 + rng.random((ncol, len(surfs) - 1)) + 0.1j], 1)
+    ref = np.stack([oracle.assemble_system(V, K, sid, normal, em[c], es[c], [0, 0, 1.0])[0] @ x[c]
+                    for c in range(ncol)])
+    return x, em, es, ref
+
+
+def _worst(y, ref):
+    return (np.abs(y - ref).max(1) / np.abs(ref).max(1)).max()
+
+
+# direct FP64 sums on the fly (one and two wavelengths; every far rule): 8 panels (one partial
+# chunk, fewer panels than waves), 288 (a tile past 16 x 16 panels), 968 (ragged chunks), and two
+# and three surfaces (own-surface sums apart, ranges that do not start at a tile)
+@pytest.mark.parametrize("nu,blobs,ncol,k_far", [(1, (), 1, 4), (6, (), 2, 4), (11, (), 1, 4),
+                                                 (5, (3,), 1, 4), (6, (3, 4), 2, 4),
+                                                 (5, (3,), 2, 1), (5, (3,), 1, 3), (5, (3,), 2, 7)])
+def test_direct_sums_on_the_fly(lib, nu, blobs, ncol, k_far):
+    surfs = _surfaces(nu, blobs)
+    x, em, es, ref = _system(surfs, ncol, 3, k_far=k_far)
+    geo = lib.Geometry(surfs, method="dense", precision="fp64", k_far=k_far, matrix_cores=False)
+    y = geo.apply(torch.as_tensor(x).cuda(), em, es).cpu().numpy()
+    assert _worst(y, ref) < 1e-12
+    again = geo.apply(torch.as_tensor(x).cuda(), em, es, noalloc=True).cpu().numpy()
+    assert (again == y).all()
