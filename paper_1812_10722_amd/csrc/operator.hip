@@ -1053,10 +1053,10 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
         // this wave's requests of tile e + 1 (made at the start of tile e - 1, or before the
         // first tile) are complete when no more than the loads issued after them are
         // outstanding: the NBS B operands of tile e - 1, this tile's descriptor, requests and
-        // NBS B operands (vmcnt field split over bits 3:0 and 15:14; expcnt and lgkmcnt not
-        // waited for); the barrier then makes every wave's part visible and frees Lc for the
+        // NBS B operands, less one to spare (vmcnt field split over bits 3:0 and 15:14; expcnt
+        // and lgkmcnt not waited for); the barrier then makes every wave's part visible and frees Lc for the
         // next tile's request
-        constexpr int VM = 2 * NBS + 1 + NREQ;
+        constexpr int VM = 2 * NBS + NREQ;
         static_assert(VM < 64, "vmcnt range");
         __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
         // (the empty statements keep the compiler from moving memory accesses across the
@@ -1077,6 +1077,10 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
         if (e >= t_end) break;
         tile(e++, std::integral_constant<int, 2>{});
     }
+    // The last B operand of a tile is used after the loop too: dead where the loop ends, its load
+    // would be moved past the wait above, which then leaves one request too many outstanding
+    // (waves without columns or K-steps of their own have no other wait for their requests).
+    asm volatile("" ::"v"(bc[NBS - 1]));
     if (o_self != nullptr && t_mid == t_end && t_mid > t_beg)
         write_sums(o_self + static_cast<size_t>(C.start) * ncols);
     write_sums(o_all);
@@ -1216,10 +1220,10 @@ k_far_wide64(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items
         }
     };
     // this wave's requests of the next half were made before the NH B-operand loads that
-    // followed them (vmcnt field split over bits 3:0 and 15:14; expcnt and lgkmcnt not waited
+    // followed them, less one to spare (vmcnt field split over bits 3:0 and 15:14; expcnt and lgkmcnt not waited
     // for); the barrier then makes every wave's part visible and frees the buffer just read
     auto end_half = [&]() {
-        constexpr int VM = NH;
+        constexpr int VM = NH - 1;
         static_assert(VM < 64, "vmcnt range");
         __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
         // (the empty statements keep the compiler from moving memory accesses across the
@@ -1245,6 +1249,7 @@ k_far_wide64(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items
         Te = Tn;
         Tn = to_desc(dn);
     }
+    asm volatile("" ::"v"(bc[NH - 1]));  // its load stays before the wait, as in k_far_wide
     if (o_self != nullptr && t_mid == t_end && t_mid > t_beg)
         write_sums(o_self + static_cast<size_t>(C.start) * ncols);
     write_sums(o_all);
