@@ -1086,6 +1086,212 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
     write_sums(o_all);
 }
 
+// FP32 products of more than 16 wavelengths, left factors read straight into LDS, in half tiles:
+// workgroups of exactly W column groups (3 .. 8), one operator each, with one wave per group
+// (TH = 1) or two, each on half of the chunk's targets (TH = 2).  Every tile runs as two halves of
+// ceil(n / 2) and the rest of its n K-steps (at most NH) through three LDS buffers of NH KB: at
+// the start of a half every wave requests its share of the half after the next into the buffer
+// just freed, so two halves are in flight per workgroup, in half the LDS of k_far_wide's
+// whole-tile buffers and with half of its B-operand registers, and no wave idles for want of
+// columns (the four-wave workgroups leave one in four without, at 17-24 wavelengths, and
+// k_far_wide three in eight at 33-40).  The FP32 partial of a tile runs over both halves and
+// joins the FP64 sums at its end: the arithmetic per output is that of k_far_tiles_op<float, NSM,
+// 1>, so the sums are identical.  What bounds it: at 24 wavelengths the matrix cores want a left
+// factor about as fast as HBM and L2 stream them; wider, the matrix cores themselves (0.75 busy).
+// 32768 panels, P = 8: 24 wavelengths 0.67 -> 0.58 ms, 32: 0.69 -> 0.64, 40: 1.02 -> 0.93,
+// 48: 1.14 -> 0.93; 31576-panel sensor, P = 10: 24: 0.79 -> 0.70, 48: 1.49 -> 1.10, 64: 1.52 -> 1.36.
+// Requires work items that do not span a chunk's own-surface boundary (plan_items, cut_self).
+template <int NSM, int W, int TH>
+__global__ void __launch_bounds__(64 * W * TH, TH == 2 ? 24 / (W * TH) : 16 / W)
+k_far_half(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
+           const int32_t* __restrict__ item_order, const int32_t* __restrict__ tile_self,
+           const TileDesc* __restrict__ tiles, const float* __restrict__ tileA,
+           const float* __restrict__ dens, const float* __restrict__ mom, int pad,
+           double* __restrict__ out_self, double* __restrict__ out_all,
+           double* __restrict__ part) {
+    constexpr int NB = NSM > DSTEPS ? NSM : DSTEPS;
+    constexpr int NH = (NB + 1) / 2;          // most K-steps of a half tile
+    constexpr int NW = W * TH, MT = 4 / TH;    // waves, target tiles per wave
+    constexpr int NREQ = (NH + NW - 1) / NW;  // K-steps each wave requests per half
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    __shared__ float4 lb0[NH * 64];
+    __shared__ float4 lb1[NH * 64];
+    __shared__ float4 lb2[NH * 64];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = wave % W, th = wave / W;  // column group and target half of this wave
+    const int c16 = lane & 15, grp = lane >> 4;
+    const int ncols = 2 * pad;
+    // two workgroups per work item, at b and b + 8: operator (b >> 3) & 1
+    const int b = blockIdx.x;
+    const int opr = (b >> 3) & 1;
+    const int item = item_order[(b >> 4) * 8 + (b & 7)];
+    if (item < 0) return;
+    const FarItem I = items[item];
+    const int chunk = I.chunk;
+    const Chunk C = chunks[chunk];
+    const int ntg = C.end - C.start;
+    const int col = opr * pad + 16 * wg + c16;
+    const uint32_t boff = static_cast<uint32_t>(grp * ncols + col) * 4u;
+    const uint32_t bstep = 16u * static_cast<uint32_t>(ncols);
+    v4f acc[MT];
+    double run[MT][4];
+#pragma unroll
+    for (int a = 0; a < MT; ++a) {
+        acc[a] = v4f{0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) run[a][q] = 0.0;
+    }
+    const bool whole = I.slot < 0;
+    const int t_beg = I.t0, t_end = I.t1;
+    const int t_mid = whole ? t_beg + tile_self[chunk] : t_beg;
+    double* const o_self = whole ? out_self : nullptr;
+    double* const o_all = whole ? out_all + static_cast<size_t>(C.start) * ncols
+                                : part + static_cast<size_t>(I.slot) * NT * ncols;
+    auto write_sums = [&](double* out) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int t = 16 * (th * MT + mt) + out_row<float>(grp, q);
+                if (t < ntg) out[static_cast<size_t>(t) * ncols + col] = run[mt][q];
+            }
+    };
+    auto b_rsrc = [&](const TileDesc& D, uint32_t rows) {
+        const float* bsrc = D.kind == 0 ? mom : dens;
+        return buffer_rsrc(bsrc + static_cast<size_t>(D.b_row0) * ncols,
+                           rows * static_cast<uint32_t>(ncols) * 4u);
+    };
+    auto to_desc = [](const v4u& w) {
+        const uint32_t w0 = __builtin_amdgcn_readfirstlane(w[0]);
+        TileDesc D;
+        D.kind = static_cast<int16_t>(w0 & 0xffffu);
+        D.nstep = static_cast<int16_t>(w0 >> 16);
+        D.a_blk = static_cast<int32_t>(__builtin_amdgcn_readfirstlane(w[1]));
+        D.b_row0 = static_cast<int32_t>(__builtin_amdgcn_readfirstlane(w[2]));
+        D.b_rows = static_cast<int32_t>(__builtin_amdgcn_readfirstlane(w[3]));
+        return D;
+    };
+    // this wave's requests for K-steps [s0, s0 + n) of tile D's left factor (its own operator's
+    // factor of a direct tile) into L: local steps wave, wave + W, ... (the last slot may be
+    // requested by more than one wave, with the same data), zeros past n
+    auto request = [&](const TileDesc& D, int s0, int n, float4* L) {
+        const int64_t off = D.a_off() + (D.kind == 1 ? static_cast<int64_t>(opr) * D.nstep * 256 : 0) +
+                            static_cast<int64_t>(s0) * 256;
+        const __amdgpu_buffer_rsrc_t ra =
+            buffer_rsrc(tileA + off, n > 0 ? static_cast<uint32_t>(n) * 1024u : 0u);
+#pragma unroll
+        for (int k = 0; k < NREQ; ++k) {
+            const int st = wave + NW * k < NH ? wave + NW * k : NH - 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(L + st * 64), 16, lane * 16,
+                                                     st * 1024, 0, 0);
+        }
+    };
+    if (o_self != nullptr && t_mid == t_beg) write_sums(o_self + static_cast<size_t>(C.start) * ncols);
+    const __amdgpu_buffer_rsrc_t rt =
+        buffer_rsrc(tiles + t_beg, static_cast<uint32_t>(t_end - t_beg) * 16u);
+    TileDesc Te = tiles[t_beg < t_end ? t_beg : 0];
+    TileDesc Tn = tiles[t_beg + 1 < t_end ? t_beg + 1 : 0];
+    float bc[NH];
+    {
+        const int n = t_beg < t_end ? Te.nstep : 0, h = (n + 1) / 2;
+        request(Te, 0, h, lb0);
+        request(Te, h, n - h, lb1);
+        const __amdgpu_buffer_rsrc_t rb =
+            b_rsrc(Te, t_beg < t_end ? static_cast<uint32_t>(Te.b_rows) : 0u);
+#pragma unroll
+        for (int i = 0; i < NH; ++i) bc[i] = load_elem<float>(rb, boff, i * bstep);
+    }
+    __syncthreads();  // waits for every load: the first tile is complete
+    // the products of one half: n K-steps from Lc with the operands in bc, each operand register
+    // then refilled with the next half's operand (step st of rbn at offset b0 + st * bstep)
+    auto products = [&](const float4* Lc, int n, __amdgpu_buffer_rsrc_t rbn, uint32_t b0) {
+        // this wave's left operands of K-step st: MT of the four target tiles of a lane
+        auto left = [&](int st, float (&a)[MT]) {
+            if constexpr (TH == 1) {
+                const Quad<float> q = lds_quad<float>(Lc, st, lane);
+                a[0] = q.x;
+                a[1] = q.y;
+                a[2] = q.z;
+                a[3] = q.w;
+            } else {
+                const float2 q = reinterpret_cast<const float2*>(Lc)[(st * 64 + lane) * 2 + th];
+                a[0] = q.x;
+                a[1] = q.y;
+            }
+        };
+        float a[MT], an[MT];
+        left(0, a);
+        uint32_t so = b0;
+#pragma unroll
+        for (int st = 0; st < NH; ++st) {
+            if (st + 1 < NH) left(st + 1, an);
+            if (st < n) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m) acc[m] = Mma<float>::op(a[m], bc[st], acc[m]);
+            }
+            bc[st] = load_elem<float>(rbn, boff, so);
+            so = next_step(so, bstep);
+#pragma unroll
+            for (int m = 0; m < MT; ++m) a[m] = an[m];
+        }
+    };
+    // at the end of half i this wave's requests of half i + 1 (made at the start of half i - 1) are
+    // complete when no more than the loads issued after them are outstanding: the NH B operands of
+    // half i - 1, then the requests and NH B operands of half i, less one to spare (vmcnt field split over bits 3:0
+    // and 15:14; expcnt and lgkmcnt not waited for); the barrier then makes every wave's part
+    // visible and frees the buffer just read
+    auto end_half = [&]() {
+        constexpr int VM = 2 * NH + NREQ - 1;
+        static_assert(VM < 64, "vmcnt range");
+        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
+        // (the empty statements keep the compiler from moving memory accesses across the
+        // barrier, which itself orders none)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // one tile, its halves in buffers P and P + 1 (mod 3)
+    auto tile = [&](int e, auto par) {
+        constexpr int P = decltype(par)::value;
+        float4* const L0 = P == 0 ? lb0 : (P == 1 ? lb1 : lb2);
+        float4* const L1 = P == 0 ? lb1 : (P == 1 ? lb2 : lb0);
+        float4* const L2 = P == 0 ? lb2 : (P == 1 ? lb0 : lb1);
+        const v4u dn = __builtin_amdgcn_raw_buffer_load_b128(
+            rt, 0, static_cast<uint32_t>(e + 2 - t_beg) * 16u, 0);
+        const int n = Te.nstep, h = (n + 1) / 2;
+        const bool more = e + 1 < t_end;
+        const int nn = more ? Tn.nstep : 0, hn = (nn + 1) / 2;
+        request(Tn, 0, hn, L2);
+        products(L0, h, b_rsrc(Te, static_cast<uint32_t>(Te.b_rows)), static_cast<uint32_t>(h) * bstep);
+        end_half();
+        request(Tn, hn, nn - hn, L0);
+        products(L1, n - h, b_rsrc(Tn, more ? static_cast<uint32_t>(Tn.b_rows) : 0u), 0u);
+#pragma unroll
+        for (int q = 0; q < MT; ++q) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) run[q][r] += static_cast<double>(acc[q][r]);
+            acc[q] = v4f{0, 0, 0, 0};
+        }
+        end_half();
+        Te = Tn;
+        Tn = to_desc(dn);
+    };
+    // the buffers cycle with the tile's position in the item: three copies of the tile in
+    // sequence, so that no branch selects among them
+    for (int e = t_beg; e < t_end;) {
+        tile(e++, std::integral_constant<int, 0>{});
+        if (e >= t_end) break;
+        tile(e++, std::integral_constant<int, 2>{});
+        if (e >= t_end) break;
+        tile(e++, std::integral_constant<int, 1>{});
+    }
+    asm volatile("" ::"v"(bc[NH - 1]));  // its load stays before the wait, as in k_far_wide
+    if (o_self != nullptr && t_mid == t_end && t_mid > t_beg)
+        write_sums(o_self + static_cast<size_t>(C.start) * ncols);
+    write_sums(o_all);
+}
+
 // Wide FP64 products (more than 64 columns per operator): the same eight-wave workgroups as
 // k_far_wide<NSM, 1> (one operator's eight column groups, two workgroups per work item), on
 // v_mfma_f64_16x16x4f64.  An FP64 left factor takes 2 KB per K-step, too large for three buffers
@@ -1966,6 +2172,21 @@ void launch_far_wide(Geometry& g, int pad, const float* dens, const float* mom, 
     launch_far_reduce(g, fp, pad, part, os, oa, s);
 }
 
+template <int NSM, int W, int TH>
+void launch_far_half(Geometry& g, int pad, const float* dens, const float* mom, double* os,
+                     double* oa, hipStream_t s) {
+    const Geometry::FarPlan& fp = far_plan_for(g, pad);
+    double* part = nullptr;
+    if (fp.n_slots > 0)
+        part = reinterpret_cast<double*>(workspace(g, g.ws_fpart, far_part_bytes(g, pad)));
+    const int nblk = fp.n_order * 2;
+    hipLaunchKernelGGL((k_far_half<NSM, W, TH>), dim3(nblk), dim3(64 * W * TH), 0, s, g.chunks.p, fp.items.p,
+                       fp.order.p, g.tile_self.p, g.tiles.p, g.tileA.p, dens, mom, pad, os, oa,
+                       part);
+    LSPR_HIP(hipGetLastError());
+    launch_far_reduce(g, fp, pad, part, os, oa, s);
+}
+
 template <int NSM>
 void launch_far_wide64(Geometry& g, int pad, const double* dens, const double* mom, double* os,
                        double* oa, hipStream_t s) {
@@ -2009,6 +2230,23 @@ void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T*
     } else if (g.pair_ops) {
         launch_far_tiles_op_s<T, NSM, 1, 2>(g, pad, abuf, dens, mom, os, oa, s);
     } else {
+        // FP32 from P = 6: half tiles, workgroups of as many column groups as there are; two waves
+        // per group at five and six groups (measured at P = 6, 8, 10 and 15: one wave is 1-20 %
+        // slower there, two are 1-15 % slower at three, four, seven and eight groups).  Seven and
+        // eight groups up to P = 8 keep the whole-tile buffers (within 2 % of each other); at
+        // P = 10 those would leave one workgroup per CU.
+        if constexpr (std::is_same<T, float>::value && NSM >= 13) {
+            if (!g.four_wave) {
+                if (groups == 3) return launch_far_half<NSM, 3, 1>(g, pad, dens, mom, os, oa, s);
+                if (groups == 4) return launch_far_half<NSM, 4, 1>(g, pad, dens, mom, os, oa, s);
+                if (groups == 5) return launch_far_half<NSM, 5, 2>(g, pad, dens, mom, os, oa, s);
+                if (groups == 6) return launch_far_half<NSM, 6, 2>(g, pad, dens, mom, os, oa, s);
+                if constexpr (NSM > 21) {
+                    if (groups == 7) return launch_far_half<NSM, 7, 1>(g, pad, dens, mom, os, oa, s);
+                    if (groups == 8) return launch_far_half<NSM, 8, 1>(g, pad, dens, mom, os, oa, s);
+                }
+            }
+        }
         if constexpr (std::is_same<T, float>::value && NSM <= 21) {
             // FP32 above 64 columns per operator: both column halves in one workgroup (up to
             // P = 8: at longer slices its registers exceed four waves per SIMD)

@@ -65,3 +65,25 @@ def test_direct_sums_on_the_fly(lib, nu, blobs, ncol, k_far):
     assert _worst(y, ref) < 1e-12
     again = geo.apply(torch.as_tensor(x).cuda(), em, es, noalloc=True).cpu().numpy()
     assert (again == y).all()
+
+
+# FP32 products of more than 16 wavelengths in half tiles: every number of column groups (3 .. 8),
+# each number of waves per group, odd and even K-steps per tile (P = 6, 8, 10, 15) and direct
+# tiles of one step (short remainders).  The arithmetic per output is that of the four-wave
+# workgroups, so the results are equal bit for bit, on every repeat (a request that had not
+# landed would show here).
+@pytest.mark.parametrize("p", [6, 8, 10, 12, 15])
+def test_half_tile_products_equal_four_wave_products(lib, p):
+    surfs = _surfaces(13, (5, 6))
+    n = sum(len(t) for _, t in surfs)
+    kw = dict(method="treecode", precision="fp32", p=p, theta=0.5)
+    four, half = lib.Geometry(surfs, four_wave=True, **kw), lib.Geometry(surfs, **kw)
+    rng = np.random.default_rng(p)
+    for nl in (17, 24, 25, 32, 33, 40, 41, 48, 49, 56, 57, 64):
+        x = torch.as_tensor(rng.standard_normal((nl, 2 * n)) +
+                            1j * rng.standard_normal((nl, 2 * n))).cuda()
+        em = np.full(nl, 1.7733)
+        es = np.stack([-3.0 + 0.3j + rng.standard_normal(nl)] + [np.full(nl, 2.5)] * 2, 1)
+        want = four.apply(x, em, es)
+        for _ in range(4):
+            assert torch.equal(half.apply(x, em, es), want), (p, nl)
