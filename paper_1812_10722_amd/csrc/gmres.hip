@@ -31,6 +31,7 @@
 // change the solution.
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 #include "precond.hpp"
 #include "profile.hpp"
@@ -42,8 +43,10 @@ namespace {
 
 constexpr int GT = 256;
 constexpr int FT = 256, FR = 8;  // finishing kernel: threads, threads per partial-sum reduction
-constexpr int GE = 16;
+constexpr int GE = 16;           // elements per thread
+constexpr int GE_SMALL = 4;      // the same where few blocks run (arnoldi_shape)
 constexpr int GSLICE = GT * GE;
+constexpr int KB = 4;            // basis vectors per round of the inner-product pass
 constexpr double INV_4PI = 0.07957747154594767;
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
@@ -66,17 +69,18 @@ __device__ __forceinline__ double wave_sum(double v) {
 //   k < nq: q_k^H p;  k = nq: p^H p;  (WITH_W) nq + 1 + k: q_k^H w;  2 nq + 1: p^H w;  2 nq + 2: w^H w
 // go to part[(slot * kmax + k) * nparts + 4 blk + wave].  The basis is taken KB vectors at a
 // time, and the wave reductions of their 4 KB partial sums are interleaved, so that the
-// cross-lane exchanges overlap instead of waiting on each other.
-template <int WITH_W>
+// cross-lane exchanges overlap instead of waiting on each other.  gridDim.z blocks share a slice's
+// rounds (block z takes rounds z, z + gridDim.z, ...; each reads p and w again).
+template <int WITH_W, int GE>
 __global__ void __launch_bounds__(GT) k_dcgs_red(const double2* __restrict__ V, int m1,
                                                  int64_t nvec, int nq,
                                                  const double2* __restrict__ w,
                                                  const int32_t* __restrict__ cols,
                                                  double2* __restrict__ part, int kmax,
                                                  int nparts) {
-    constexpr int KB = 4, NV = WITH_W ? 4 : 2;  // values per basis vector: s (re, im) [, z]
+    constexpr int NV = WITH_W ? 4 : 2;  // values per basis vector: s (re, im) [, z]
     const int slot = blockIdx.y, col = cols[slot];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * GSLICE;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * GT * GE;
     const double2* Vc = V + static_cast<int64_t>(col) * m1 * nvec;
     const double2* wc = w + col * nvec;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -103,7 +107,7 @@ __global__ void __launch_bounds__(GT) k_dcgs_red(const double2* __restrict__ V, 
             wl[e] = make_double2(0.0, 0.0);
         }
     }
-    for (int k0 = 0; k0 < nq; k0 += KB) {
+    for (int k0 = KB * blockIdx.z; k0 < nq; k0 += KB * gridDim.z) {
         double v[KB][NV];
 #pragma unroll
         for (int kk = 0; kk < KB; ++kk) {
@@ -145,6 +149,7 @@ __global__ void __launch_bounds__(GT) k_dcgs_red(const double2* __restrict__ V, 
             }
         }
     }
+    if (blockIdx.z != 0) return;
     double al = 0.0, br = 0.0, bi = 0.0, ga = 0.0;
 #pragma unroll
     for (int e = 0; e < GE; ++e) {
@@ -366,14 +371,16 @@ __global__ void __launch_bounds__(FT) k_dcgs_finish(const double2* __restrict__ 
 }
 
 // Second pass of step j: q_j = (p - Q s) / r into slot j and the next provisional vector
-// (w - Q (z - s t) - p t) / (r nu) into slot j + 1, reading each basis vector once.
+// (w - Q (z - s t) - p t) / (r nu) into slot j + 1, reading each basis vector once.  The loads of
+// 32 / GE basis vectors are in flight together.
+template <int GE>
 __global__ void __launch_bounds__(GT) k_dcgs_update(double2* __restrict__ V, int m1, int64_t nvec,
                                                     int j, const double2* __restrict__ w,
                                                     const int32_t* __restrict__ cols,
                                                     const double2* __restrict__ coef, int kmax) {
     extern __shared__ double2 cfs[];  // [2 j]: s, then z - s t
     const int col = cols[blockIdx.y];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * GSLICE;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * GT * GE;
     double2* Vc = V + static_cast<int64_t>(col) * m1 * nvec;
     const double2* cf = coef + col * kmax;
     for (int i = threadIdx.x; i < j; i += GT) {
@@ -400,7 +407,7 @@ __global__ void __launch_bounds__(GT) k_dcgs_update(double2* __restrict__ V, int
         aq[e] = p;
         aw[e] = make_double2(wv.x - pt.x, wv.y - pt.y);
     }
-#pragma unroll 2
+#pragma unroll 32 / GE
     for (int i = 0; i < j; ++i) {
         const double2* qi = Vc + i * nvec;
         const double2 cq = cfs[i], cw = cfs[j + i];
@@ -498,26 +505,45 @@ __global__ void __launch_bounds__(64) k_backsolve(const double2* __restrict__ H,
     }
 }
 
-// u_col = sum_{k < jn} y_k V_k
+// u_col = sum_{k < jn} y_k V_k, basis vector by basis vector (GE loads in flight per vector)
+template <int GE>
 __global__ void __launch_bounds__(GT) k_basis_combine(const double2* __restrict__ V, int m1,
                                                       int64_t nvec, const double2* __restrict__ y,
                                                       int m, const int32_t* __restrict__ jn,
                                                       const int32_t* __restrict__ cols,
                                                       double2* __restrict__ u) {
+    extern __shared__ double2 ys[];  // [m]
     const int col = cols[blockIdx.y];
     const int n = jn[col];
-    const int64_t base = static_cast<int64_t>(blockIdx.x) * GSLICE;
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * GT * GE;
+    for (int k = threadIdx.x; k < n; k += GT) ys[k] = y[col * m + k];
+    __syncthreads();
+    const double2* Vc = V + static_cast<int64_t>(col) * m1 * nvec;
+    int64_t nn[GE];
+    double2 a[GE];
 #pragma unroll
     for (int e = 0; e < GE; ++e) {
         const int64_t q = base + e * GT + threadIdx.x;
-        if (q >= nvec) continue;
-        double2 a = make_double2(0.0, 0.0);
-        for (int k = 0; k < n; ++k) {
-            const double2 p = cmul(V[(static_cast<int64_t>(col) * m1 + k) * nvec + q], y[col * m + k]);
-            a.x += p.x;
-            a.y += p.y;
+        nn[e] = q < nvec ? q : nvec - 1;
+        a[e] = make_double2(0.0, 0.0);
+    }
+#pragma unroll 32 / GE
+    for (int k = 0; k < n; ++k) {
+        const double2 yk = ys[k];
+        double2 v[GE];
+#pragma unroll
+        for (int e = 0; e < GE; ++e) v[e] = Vc[k * nvec + nn[e]];
+#pragma unroll
+        for (int e = 0; e < GE; ++e) {
+            const double2 p = cmul(v[e], yk);
+            a[e].x += p.x;
+            a[e].y += p.y;
         }
-        u[col * nvec + q] = a;
+    }
+#pragma unroll
+    for (int e = 0; e < GE; ++e) {
+        const int64_t q = base + e * GT + threadIdx.x;
+        if (q < nvec) u[col * nvec + q] = a[e];
     }
 }
 
@@ -600,6 +626,35 @@ __global__ void k_norm_final(const double* __restrict__ part2, int nblk,
 
 int blocks_for(int64_t nvec) { return static_cast<int>((nvec + GSLICE - 1) / GSLICE); }
 
+// Launch shape of the Arnoldi passes over ns vectors of nvec elements: 16 elements per thread
+// read the basis at 0.87-0.96 of a plain streaming read once the blocks fill the chip; with fewer
+// than two blocks per CU, 4 elements per thread make four times as many, and the inner-product
+// pass's rounds are spread over up to 1024 blocks (a pass is then a few dependent loads deep).
+// 512 panels, 1 wavelength, 24 iterations: 16.6 -> 5.1 us per inner-product pass, 9.7 -> 4.7 us per
+// update; 24464 panels, up to 21 wavelengths (252 blocks at 16 elements): 63 -> 47 and 44 -> 40 us.
+constexpr int SMALL_BLOCKS = 512;
+int small_blocks_for(int64_t nvec) {
+    return static_cast<int>((nvec + GT * GE_SMALL - 1) / (GT * GE_SMALL));
+}
+struct ArnoldiShape {
+    bool small;
+    int nblk, zsplit;
+};
+ArnoldiShape arnoldi_shape(int64_t nvec, int ns, int nq) {
+    ArnoldiShape a{blocks_for(nvec) * ns < SMALL_BLOCKS, blocks_for(nvec), 1};
+    if (a.small) a.nblk = small_blocks_for(nvec);
+    const int rounds = std::max(1, (nq + KB - 1) / KB);
+    a.zsplit = std::min(rounds, std::max(1, 1024 / (a.nblk * ns)));
+    return a;
+}
+// Blocks (over all vectors) of the largest launch for up to B vectors: at most 4 SMALL_BLOCKS,
+// or those of 16 elements per thread.
+size_t arnoldi_blocks(int64_t nvec, int B) {
+    const int nb = blocks_for(nvec), small = std::min(B, (SMALL_BLOCKS - 1) / nb);
+    return std::max<size_t>(static_cast<size_t>(B) * nb,
+                            static_cast<size_t>(small) * small_blocks_for(nvec));
+}
+
 // Pinned host memory for the residual estimates, one block per host thread, allocated once and
 // kept for the life of the process (freeing pinned memory can wait for the whole device, which
 // would stall concurrent requests).
@@ -668,11 +723,11 @@ SolveResult gmres_solve(Geometry& g, int prec, int B, const double2* ratio_d,
     const bool pre = gm.precond != 0;
     DevBuf<double2> V(static_cast<size_t>(B) * m1 * nvec), w(B * nvec), bvec(B * nvec);
     const int kmax = 2 * m1 + 3;
-    const int nparts = 4 * nblk;  // one partial sum per wave of each block
     DevBuf<double2> Hr(static_cast<size_t>(B) * m * m1), H(static_cast<size_t>(B) * m * m1);
     DevBuf<double2> hp(B * (m1 + 1)), cs(B * m), sn(B * m), gv(B * m1), y(B * m);
     DevBuf<double2> coef(B * kmax);
-    DevBuf<double2> part(static_cast<size_t>(B) * kmax * nparts);
+    // one partial sum per inner product and wave
+    DevBuf<double2> part(kmax * 4 * arnoldi_blocks(nvec, B));
     DevBuf<double> part2(static_cast<size_t>(B) * nblk), inv(B), nrm(B);
     DevBuf<double> nu(B), est(2 * B), r_fin(B);  // est: final estimates, then predicted ones
     DevBuf<int32_t> cols_d(B), jn_d(B), fin(B);
@@ -761,15 +816,33 @@ SolveResult gmres_solve(Geometry& g, int prec, int B, const double2* ratio_d,
     };
     Event est_ready;
     auto reduce_finish = [&](int ns, int nq, int with_w, int mode, int j) {
-        if (with_w)
-            hipLaunchKernelGGL(k_dcgs_red<1>, dim3(nblk, ns), dim3(GT), 0, s, V.p, m1, nvec, nq,
-                               w.p, cols_d.p, part.p, kmax, nparts);
-        else
-            hipLaunchKernelGGL(k_dcgs_red<0>, dim3(nblk, ns), dim3(GT), 0, s, V.p, m1, nvec, nq,
-                               w.p, cols_d.p, part.p, kmax, nparts);
+        const ArnoldiShape a = arnoldi_shape(nvec, ns, nq);
+        const int nparts = 4 * a.nblk;
+        auto red = [&](auto w_, auto ge_) {
+            hipLaunchKernelGGL((k_dcgs_red<decltype(w_)::value, decltype(ge_)::value>),
+                               dim3(a.nblk, ns, a.zsplit), dim3(GT), 0, s, V.p, m1, nvec, nq, w.p,
+                               cols_d.p, part.p, kmax, nparts);
+        };
+        auto width = [&](auto w_) {
+            if (a.small) red(w_, std::integral_constant<int, GE_SMALL>{});
+            else red(w_, std::integral_constant<int, GE>{});
+        };
+        if (with_w) width(std::integral_constant<int, 1>{});
+        else width(std::integral_constant<int, 0>{});
         hipLaunchKernelGGL(k_dcgs_finish, dim3(ns), dim3(FT),
                            (kmax + 2 * (m1 + 1) + 2 * m + (m1 + 1)) * sizeof(double2), s, part.p,
                            nparts, cols_d.p, mode, j, AS);
+        LSPR_HIP(hipGetLastError());
+    };
+    auto update = [&](int ns, int j) {
+        const ArnoldiShape a = arnoldi_shape(nvec, ns, j);
+        auto launch = [&](auto ge_) {
+            hipLaunchKernelGGL((k_dcgs_update<decltype(ge_)::value>), dim3(a.nblk, ns), dim3(GT),
+                               2 * j * sizeof(double2), s, V.p, m1, nvec, j, w.p, cols_d.p, coef.p,
+                               kmax);
+        };
+        if (a.small) launch(std::integral_constant<int, GE_SMALL>{});
+        else launch(std::integral_constant<int, GE>{});
         LSPR_HIP(hipGetLastError());
     };
     while (!active.empty()) {
@@ -788,10 +861,7 @@ SolveResult gmres_solve(Geometry& g, int prec, int B, const double2* ratio_d,
                 prof::Scope sc("arnoldi", s, 32.0 * (j + 1) * double(nvec) * ns,
                                (2.0 * j + 8.0) * 16.0 * double(nvec) * ns);
                 reduce_finish(ns, j, 1, 0, j);
-                hipLaunchKernelGGL(k_dcgs_update, dim3(nblk, ns), dim3(GT),
-                                   2 * j * sizeof(double2), s, V.p, m1, nvec, j, w.p, cols_d.p,
-                                   coef.p, kmax);
-                LSPR_HIP(hipGetLastError());
+                update(ns, j);
             }
             LSPR_HIP(hipMemcpyAsync(est_h, est.p, 2 * B * sizeof(double), hipMemcpyDeviceToHost, s));
             // The next step's product for the same columns is queued behind the estimates when
@@ -853,8 +923,16 @@ SolveResult gmres_solve(Geometry& g, int prec, int B, const double2* ratio_d,
         LSPR_HIP(hipMemcpyAsync(jn_d.p, jn.data(), B * 4, hipMemcpyHostToDevice, s));
         hipLaunchKernelGGL(k_backsolve, dim3(ns), dim3(64), (m + 1) * sizeof(double2), s, H.p,
                            gv.p, jn_d.p, cols_d.p, m, y.p);
-        hipLaunchKernelGGL(k_basis_combine, dim3(nblk, ns), dim3(GT), 0, s, V.p, m1, nvec, y.p,
-                           m, jn_d.p, cols_d.p, w.p);
+        {
+            const ArnoldiShape a = arnoldi_shape(nvec, ns, m);
+            auto combine = [&](auto ge_) {
+                hipLaunchKernelGGL((k_basis_combine<decltype(ge_)::value>), dim3(a.nblk, ns),
+                                   dim3(GT), m * sizeof(double2), s, V.p, m1, nvec, y.p, m, jn_d.p,
+                                   cols_d.p, w.p);
+            };
+            if (a.small) combine(std::integral_constant<int, GE_SMALL>{});
+            else combine(std::integral_constant<int, GE>{});
+        }
         LSPR_HIP(hipGetLastError());
         if (pre) {
             const int64_t t = static_cast<int64_t>(g.N) * ns;
