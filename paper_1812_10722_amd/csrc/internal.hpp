@@ -562,22 +562,27 @@ struct TilePlan {
         std::vector<int32_t> order;
         std::vector<FarRed> red;
         int n_slots = 0;
-    } far[3];                                    // per launch class
+    } far[3], fine[3];                           // per launch class; fine: for few chunks
+    bool has_fine[3] = {false, false, false};
     std::vector<int32_t> dto, dtr, dti;          // per chunk: direct tiles by first panel
     int64_t aoff = 0;                            // elements of one tile store
     int64_t tile_steps = 0, max_chunk_steps = 0;
 };
 // Fills P (its vectors keep their capacity).
 void plan_tiles(const Geometry& g, TilePlan& P);
-void plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off,
+bool plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off,
                 const std::vector<int32_t>& self, double split, double tail, bool cut_self,
-                TilePlan::Items& W);
+                bool fine, TilePlan::Items& W);
 // Tile plans kept for reuse: a plan refilled in place keeps its host memory mapped from one
 // geometry to the next, instead of fresh pages being faulted in on every set-up.
 std::unique_ptr<TilePlan> take_plan();
 void put_plan(std::unique_ptr<TilePlan> p);
 // Scratch bytes the far-field pieces of a product of pad columns per operator write.
+size_t far_part_bytes(int n_slots, int pad);
 size_t far_part_bytes(const Geometry& g, int pad);
+// Whether every product of launch class `cls` that lspr_apply_noalloc runs with `before` partial-
+// sum slots fits its scratch with `after` too.
+bool noalloc_keeps_fitting(const Geometry& g, int cls, int before, int after);
 // Elements of one tile store, from the host lists (the size plan_tiles will find).
 int64_t estimate_tile_elems(const Geometry& g);
 // Geometry-only left factors of the matrix-core far-field product, in each needed precision.

@@ -42,23 +42,41 @@ uint8_t* scratch_on_device() {
 
 namespace lspr {
 
-size_t apply_scratch_bytes(const Geometry& g, int B, int prec) {
-    const Cols c = make_cols(g, 2 * B, prec);
-    const size_t esz = c.prec == LSPR_FP32 ? 4 : 8;
+namespace {
+// Scratch of one batch of B columns, padded to `pad` real columns per operator of esz bytes, whose
+// far-field pieces write `far_part` bytes.
+size_t batch_bytes(const Geometry& g, int B, int pad, size_t esz, size_t far_part) {
     const size_t nvec = 2 * static_cast<size_t>(g.N);
-    const size_t nd = static_cast<size_t>(g.N) * 2 * c.pad;
+    const size_t nd = static_cast<size_t>(g.N) * 2 * pad;
     size_t b = arena_piece(static_cast<size_t>(B) * g.S * sizeof(double2));  // ratios
     b += 2 * arena_piece(static_cast<size_t>(B) * nvec * sizeof(double2));   // x, y sorted
     b += arena_piece(nd * esz);                                              // densities
     b += arena_piece(nd * sizeof(double) * (g.S > 1 ? 2 : 1));               // raw sums
     if (!g.mom_boxes.empty()) {
-        b += arena_piece(g.mom_boxes.size() * g.n_terms * 2 * c.pad * esz);  // moments
+        b += arena_piece(g.mom_boxes.size() * g.n_terms * 2 * pad * esz);    // moments
         if (g.n_slots > 0)
-            b += arena_piece(static_cast<size_t>(g.n_slots) * g.n_terms * 2 * c.pad * esz);
+            b += arena_piece(static_cast<size_t>(g.n_slots) * g.n_terms * 2 * pad * esz);
     }
-    if (c.mfma && far_part_bytes(g, c.pad) > 0)                          // far-field pieces
-        b += arena_piece(far_part_bytes(g, c.pad));
+    if (far_part > 0) b += arena_piece(far_part);                            // far-field pieces
     return b;
+}
+}  // namespace
+
+size_t apply_scratch_bytes(const Geometry& g, int B, int prec) {
+    const Cols c = make_cols(g, 2 * B, prec);
+    return batch_bytes(g, B, c.pad, c.prec == LSPR_FP32 ? 4 : 8, c.mfma ? far_part_bytes(g, c.pad) : 0);
+}
+
+bool noalloc_keeps_fitting(const Geometry& g, int cls, int before, int after) {
+    const size_t esz = g.need64 ? 8 : 4;  // lspr_apply's precision
+    const int first[4] = {1, 17, 33, MAX_BATCH + 1};
+    for (int B = first[cls]; B < first[cls + 1]; ++B) {
+        const int pad = (2 * B + 15) / 16 * 16;  // matrix-core products: make_cols
+        if (batch_bytes(g, B, pad, esz, far_part_bytes(before, pad)) <= SCRATCH_BYTES &&
+            batch_bytes(g, B, pad, esz, far_part_bytes(after, pad)) > SCRATCH_BYTES)
+            return false;
+    }
+    return true;
 }
 
 }  // namespace lspr

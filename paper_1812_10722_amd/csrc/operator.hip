@@ -2102,8 +2102,11 @@ inline const Geometry::FarPlan& far_plan_for(const Geometry& g, int pad) {
 }  // namespace
 
 // Scratch bytes of the pieces' partial sums of a launch of pad columns per operator.
+size_t far_part_bytes(int n_slots, int pad) {
+    return static_cast<size_t>(n_slots) * NT * 2 * pad * sizeof(double);
+}
 size_t far_part_bytes(const Geometry& g, int pad) {
-    return static_cast<size_t>(far_plan_for(g, pad).n_slots) * NT * 2 * pad * sizeof(double);
+    return far_part_bytes(far_plan_for(g, pad).n_slots, pad);
 }
 
 namespace {
@@ -2565,9 +2568,19 @@ int64_t estimate_tile_elems(const Geometry& g) {
 // sides of its own-surface boundary is cut there too, so no item spans it.  A chunk of several
 // items has consecutive partial-sum slots in tile order (own-surface pieces first), added in
 // that order by k_far_reduce.
-void plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off,
+// `fine`: the plan for few chunks, or false (nothing planned) where the first one is as good.  With
+// a few chunks per XCD, pieces of about the mean leave most CUs idle or hold a launch to its
+// longest piece, so the limit is the cost per item of FINE_ITEMS items (they fill the chip: two
+// workgroups each, 512-1024 slots), no less than FINE_COST (4-5 tiles of P = 8; shorter pieces
+// pay more for their start and their partial sums than they gain).  Taken below 0.45 of the
+// first limit (up to about 14700 panels): 2048 panels dense FP64, 1 wavelength 49 -> 22 us, 64:
+// 143 -> 53; 2312 panels P = 8 FP32 31 -> 22 and 86 -> 48; 8712 panels P = 15 FP64, 5 wavelengths
+// 262 -> 232; 12800 panels dense FP64, 64 wavelengths 1731 -> 1239; at 16200 panels it is 3 %
+// slower at 64 wavelengths, and at 512 panels 1-2 us of 12.
+constexpr double FINE_ITEMS = 512.0, FINE_COST = 120.0;
+bool plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off,
                 const std::vector<int32_t>& self, double split, double tail, bool cut_self,
-                TilePlan::Items& W) {
+                bool fine, TilePlan::Items& W) {
     W.items.clear();
     W.red.clear();
     W.n_slots = 0;
@@ -2580,7 +2593,13 @@ void plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off
     };
     double total = 0.0;
     for (int c = 0; c < nc; ++c) total += rcost(off[c], off[c + 1]);
-    const double cap = nc > 0 ? split * total / nc : 0.0;
+    double cap = nc > 0 ? split * total / nc : 0.0, tailcap = 0.25 * cap;
+    if (fine) {
+        const double lim = std::max(total / FINE_ITEMS, FINE_COST);
+        if (lim > 0.45 * cap) return false;
+        cap = lim;
+        tailcap = std::max(0.25 * cap, FINE_COST);
+    }
     struct Piece {
         int32_t c, t0, t1, run;
         double cost;
@@ -2653,7 +2672,7 @@ void plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off
         std::vector<Piece> ref;
         for (size_t i = 0; i < pcs.size(); ++i) {
             if (fine[i])
-                cut_chunk(pcs[i].c, pcs[i].t0, pcs[i].t1, pcs[i].run, 0.25 * cap, ref);
+                cut_chunk(pcs[i].c, pcs[i].t0, pcs[i].t1, pcs[i].run, tailcap, ref);
             else
                 ref.push_back(pcs[i]);
         }
@@ -2686,6 +2705,7 @@ void plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off
     W.order.assign(std::max<size_t>(per, 1) * 8, -1);
     for (int r = 0; r < 8; ++r)
         for (size_t i = 0; i < runs[r].size(); ++i) W.order[i * 8 + r] = runs[r][i];
+    return true;
 }
 
 namespace {
@@ -2827,10 +2847,15 @@ void plan_tiles(const Geometry& g, TilePlan& P) {
         int same = -1;
         for (int k = 0; k < cls && same < 0; ++k)
             if (g.far_split[k] == g.far_split[cls] && g.far_tail[k] == g.far_tail[cls]) same = k;
-        if (same >= 0)
+        if (same >= 0) {
             P.far[cls] = P.far[same];
-        else
-            plan_items(tiles, toff, tself, g.far_split[cls], g.far_tail[cls], true, P.far[cls]);
+            P.has_fine[cls] = P.has_fine[same];
+            if (P.has_fine[cls]) P.fine[cls] = P.fine[same];
+        } else {
+            plan_items(tiles, toff, tself, g.far_split[cls], g.far_tail[cls], true, false, P.far[cls]);
+            P.has_fine[cls] = plan_items(tiles, toff, tself, g.far_split[cls], g.far_tail[cls], true,
+                                         true, P.fine[cls]);
+        }
     }
     // each chunk's direct tiles sorted by first source panel, for the near-field fold
     P.dto.assign(nc + 1, 0);
@@ -2890,7 +2915,10 @@ void build_tiles(Geometry& g, const TilePlan& P) {
     up.add(g.tile_self.p, P.tself.data(), P.tself.size());
     for (int cls = 0; cls < 3; ++cls) {
         Geometry::FarPlan& fp = g.far_plan[cls];
-        const TilePlan::Items& W = P.far[cls];
+        // (more partial sums must not make lspr_apply_noalloc refuse a product)
+        const bool fine = P.has_fine[cls] &&
+                          noalloc_keeps_fitting(g, cls, P.far[cls].n_slots, P.fine[cls].n_slots);
+        const TilePlan::Items& W = fine ? P.fine[cls] : P.far[cls];
         fp.items.alloc(W.items.size());
         fp.order.alloc(W.order.size());
         up.add(fp.items.p, W.items.data(), W.items.size());

@@ -87,3 +87,22 @@ def test_half_tile_products_equal_four_wave_products(lib, p):
         want = four.apply(x, em, es)
         for _ in range(4):
             assert torch.equal(half.apply(x, em, es), want), (p, nl)
+
+
+# a mesh of few chunks, whose far field is cut into pieces of a few tiles: every launch class (1-16,
+# 17-32 and 33-64 wavelengths), several surfaces (own-surface pieces apart) and a ragged last
+# chunk; FP32 sums of whole tiles round as before, so 2e-6 of the largest entry bounds them (single
+# precision values and densities, 928 of them)
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32", 2e-6)])
+def test_products_of_few_chunks(lib, precision, tol):
+    surfs = _surfaces(10, (4,))
+    geo = lib.Geometry(surfs, method="dense", precision=precision)
+    for ncol in (1, 3, 16, 17, 33, 64):
+        x, em, es, ref = _system(surfs, ncol, ncol) if ncol <= 17 else (x, em, es, ref)
+        rep = -(-ncol // len(x))
+        xs, ems, ess = np.tile(x, (rep, 1))[:ncol], np.tile(em, rep)[:ncol], np.tile(es, (rep, 1))[:ncol]
+        want = np.tile(ref, (rep, 1))[:ncol]
+        xt = torch.as_tensor(xs).cuda()
+        y = geo.apply(xt, ems, ess).cpu().numpy()
+        assert _worst(y, want) < tol, ncol
+        assert (geo.apply(xt, ems, ess, noalloc=True).cpu().numpy() == y).all()
