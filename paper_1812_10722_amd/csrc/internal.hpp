@@ -360,7 +360,8 @@ struct FarItem {
     int32_t chunk, t0, t1, slot;
 };
 // A chunk cut into pieces: its partial sums are scratch blocks [slot0, slot1), the first
-// `nself` of them over own-surface tiles; they are added in block order.
+// `nself` of them over own-surface tiles; they are added in block order (slot0 = slot1: a whole
+// chunk, whose sums the far-field kernel wrote).
 struct FarRed {
     int32_t chunk, slot0, slot1, nself;
 };
@@ -422,7 +423,7 @@ struct Geometry {
     struct FarPlan {
         DevBuf<FarItem> items;
         DevBuf<int32_t> order;  // workgroup -> item (-1: none); a multiple of 8 entries
-        DevBuf<FarRed> red;     // chunks cut into pieces
+        DevBuf<FarRed> red;     // [n_chunks] partial sums of each chunk (when some are cut)
         int n_order = 0, n_red = 0, n_slots = 0;
         size_t bytes() const { return items.bytes() + order.bytes() + red.bytes(); }
     };
@@ -541,12 +542,21 @@ void build_lists(Geometry& g);
 void build_near_table(Geometry& g);
 
 // ---------------------------------------------------------------- operator (operator.hip)
+// Partial sums of the chunks a product cut into pieces, which the reader of the sums adds: per
+// chunk (null: no chunk was cut), and the scratch blocks [slot][64][2 pad].
+struct FarSums {
+    const FarRed* red = nullptr;
+    const double* part = nullptr;
+};
 // Raw layer sums for a packed density: dens [N][2*pad] in the precision c.prec (K columns
 // then V columns, sorted panel order).  out_self/out_all [N][2*pad] FP64 receive, per target,
 // the K and V sums over its own surface and over all surfaces, including the near-singular
-// and singular corrections, without the 1/(4 pi) factor.
-void apply_raw(Geometry& g, const Cols& c, const void* dens, double* out_self, double* out_all,
-               hipStream_t s);
+// and singular corrections, without the 1/(4 pi) factor; the rows of the chunks cut into pieces
+// are left to the partial sums returned (finish_sums fills them in).
+FarSums apply_raw(Geometry& g, const Cols& c, const void* dens, double* out_self, double* out_all,
+                  hipStream_t s);
+void finish_sums(Geometry& g, const Cols& c, const FarSums& f, double* out_self, double* out_all,
+                 hipStream_t s);
 void precompute_rhs(Geometry& g);
 // Host part of the matrix-core tiles: descriptors, the tiles of each chunk, workgroup order and
 // the direct tiles sorted for the near-field fold.  Reads only host copies of the lists (and

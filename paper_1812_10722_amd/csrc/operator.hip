@@ -1462,15 +1462,17 @@ k_far_wide64(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items
 }
 
 // Sums of the chunks cut into pieces: for each target row and column, the pieces' FP64 partial
-// sums added in piece order (own-surface pieces first; their sum is the own-surface result).
+// sums added in piece order (own-surface pieces first; their sum is the own-surface result).  A
+// product's row combination adds them itself; this pass serves the readers of plain sums.
 __global__ void __launch_bounds__(256)
-k_far_reduce(const Chunk* __restrict__ chunks, const FarRed* __restrict__ red, int n_red,
+k_far_reduce(const Chunk* __restrict__ chunks, const FarRed* __restrict__ red, int n_chunks,
              int ncols, const double* __restrict__ part, double* __restrict__ out_self,
              double* __restrict__ out_all) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     const int per = NT * ncols;
-    if (i >= static_cast<int64_t>(n_red) * per) return;
+    if (i >= static_cast<int64_t>(n_chunks) * per) return;
     const FarRed R = red[i / per];
+    if (R.slot1 == R.slot0) return;
     const int rc = static_cast<int>(i % per), t = rc / ncols;
     const Chunk C = chunks[R.chunk];
     if (t >= C.end - C.start) return;
@@ -2111,24 +2113,17 @@ size_t far_part_bytes(const Geometry& g, int pad) {
 
 namespace {
 
-// Sums of the chunks a launch cut into pieces (after the far-field kernel, same stream).
-void launch_far_reduce(Geometry& g, const Geometry::FarPlan& fp, int pad, const double* part,
-                       double* os, double* oa, hipStream_t s) {
-    if (fp.n_red == 0) return;
-    const int64_t tot = static_cast<int64_t>(fp.n_red) * NT * 2 * pad;
-    hipLaunchKernelGGL(k_far_reduce, dim3((tot + 255) / 256), dim3(256), 0, s, g.chunks.p,
-                       fp.red.p, fp.n_red, 2 * pad, part, os, oa);
-    LSPR_HIP(hipGetLastError());
+// Scratch blocks of the pieces of a launch of pad columns per operator (null without pieces).
+double* far_scratch(Geometry& g, int pad) {
+    if (far_plan_for(g, pad).n_slots == 0) return nullptr;
+    return reinterpret_cast<double*>(workspace(g, g.ws_fpart, far_part_bytes(g, pad)));
 }
 
 template <class T, int NSM, int S, int OPS = 1>
 void launch_far_tiles_op_s(Geometry& g, int pad, int abuf, const T* dens, const T* mom,
-                           double* os, double* oa, hipStream_t s) {
+                           double* os, double* oa, double* part, hipStream_t s) {
     const int halves = pad > 64 ? 2 : 1;
     const Geometry::FarPlan& fp = far_plan_for(g, pad);
-    double* part = nullptr;
-    if (fp.n_slots > 0)
-        part = reinterpret_cast<double*>(workspace(g, g.ws_fpart, far_part_bytes(g, pad)));
     const int nblk = fp.n_order * (OPS == 2 ? 1 : 2) * halves;
     // the left factor (OPS = 2: a direct tile's two), then (S > 1) one slot of FP64 sums per
     // column group for the final additions
@@ -2142,67 +2137,50 @@ void launch_far_tiles_op_s(Geometry& g, int pad, int abuf, const T* dens, const 
                        g.chunks.p, fp.items.p, fp.order.p, g.tile_self.p, g.tiles.p,
                        tiles_of<T>(g), dens, mom, pad, pad / 16, halves, os, oa, part);
     LSPR_HIP(hipGetLastError());
-    launch_far_reduce(g, fp, pad, part, os, oa, s);
 }
 
 template <class T, int NSM, int S>
 void launch_far_stream(Geometry& g, int pad, const T* dens, const T* mom, double* os,
-                       double* oa, hipStream_t s) {
+                       double* oa, double* part, hipStream_t s) {
     const Geometry::FarPlan& fp = far_plan_for(g, pad);
-    double* part = nullptr;
-    if (fp.n_slots > 0)
-        part = reinterpret_cast<double*>(workspace(g, g.ws_fpart, far_part_bytes(g, pad)));
     const int nblk = fp.n_order * 2;
     hipLaunchKernelGGL((k_far_stream<T, NSM, S>), dim3(nblk), dim3(256), 0, s, g.chunks.p,
                        fp.items.p, fp.order.p, g.tile_self.p, g.tiles.p, tiles_of<T>(g), dens,
                        mom, pad, pad / 16, os, oa, part);
     LSPR_HIP(hipGetLastError());
-    launch_far_reduce(g, fp, pad, part, os, oa, s);
 }
 
 template <int NSM, int S>
 void launch_far_wide(Geometry& g, int pad, const float* dens, const float* mom, double* os,
-                     double* oa, hipStream_t s) {
+                     double* oa, double* part, hipStream_t s) {
     const Geometry::FarPlan& fp = far_plan_for(g, pad);
-    double* part = nullptr;
-    if (fp.n_slots > 0)
-        part = reinterpret_cast<double*>(workspace(g, g.ws_fpart, far_part_bytes(g, pad)));
     const int nblk = fp.n_order * 2;
     hipLaunchKernelGGL((k_far_wide<NSM, S>), dim3(nblk), dim3(512), 0, s, g.chunks.p, fp.items.p,
                        fp.order.p, g.tile_self.p, g.tiles.p, g.tileA.p, dens, mom, pad, pad / 16,
                        os, oa, part);
     LSPR_HIP(hipGetLastError());
-    launch_far_reduce(g, fp, pad, part, os, oa, s);
 }
 
 template <int NSM, int W, int TH>
 void launch_far_half(Geometry& g, int pad, const float* dens, const float* mom, double* os,
-                     double* oa, hipStream_t s) {
+                     double* oa, double* part, hipStream_t s) {
     const Geometry::FarPlan& fp = far_plan_for(g, pad);
-    double* part = nullptr;
-    if (fp.n_slots > 0)
-        part = reinterpret_cast<double*>(workspace(g, g.ws_fpart, far_part_bytes(g, pad)));
     const int nblk = fp.n_order * 2;
     hipLaunchKernelGGL((k_far_half<NSM, W, TH>), dim3(nblk), dim3(64 * W * TH), 0, s, g.chunks.p, fp.items.p,
                        fp.order.p, g.tile_self.p, g.tiles.p, g.tileA.p, dens, mom, pad, os, oa,
                        part);
     LSPR_HIP(hipGetLastError());
-    launch_far_reduce(g, fp, pad, part, os, oa, s);
 }
 
 template <int NSM>
 void launch_far_wide64(Geometry& g, int pad, const double* dens, const double* mom, double* os,
-                       double* oa, hipStream_t s) {
+                       double* oa, double* part, hipStream_t s) {
     const Geometry::FarPlan& fp = far_plan_for(g, pad);
-    double* part = nullptr;
-    if (fp.n_slots > 0)
-        part = reinterpret_cast<double*>(workspace(g, g.ws_fpart, far_part_bytes(g, pad)));
     const int nblk = fp.n_order * 2;
     hipLaunchKernelGGL((k_far_wide64<NSM>), dim3(nblk), dim3(512), 0, s, g.chunks.p, fp.items.p,
                        fp.order.p, g.tile_self.p, g.tiles.p, g.tileA64.p, dens, mom, pad,
                        pad / 16, os, oa, part);
     LSPR_HIP(hipGetLastError());
-    launch_far_reduce(g, fp, pad, part, os, oa, s);
 }
 
 // one column group per operator: four waves share it; two: two waves each; more: one each.
@@ -2210,28 +2188,28 @@ void launch_far_wide64(Geometry& g, int pad, const double* dens, const double* m
 // when the geometry asks for it.
 template <class T, int NSM>
 void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T* mom,
-                         double* os, double* oa, hipStream_t s) {
+                         double* os, double* oa, double* part, hipStream_t s) {
     const int groups = pad / 16;
     // FP32 products of up to 32 columns per operator at P = 8 or 15: eight-wave workgroups that
     // read the left factors straight into LDS, with 4 or 8 waves per column group (two waves
     // per group, for three or four groups, need more than four waves' registers per SIMD)
     if constexpr (std::is_same<T, float>::value && (NSM == 21 || NSM == 16)) {
         if (!g.four_wave && !g.stream_narrow && !g.pair_narrow && groups <= 2) {
-            if (groups == 1) launch_far_wide<NSM, 8>(g, pad, dens, mom, os, oa, s);
-            else launch_far_wide<NSM, 4>(g, pad, dens, mom, os, oa, s);
+            if (groups == 1) launch_far_wide<NSM, 8>(g, pad, dens, mom, os, oa, part, s);
+            else launch_far_wide<NSM, 4>(g, pad, dens, mom, os, oa, part, s);
             return;
         }
     }
     if (groups == 1) {
-        if (g.stream_narrow) launch_far_stream<T, NSM, 4>(g, pad, dens, mom, os, oa, s);
-        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 4, 2>(g, pad, abuf, dens, mom, os, oa, s);
-        else launch_far_tiles_op_s<T, NSM, 4>(g, pad, abuf, dens, mom, os, oa, s);
+        if (g.stream_narrow) launch_far_stream<T, NSM, 4>(g, pad, dens, mom, os, oa, part, s);
+        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 4, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
+        else launch_far_tiles_op_s<T, NSM, 4>(g, pad, abuf, dens, mom, os, oa, part, s);
     } else if (groups == 2) {
-        if (g.stream_narrow) launch_far_stream<T, NSM, 2>(g, pad, dens, mom, os, oa, s);
-        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 2, 2>(g, pad, abuf, dens, mom, os, oa, s);
-        else launch_far_tiles_op_s<T, NSM, 2>(g, pad, abuf, dens, mom, os, oa, s);
+        if (g.stream_narrow) launch_far_stream<T, NSM, 2>(g, pad, dens, mom, os, oa, part, s);
+        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 2, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
+        else launch_far_tiles_op_s<T, NSM, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
     } else if (g.pair_ops) {
-        launch_far_tiles_op_s<T, NSM, 1, 2>(g, pad, abuf, dens, mom, os, oa, s);
+        launch_far_tiles_op_s<T, NSM, 1, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
     } else {
         // FP32 from P = 6: half tiles, workgroups of as many column groups as there are; two waves
         // per group at five and six groups (measured at P = 6, 8, 10 and 15: one wave is 1-20 %
@@ -2240,13 +2218,13 @@ void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T*
         // P = 10 those would leave one workgroup per CU.
         if constexpr (std::is_same<T, float>::value && NSM >= 13) {
             if (!g.four_wave) {
-                if (groups == 3) return launch_far_half<NSM, 3, 1>(g, pad, dens, mom, os, oa, s);
-                if (groups == 4) return launch_far_half<NSM, 4, 1>(g, pad, dens, mom, os, oa, s);
-                if (groups == 5) return launch_far_half<NSM, 5, 2>(g, pad, dens, mom, os, oa, s);
-                if (groups == 6) return launch_far_half<NSM, 6, 2>(g, pad, dens, mom, os, oa, s);
+                if (groups == 3) return launch_far_half<NSM, 3, 1>(g, pad, dens, mom, os, oa, part, s);
+                if (groups == 4) return launch_far_half<NSM, 4, 1>(g, pad, dens, mom, os, oa, part, s);
+                if (groups == 5) return launch_far_half<NSM, 5, 2>(g, pad, dens, mom, os, oa, part, s);
+                if (groups == 6) return launch_far_half<NSM, 6, 2>(g, pad, dens, mom, os, oa, part, s);
                 if constexpr (NSM > 21) {
-                    if (groups == 7) return launch_far_half<NSM, 7, 1>(g, pad, dens, mom, os, oa, s);
-                    if (groups == 8) return launch_far_half<NSM, 8, 1>(g, pad, dens, mom, os, oa, s);
+                    if (groups == 7) return launch_far_half<NSM, 7, 1>(g, pad, dens, mom, os, oa, part, s);
+                    if (groups == 8) return launch_far_half<NSM, 8, 1>(g, pad, dens, mom, os, oa, part, s);
                 }
             }
         }
@@ -2254,29 +2232,29 @@ void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T*
             // FP32 above 64 columns per operator: both column halves in one workgroup (up to
             // P = 8: at longer slices its registers exceed four waves per SIMD)
             if (groups > 4 && !g.four_wave) {
-                launch_far_wide<NSM, 1>(g, pad, dens, mom, os, oa, s);
+                launch_far_wide<NSM, 1>(g, pad, dens, mom, os, oa, part, s);
                 return;
             }
         }
         if constexpr (std::is_same<T, double>::value && NSM <= 21) {
             // FP64 above 64 columns per operator: the same, in half tiles
             if (groups > 4 && !g.four_wave) {
-                launch_far_wide64<NSM>(g, pad, dens, mom, os, oa, s);
+                launch_far_wide64<NSM>(g, pad, dens, mom, os, oa, part, s);
                 return;
             }
         }
-        launch_far_tiles_op_s<T, NSM, 1>(g, pad, abuf, dens, mom, os, oa, s);
+        launch_far_tiles_op_s<T, NSM, 1>(g, pad, abuf, dens, mom, os, oa, part, s);
     }
 }
 
 template <class T>
 void launch_far_tiles(Geometry& g, int pad, const T* dens, const T* mom, double* os,
-                      double* oa, hipStream_t s) {
+                      double* oa, double* part, hipStream_t s) {
     const int nsm = expansion_slice_steps(g.n_terms);
     const int abuf = direct_steps(g.n_terms) * 256;  // largest part a workgroup stages
 #define LSPR_FAR_OP(NSM_)                                                                    \
     case NSM_:                                                                               \
-        launch_far_tiles_op<T, NSM_>(g, pad, abuf, dens, mom, os, oa, s);                    \
+        launch_far_tiles_op<T, NSM_>(g, pad, abuf, dens, mom, os, oa, part, s);                    \
         return;
     switch (nsm) {  // K-steps of an expansion slice for P = 2, 4, 6, 12, 15, 8, 10
         LSPR_FAR_OP(3)
@@ -2414,7 +2392,7 @@ bool launch_direct(Geometry&, const Cols&, const float*, double*, double*, hipSt
 }
 
 template <class T>
-void apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* oa,
+FarSums apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* oa,
                  hipStream_t s) {
     LSPR_REQUIRE(src_of<T>(g) != nullptr, LSPR_E_INVALID,
                  "the geometry was not built for products in this precision");
@@ -2425,6 +2403,7 @@ void apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* 
     const int NF = (g.P + 1) * (g.P + 2) * (g.P + 3) / 6;
     const double mom_bytes = double(g.mom_boxes.size()) * g.n_terms * 2 * c.pad * esz;
     const bool fp64 = sizeof(T) == 8;
+    FarSums sums;
     T* mom = nullptr;
     if (!g.mom_boxes.empty()) {
         const size_t need = g.mom_boxes.size() * g.n_terms * 2 * c.pad * sizeof(T);
@@ -2464,7 +2443,9 @@ void apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* 
         if (c.mfma) {
             LSPR_REQUIRE(tiles_of<T>(g) != nullptr || (g.n_m2p == 0 && g.n_p2p == 0),
                          LSPR_E_INVALID, "matrix-core tiles were not built");
-            launch_far_tiles<T>(g, c.pad, dens, mom, os, oa, s);
+            sums.part = far_scratch(g, c.pad);
+            if (sums.part != nullptr) sums.red = far_plan_for(g, c.pad).red.p;
+            launch_far_tiles<T>(g, c.pad, dens, mom, os, oa, const_cast<double*>(sums.part), s);
         } else if (!launch_direct(g, c, dens, os, oa, s)) {
             switch (c.cpt) {
                 case 2: launch_far_cpt<T, 2>(g, c.pad, dens, mom, os, oa, s); break;
@@ -2474,7 +2455,8 @@ void apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* 
             }
         }
     }
-    if (c.mfma && (fp64 ? g.near_in_tiles64 : g.near_in_tiles32)) return;
+    if (c.mfma && (fp64 ? g.near_in_tiles64 : g.near_in_tiles32)) return sums;
+    finish_sums(g, c, sums, os, oa, s);  // the corrections add to complete sums
     const int64_t tot = static_cast<int64_t>(g.N) * 2 * c.pad;
     prof::Scope sc("near", s, double(g.n_near + g.N) * 2.0 * 2 * nc,
                    double(g.n_near) * 20 + dens_bytes + 2 * out_bytes);
@@ -2482,6 +2464,7 @@ void apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, double* 
                        g.near_off64.p, g.near_col.p, g.near_dv.p, g.near_dk.p, g.vself.p,
                        g.surf.p, g.N, dens, c.pad, os, oa);
     LSPR_HIP(hipGetLastError());
+    return FarSums{};
 }
 
 template <class T, int P>
@@ -2927,8 +2910,10 @@ void build_tiles(Geometry& g, const TilePlan& P) {
         fp.n_red = static_cast<int>(W.red.size());
         fp.n_slots = W.n_slots;
         if (!W.red.empty()) {
-            fp.red.alloc(W.red.size());
-            up.add(fp.red.p, W.red.data(), W.red.size());
+            std::vector<FarRed> red(nc, FarRed{0, 0, 0, 0});
+            for (const FarRed& R : W.red) red[R.chunk] = R;
+            fp.red.alloc(nc);
+            up.add(fp.red.p, red.data(), red.size());
         }
     }
     const int n_m2p = static_cast<int>(g.n_m2p), n_p2p = static_cast<int>(P.p2p_tile.size());
@@ -3008,13 +2993,21 @@ Cols make_cols(const Geometry& g, int ncol, int prec) {
 
 int expansion_terms(int P) { return (P + 1) * (P + 1); }
 
-void apply_raw(Geometry& g, const Cols& c, const void* dens, double* out_self, double* out_all,
-               hipStream_t s) {
+void finish_sums(Geometry& g, const Cols& c, const FarSums& f, double* out_self, double* out_all,
+                 hipStream_t s) {
+    if (f.red == nullptr) return;
+    const int64_t tot = static_cast<int64_t>(g.n_chunks) * NT * 2 * c.pad;
+    hipLaunchKernelGGL(k_far_reduce, dim3((tot + 255) / 256), dim3(256), 0, s, g.chunks.p, f.red,
+                       g.n_chunks, 2 * c.pad, f.part, g.S > 1 ? out_self : nullptr, out_all);
+    LSPR_HIP(hipGetLastError());
+}
+
+FarSums apply_raw(Geometry& g, const Cols& c, const void* dens, double* out_self, double* out_all,
+                  hipStream_t s) {
     double* os = g.S > 1 ? out_self : nullptr;
     if (c.prec == LSPR_FP32)
-        apply_far_t<float>(g, c, static_cast<const float*>(dens), os, out_all, s);
-    else
-        apply_far_t<double>(g, c, static_cast<const double*>(dens), os, out_all, s);
+        return apply_far_t<float>(g, c, static_cast<const float*>(dens), os, out_all, s);
+    return apply_far_t<double>(g, c, static_cast<const double*>(dens), os, out_all, s);
 }
 
 }  // namespace lspr

@@ -23,6 +23,7 @@ namespace lspr {
 namespace {
 
 constexpr int TPB = 256;
+constexpr int CHUNK = 64;  // most targets of a chunk
 constexpr double INV_4PI = 0.07957747154594767;  // 1 / (4 pi)
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
@@ -106,26 +107,53 @@ __device__ __forceinline__ void combine_one(const double2* __restrict__ x, int64
     yc[N + i] = make_double2(0.5 * phi.x - k_all.x + v_all.x, 0.5 * phi.y - k_all.y + v_all.y);
 }
 
-// Rows of Eq. matrix_multi from the raw sums (no 1/4pi yet).  Block = pp consecutive panels:
-// their rows of raw sums are read whole into LDS (row stride 2 pad + 1), then (slot, panel)
-// pairs with the panel fastest read x and write y along the panels.
+// Rows of Eq. matrix_multi from the raw sums (no 1/4pi yet).  Block = pp consecutive panels of a
+// chunk (64 / pp blocks per chunk): their rows of raw sums are read whole into LDS (row stride
+// 2 pad + 1), then (slot, panel) pairs with the panel fastest read x and write y along the
+// panels.  The rows of a chunk cut into pieces are the pieces' partial sums added in piece order
+// (as k_far_reduce does, without its launch and its pass over the sums: 4-22 us per product).
 __global__ void __launch_bounds__(TPB) k_combine(const double2* __restrict__ x, int64_t x_stride,
                                                  double2* __restrict__ y, int64_t y_stride,
                                                  const int32_t* __restrict__ cols, int nslot,
                                                  int N, const double2* __restrict__ ratio, int S,
                                                  const int32_t* __restrict__ surf,
                                                  const double* __restrict__ vself, int pad,
-                                                 int pp, const double* __restrict__ out_self,
+                                                 int pp, const Chunk* __restrict__ chunks,
+                                                 const FarRed* __restrict__ red,
+                                                 const double* __restrict__ part,
+                                                 const double* __restrict__ out_self,
                                                  const double* __restrict__ out_all) {
     extern __shared__ double comb_sh[];
     const int ncols = 2 * pad, ld = ncols + 1;
-    const int i0 = blockIdx.x * pp, np = min(pp, N - i0);
+    const int per = CHUNK / pp, ch = blockIdx.x / per;
+    const Chunk C = chunks[ch];
+    const int r0 = (blockIdx.x % per) * pp, i0 = C.start + r0, np = min(pp, C.end - i0);
+    if (np <= 0) return;
     double* ta = comb_sh;
     double* ts = out_self ? comb_sh + pp * ld : comb_sh;
-    for (int e = threadIdx.x; e < np * ncols; e += TPB) {
-        const int p = e / ncols, c = e % ncols;
-        ta[p * ld + c] = out_all[static_cast<size_t>(i0) * ncols + e];
-        if (out_self) ts[p * ld + c] = out_self[static_cast<size_t>(i0) * ncols + e];
+    FarRed R{0, 0, 0, 0};
+    if (red != nullptr) R = red[ch];
+    if (R.slot1 > R.slot0) {
+        const size_t block = static_cast<size_t>(CHUNK) * ncols;
+        const double* p0 = part + R.slot0 * block + static_cast<size_t>(r0) * ncols;
+        const int n = R.slot1 - R.slot0;
+        for (int e = threadIdx.x; e < np * ncols; e += TPB) {
+            const int at = (e / ncols) * ld + e % ncols;
+            double s = 0.0, own = 0.0;
+#pragma unroll 4
+            for (int k = 0; k < n; ++k) {
+                own = k == R.nself ? s : own;
+                s += p0[k * block + e];
+            }
+            ta[at] = s;
+            if (out_self) ts[at] = R.nself == n ? s : own;
+        }
+    } else {
+        for (int e = threadIdx.x; e < np * ncols; e += TPB) {
+            const int at = (e / ncols) * ld + e % ncols;
+            ta[at] = out_all[static_cast<size_t>(i0) * ncols + e];
+            if (out_self) ts[at] = out_self[static_cast<size_t>(i0) * ncols + e];
+        }
     }
     __syncthreads();
     for (int u = threadIdx.x; u < nslot * pp; u += TPB) {
@@ -220,7 +248,7 @@ void precompute_rhs(Geometry& g) {
         hipLaunchKernelGGL(k_rhs_dens<double>, dim3((tot + TPB - 1) / TPB), dim3(TPB), 0, s,
                            g.nrm.p, g.surf.p, g.N, g.S, c.pad, reinterpret_cast<double*>(dens.p));
     LSPR_HIP(hipGetLastError());
-    apply_raw(g, c, dens.p, os.p, oa.p, s);
+    finish_sums(g, c, apply_raw(g, c, dens.p, os.p, oa.p, s), os.p, oa.p, s);
     g.rhs_u.alloc(static_cast<size_t>(3) * g.S * g.N);
     const int64_t nu = static_cast<int64_t>(3) * g.S * g.N;
     hipLaunchKernelGGL(k_rhs_extract, dim3((nu + TPB - 1) / TPB), dim3(TPB), 0, s, oa.p, g.N,
@@ -326,12 +354,13 @@ void system_apply(Geometry& g, int prec, int nslot, const double2* ratio_d, cons
                            d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs, c.pad, ppk,
                            reinterpret_cast<double*>(dens));
     LSPR_HIP(hipGetLastError());
-    apply_raw(g, c, dens, os, oa, s);
+    const FarSums sums = apply_raw(g, c, dens, os, oa, s);
     const size_t crow = ld * sizeof(double) * (os ? 2 : 1);
     const int ppc = panels_per_block(crow);
-    hipLaunchKernelGGL(k_combine, dim3((g.N + ppc - 1) / ppc), dim3(TPB), ppc * crow, s, x,
+    LSPR_REQUIRE(g.tchunk <= CHUNK, LSPR_E_INVALID, "chunks larger than the row combination takes");
+    hipLaunchKernelGGL(k_combine, dim3(g.n_chunks * (CHUNK / ppc)), dim3(TPB), ppc * crow, s, x,
                        x_stride, y, y_stride, d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs,
-                       c.pad, ppc, os, oa);
+                       c.pad, ppc, g.chunks.p, sums.red, sums.part, os, oa);
     LSPR_HIP(hipGetLastError());
 }
 
