@@ -562,7 +562,7 @@ size_t lspr::Geometry::device_bytes() const {
            mom_slot.bytes() + chunks.bytes() + m2p_off.bytes() + m2p_box.bytes() +
            m2p_self.bytes() + p2p_off.bytes() + p2p_rng.bytes() + p2p_self.bytes() +
            near_off64.bytes() + near_col.bytes() + near_dv.bytes() + near_dk.bytes() +
-           vself.bytes() + rhs_u.bytes() + charge_u.bytes() + ws_inv_eps.bytes() + ws_dens.bytes() + ws_mom.bytes() + ws_out.bytes() +
+           vself.bytes() + rhs_u.bytes() + charge_u.bytes() + ws_inv_eps.bytes() + ws_ratio.bytes() + ws_dens.bytes() + ws_mom.bytes() + ws_out.bytes() +
            ws_part.bytes() + p2m_seg.bytes() + p2m_red.bytes() + p2mA.bytes() + p2mA64.bytes() + p2m_aoff.bytes() + tiles.bytes() + tile_off.bytes() + chunk_order.bytes() +
            far_plan[0].bytes() + far_plan[1].bytes() + far_plan[2].bytes() + ws_fpart.bytes() +
            tile_self.bytes() + tileA.bytes() + tileA64.bytes() + src32.bytes() + src64.bytes();
@@ -725,12 +725,17 @@ int lspr_apply(lspr_geometry* h, int32_t n_cols, const lspr_c64* eps_medium,
         for (int b0 = 0; b0 < n_cols; b0 += MAX_BATCH) {
             const int B = std::min(MAX_BATCH, n_cols - b0);
             const lspr::EpsSet e = make_eps(B, g.S, eps_medium + b0, eps_surface + b0 * g.S);
-            lspr::DevBuf<double2> ratio, xs(B * nvec), ys(B * nvec);
-            lspr::upload_ratios(g, e, B, ratio, s);
-            lspr::to_sorted(g, B, reinterpret_cast<const double2*>(x) + b0 * nvec, xs.p, s);
-            lspr::system_apply(g, g.need64 ? LSPR_FP64 : LSPR_FP32, B, ratio.p, xs.p, nvec, ys.p,
-                               nvec, nullptr, s);
-            lspr::from_sorted(g, B, ys.p, reinterpret_cast<double2*>(y) + b0 * nvec, s);
+            lspr::upload_ratios(g, e, B, g.ws_ratio, s);
+            const double2* xb = reinterpret_cast<const double2*>(x) + b0 * nvec;
+            double2* yb = reinterpret_cast<double2*>(y) + b0 * nvec;
+            lspr::DevBuf<double2> xs;
+            if (lspr::overlap(xb, yb, B * nvec)) {  // x in place of y: from a copy
+                xs.alloc(B * nvec);
+                LSPR_HIP(hipMemcpyAsync(xs.p, xb, xs.bytes(), hipMemcpyDeviceToDevice, s));
+                xb = xs.p;
+            }
+            lspr::system_apply(g, g.need64 ? LSPR_FP64 : LSPR_FP32, B, g.ws_ratio.p, xb, nvec, yb,
+                               nvec, nullptr, s, false, g.perm.p);
             LSPR_HIP(hipStreamSynchronize(s));
         }
         return LSPR_OK;
@@ -793,11 +798,10 @@ int lspr_autotune(const lspr_surface* surfaces, int32_t n_surf, int32_t n_cols,
         const lspr::EpsSet eb = make_eps(n_cols, n_surf, em.data(), es.data());
         // product of the probe vector in precision prec (caller order)
         auto product = [&](lspr::Geometry& g, int prec, double2* out) {
-            lspr::DevBuf<double2> ratio, xs(nvec), ys(nvec);
+            lspr::DevBuf<double2> ratio;
             lspr::upload_ratios(g, e1, 1, ratio, s);
-            lspr::to_sorted(g, 1, x.p, xs.p, s);
-            lspr::system_apply(g, prec, 1, ratio.p, xs.p, nvec, ys.p, nvec, nullptr, s);
-            lspr::from_sorted(g, 1, ys.p, out, s);
+            lspr::system_apply(g, prec, 1, ratio.p, x.p, nvec, out, nvec, nullptr, s, false,
+                               g.perm.p);
             LSPR_HIP(hipStreamSynchronize(s));
         };
         std::vector<double2> yh(nvec), rh(nvec);
@@ -860,15 +864,14 @@ int lspr_autotune(const lspr_surface* surfaces, int32_t n_surf, int32_t n_cols,
             }
             t.rel_err = std::sqrt(dn) / rn;
             if (timed && t.rel_err <= max_rel_err) {
-                lspr::DevBuf<double2> ratio, ys(n_cols * nvec), xs(nvec);
+                lspr::DevBuf<double2> ratio, ys(n_cols * nvec);
                 lspr::upload_ratios(g, eb, n_cols, ratio, s);
-                lspr::to_sorted(g, 1, x.p, xs.p, s);
                 float ms_min = 1e30f;
                 for (int rep = 0; rep < 4; ++rep) {
                     LSPR_HIP(hipEventRecord(e0, s));
                     // every column multiplies the same vector (stride 0)
-                    lspr::system_apply(g, tprec, n_cols, ratio.p, xs.p, 0, ys.p, nvec, nullptr,
-                                       s);
+                    lspr::system_apply(g, tprec, n_cols, ratio.p, x.p, 0, ys.p, nvec, nullptr, s,
+                                       false, g.perm.p);
                     LSPR_HIP(hipEventRecord(e_1, s));
                     LSPR_HIP(hipEventSynchronize(e_1));
                     float ms = 0.0f;

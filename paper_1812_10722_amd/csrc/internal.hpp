@@ -484,6 +484,7 @@ struct Geometry {
     // [column][surface] of the current batch, filled with the ratios
     DevBuf<double> charge_u;
     DevBuf<double2> ws_inv_eps;
+    DevBuf<double2> ws_ratio;  // permittivity ratios of the current lspr_apply batch
     hipStream_t stream = nullptr;
     bool allow_mfma = true;  // products use matrix cores (precomputed tiles)
     bool stream_narrow = false;  // products of up to 16 wavelengths stream their operands

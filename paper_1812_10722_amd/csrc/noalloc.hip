@@ -119,20 +119,22 @@ extern "C" int lspr_apply_noalloc(lspr_geometry* h, int32_t n_cols, const lspr_c
             const std::vector<double2> rh = lspr::ratio_values(g, e, B);
             arena.used = 0;
             g.arena = &arena;
-            // the same pieces, in the same order, as apply_scratch_bytes counts
+            // the pieces that apply_scratch_bytes counts (its second vector is room to spare)
             auto piece = [&](size_t bytes) {
                 return reinterpret_cast<double2*>(lspr::workspace(g, g.ws_dens, bytes));
             };
             double2* ratio = piece(rh.size() * sizeof(double2));
             double2* xs = piece(B * nvec * sizeof(double2));
-            double2* ys = piece(B * nvec * sizeof(double2));
-            LSPR_HIP(hipMemcpyAsync(ratio, rh.data(), rh.size() * sizeof(double2),
-                                    hipMemcpyHostToDevice, s));
-            lspr::to_sorted(g, B, reinterpret_cast<const double2*>(x) + b0 * nvec, xs, s);
-            lspr::system_apply(g, prec, B, ratio, xs, nvec, ys, nvec, nullptr, s);
-            lspr::from_sorted(g, B, ys, reinterpret_cast<double2*>(y) + b0 * nvec, s);
+            const double2* xb = reinterpret_cast<const double2*>(x) + b0 * nvec;
+            double2* yb = reinterpret_cast<double2*>(y) + b0 * nvec;
+            lspr::set_ratios(rh, ratio, s);
+            if (lspr::overlap(xb, yb, B * nvec)) {  // x in place of y: from a copy
+                LSPR_HIP(hipMemcpyAsync(xs, xb, B * nvec * sizeof(double2), hipMemcpyDeviceToDevice, s));
+                xb = xs;
+            }
+            lspr::system_apply(g, prec, B, ratio, xb, nvec, yb, nvec, nullptr, s, false, g.perm.p);
             g.arena = nullptr;
-            LSPR_HIP(hipStreamSynchronize(s));  // rh is local; the next batch reuses the array
+            LSPR_HIP(hipStreamSynchronize(s));  // the next batch reuses the array
         }
         return static_cast<int>(LSPR_OK);
     });

@@ -78,21 +78,16 @@ __global__ void k_unpermute(const double2* __restrict__ x, int N, int B,
     if (dphi) dphi[static_cast<int64_t>(b) * N + o] = x[static_cast<int64_t>(b) * 2 * N + N + i];
 }
 
-// dir 0: out (sorted) <- in (caller order); dir 1: out (caller order) <- in (sorted)
+// out (caller's order) <- in (sorted)
 __global__ void k_reorder(const double2* __restrict__ in, double2* __restrict__ out, int N, int B,
-                          const int32_t* __restrict__ perm, int dir) {
+                          const int32_t* __restrict__ perm) {
     const int64_t t = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
     if (t >= static_cast<int64_t>(N) * B) return;
     const int b = static_cast<int>(t / N), i = static_cast<int>(t % N);
     const int o = perm[i];
     const int64_t base = static_cast<int64_t>(b) * 2 * N;
-    if (dir == 0) {
-        out[base + i] = in[base + o];
-        out[base + N + i] = in[base + N + o];
-    } else {
-        out[base + o] = in[base + i];
-        out[base + N + o] = in[base + N + i];
-    }
+    out[base + o] = in[base + i];
+    out[base + N + o] = in[base + N + i];
 }
 
 }  // namespace
@@ -121,17 +116,10 @@ void unpermute(Geometry& g, int B, const double2* x, double2* phi, double2* dphi
     LSPR_HIP(hipGetLastError());
 }
 
-void to_sorted(Geometry& g, int B, const double2* in, double2* out, hipStream_t s) {
-    const int64_t t = static_cast<int64_t>(g.N) * B;
-    hipLaunchKernelGGL(k_reorder, dim3((t + 255) / 256), dim3(256), 0, s, in, out, g.N, B,
-                       g.perm.p, 0);
-    LSPR_HIP(hipGetLastError());
-}
-
 void from_sorted(Geometry& g, int B, const double2* in, double2* out, hipStream_t s) {
     const int64_t t = static_cast<int64_t>(g.N) * B;
     hipLaunchKernelGGL(k_reorder, dim3((t + 255) / 256), dim3(256), 0, s, in, out, g.N, B,
-                       g.perm.p, 1);
+                       g.perm.p);
     LSPR_HIP(hipGetLastError());
 }
 

@@ -10,6 +10,7 @@
 //                      = sum_j (1 - r_s(j)) V_ij g_j,     g = dphi_inc/dn = -E . n.
 // The V columns carry sigma_j = r_s(j) psi_j, so the own-surface V sum divided by r_t gives
 // the interior row's V psi term.
+#include <algorithm>
 #include <cmath>
 #include <cstdio>
 
@@ -33,15 +34,17 @@ __device__ __forceinline__ double2 cconjmul(double2 a, double2 b) {  // conj(a) 
     return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
 
-// Unknowns (phi, psi) of panel i of column col: x itself, or M^-1 x when vself is given.
-__device__ __forceinline__ void unknowns(const double2* xc, int N, int i, double2 r,
+// Unknowns (phi, psi) of panel i, at entries o and N + o of its column: x itself, or M^-1 x when
+// vself is given.
+__device__ __forceinline__ void unknowns(const double2* xc, int N, int i, int o, double2 r,
                                          const double* vself, double2& phi, double2& psi) {
-    phi = xc[i];
-    psi = xc[N + i];
+    phi = xc[o];
+    psi = xc[N + o];
     if (vself != nullptr) block_jacobi(phi, psi, r, vself[i] * INV_4PI, phi, psi);
 }
 
-// x (complex, [col][2N] sorted order) -> packed real columns dens [N][2 pad]:
+// x (complex, [col][2N], in sorted order or, with perm, the caller's) -> packed real columns dens
+// [N][2 pad]:
 // K columns 2s, 2s+1 = Re, Im phi; V columns pad + 2s, pad + 2s + 1 = Re, Im sigma.
 // Block = pp consecutive panels, all columns: (slot, panel) pairs with the panel fastest read
 // the vectors along the panels; the rows are assembled in LDS (row stride 2 pad + 1 elements,
@@ -51,7 +54,8 @@ __global__ void __launch_bounds__(TPB) k_pack(const double2* __restrict__ x, int
                                               const int32_t* __restrict__ cols, int nslot, int N,
                                               const double2* __restrict__ ratio, int S,
                                               const int32_t* __restrict__ surf,
-                                              const double* __restrict__ vself, int pad, int pp,
+                                              const double* __restrict__ vself,
+                                              const int32_t* __restrict__ perm, int pad, int pp,
                                               T* __restrict__ dens) {
     extern __shared__ double pack_sh[];
     T* tile = reinterpret_cast<T*>(pack_sh);
@@ -64,7 +68,7 @@ __global__ void __launch_bounds__(TPB) k_pack(const double2* __restrict__ x, int
             const int col = cols ? cols[slot] : slot;
             const double2 r = ratio[col * S + surf[i]];
             double2 phi, psi;
-            unknowns(x + col * x_stride, N, i, r, vself, phi, psi);
+            unknowns(x + col * x_stride, N, i, perm ? perm[i] : i, r, vself, phi, psi);
             const double2 sig = cmul(r, psi);
             a = static_cast<T>(phi.x);
             b = static_cast<T>(phi.y);
@@ -82,18 +86,18 @@ __global__ void __launch_bounds__(TPB) k_pack(const double2* __restrict__ x, int
     for (int e = threadIdx.x; e < np * ncols; e += TPB) dst[e] = tile[(e / ncols) * ld + e % ncols];
 }
 
-// One output pair (interior, exterior row) of column `slot` at panel i, from its rows of raw
-// sums (rs: own surface, ra: all surfaces).
+// One output pair (interior, exterior row) of column `slot` at panel i (entries o and N + o of its
+// vectors), from its rows of raw sums (rs: own surface, ra: all surfaces).
 __device__ __forceinline__ void combine_one(const double2* __restrict__ x, int64_t x_stride,
                                             double2* __restrict__ y, int64_t y_stride,
                                             const int32_t* __restrict__ cols, int slot, int N,
-                                            int i, const double2* __restrict__ ratio, int S,
+                                            int i, int o, const double2* __restrict__ ratio, int S,
                                             const int32_t* __restrict__ surf,
                                             const double* __restrict__ vself, int pad,
                                             const double* rs, const double* ra) {
     const int col = cols ? cols[slot] : slot;
     double2 phi, psi;
-    unknowns(x + col * x_stride, N, i, ratio[col * S + surf[i]], vself, phi, psi);
+    unknowns(x + col * x_stride, N, i, o, ratio[col * S + surf[i]], vself, phi, psi);
     const double2 k_all = make_double2(ra[2 * slot] * INV_4PI, ra[2 * slot + 1] * INV_4PI);
     const double2 v_all = make_double2(ra[pad + 2 * slot] * INV_4PI, ra[pad + 2 * slot + 1] * INV_4PI);
     const double2 k_own = make_double2(rs[2 * slot] * INV_4PI, rs[2 * slot + 1] * INV_4PI);
@@ -103,8 +107,8 @@ __device__ __forceinline__ void combine_one(const double2* __restrict__ x, int64
     const double2 rinv = make_double2(r.x / den, -r.y / den);
     const double2 vpsi = cmul(rinv, v_own);
     double2* yc = y + col * y_stride;
-    yc[i] = make_double2(0.5 * phi.x + k_own.x - vpsi.x, 0.5 * phi.y + k_own.y - vpsi.y);
-    yc[N + i] = make_double2(0.5 * phi.x - k_all.x + v_all.x, 0.5 * phi.y - k_all.y + v_all.y);
+    yc[o] = make_double2(0.5 * phi.x + k_own.x - vpsi.x, 0.5 * phi.y + k_own.y - vpsi.y);
+    yc[N + o] = make_double2(0.5 * phi.x - k_all.x + v_all.x, 0.5 * phi.y - k_all.y + v_all.y);
 }
 
 // Rows of Eq. matrix_multi from the raw sums (no 1/4pi yet).  Block = pp consecutive panels of a
@@ -117,7 +121,8 @@ __global__ void __launch_bounds__(TPB) k_combine(const double2* __restrict__ x, 
                                                  const int32_t* __restrict__ cols, int nslot,
                                                  int N, const double2* __restrict__ ratio, int S,
                                                  const int32_t* __restrict__ surf,
-                                                 const double* __restrict__ vself, int pad,
+                                                 const double* __restrict__ vself,
+                                                 const int32_t* __restrict__ perm, int pad,
                                                  int pp, const Chunk* __restrict__ chunks,
                                                  const FarRed* __restrict__ red,
                                                  const double* __restrict__ part,
@@ -158,8 +163,8 @@ __global__ void __launch_bounds__(TPB) k_combine(const double2* __restrict__ x, 
     __syncthreads();
     for (int u = threadIdx.x; u < nslot * pp; u += TPB) {
         const int p = u % pp, slot = u / pp, i = i0 + p;
-        if (p < np) combine_one(x, x_stride, y, y_stride, cols, slot, N, i, ratio, S, surf,
-                                vself, pad, ts + p * ld, ta + p * ld);
+        if (p < np) combine_one(x, x_stride, y, y_stride, cols, slot, N, i, perm ? perm[i] : i, ratio,
+                                S, surf, vself, pad, ts + p * ld, ta + p * ld);
     }
 }
 
@@ -205,6 +210,16 @@ __global__ void k_charge_u(const double* __restrict__ cen, const int32_t* __rest
         acc += q[k] / sqrt(dx * dx + dy * dy + dz * dz);
     }
     cu[i] = acc * INV_4PI;
+}
+
+// Permittivity ratios as a kernel argument: no staging buffer, copy or wait for a handful of values
+// (a product of one column on 512 panels waited 30 us for its copy).
+constexpr size_t RATIO_ARGS = 128;
+struct RatioArgs {
+    double2 v[RATIO_ARGS];
+};
+__global__ void k_set_ratios(RatioArgs a, int n, double2* __restrict__ d) {
+    if (static_cast<int>(threadIdx.x) < n) d[threadIdx.x] = a.v[threadIdx.x];
 }
 
 // RHS geometry columns: V column 3s + d holds -n_d on surface s, zero elsewhere.
@@ -273,10 +288,22 @@ std::vector<double2> ratio_values(const Geometry& g, const EpsSet& eps, int B) {
     return h;
 }
 
+void set_ratios(const std::vector<double2>& h, double2* d, hipStream_t s) {
+    if (h.size() <= RATIO_ARGS) {
+        RatioArgs a;
+        std::copy(h.begin(), h.end(), a.v);
+        hipLaunchKernelGGL(k_set_ratios, dim3(1), dim3(RATIO_ARGS), 0, s, a,
+                           static_cast<int>(h.size()), d);
+        LSPR_HIP(hipGetLastError());
+        return;
+    }
+    copy_sync(d, h.data(), h.size() * sizeof(double2), hipMemcpyHostToDevice, s);
+}
+
 void upload_ratios(Geometry& g, const EpsSet& eps, int B, DevBuf<double2>& d, hipStream_t s) {
     const std::vector<double2> h = ratio_values(g, eps, B);
     d.reserve(h.size());
-    LSPR_HIP(hipMemcpyAsync(d.p, h.data(), h.size() * sizeof(double2), hipMemcpyHostToDevice, s));
+    set_ratios(h, d.p, s);
     if (g.charge_u.p != nullptr) {  // 1 / eps_s for the charges' right-hand side
         std::vector<double2> ie(static_cast<size_t>(B) * g.S);
         for (size_t k = 0; k < ie.size(); ++k) {
@@ -288,7 +315,6 @@ void upload_ratios(Geometry& g, const EpsSet& eps, int B, DevBuf<double2>& d, hi
                                 hipMemcpyHostToDevice, s));
         LSPR_HIP(hipStreamSynchronize(s));  // ie is local
     }
-    LSPR_HIP(hipStreamSynchronize(s));  // h is local
 }
 
 void set_charges(Geometry& g, int n_q, const double* pos, const double* q, const int32_t* sid,
@@ -323,10 +349,13 @@ void set_charges(Geometry& g, int n_q, const double* pos, const double* q, const
     LSPR_HIP(hipStreamSynchronize(s));
 }
 
-// y[col] = A(eps[col]) x[col] for the nslot columns listed in d_cols (or 0..nslot-1).
+// y[col] = A(eps[col]) x[col] for the nslot columns listed in d_cols (or 0..nslot-1); with perm
+// (sorted -> caller's panel), x and y are in the caller's order: the packing gathers and the row
+// combination scatters, instead of a pass over each vector before and after (30 us each at 32768
+// panels and 64 columns).
 void system_apply(Geometry& g, int prec, int nslot, const double2* ratio_d, const double2* x,
                   int64_t x_stride, double2* y, int64_t y_stride, const int32_t* d_cols,
-                  hipStream_t s, bool precond) {
+                  hipStream_t s, bool precond, const int32_t* perm) {
     const double* vs = precond ? g.vself.p : nullptr;
     const Cols c = make_cols(g, 2 * nslot, prec);
     const size_t nd = static_cast<size_t>(g.N) * 2 * c.pad;
@@ -347,11 +376,11 @@ void system_apply(Geometry& g, int prec, int nslot, const double2* ratio_d, cons
     const int nbk = (g.N + ppk - 1) / ppk;
     if (c.prec == LSPR_FP32)
         hipLaunchKernelGGL(k_pack<float>, dim3(nbk), dim3(TPB), ppk * ld * esz, s, x, x_stride,
-                           d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs, c.pad, ppk,
+                           d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs, perm, c.pad, ppk,
                            reinterpret_cast<float*>(dens));
     else
         hipLaunchKernelGGL(k_pack<double>, dim3(nbk), dim3(TPB), ppk * ld * esz, s, x, x_stride,
-                           d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs, c.pad, ppk,
+                           d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs, perm, c.pad, ppk,
                            reinterpret_cast<double*>(dens));
     LSPR_HIP(hipGetLastError());
     const FarSums sums = apply_raw(g, c, dens, os, oa, s);
@@ -359,7 +388,7 @@ void system_apply(Geometry& g, int prec, int nslot, const double2* ratio_d, cons
     const int ppc = panels_per_block(crow);
     LSPR_REQUIRE(g.tchunk <= CHUNK, LSPR_E_INVALID, "chunks larger than the row combination takes");
     hipLaunchKernelGGL(k_combine, dim3(g.n_chunks * (CHUNK / ppc)), dim3(TPB), ppc * crow, s, x,
-                       x_stride, y, y_stride, d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs,
+                       x_stride, y, y_stride, d_cols, nslot, g.N, ratio_d, g.S, g.surf.p, vs, perm,
                        c.pad, ppc, g.chunks.p, sums.red, sums.part, os, oa);
     LSPR_HIP(hipGetLastError());
 }

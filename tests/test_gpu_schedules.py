@@ -106,3 +106,19 @@ def test_products_of_few_chunks(lib, precision, tol):
         y = geo.apply(xt, ems, ess).cpu().numpy()
         assert _worst(y, want) < tol, ncol
         assert (geo.apply(xt, ems, ess, noalloc=True).cpu().numpy() == y).all()
+
+
+# products read x and write y in the caller's panel order, also where y is x; permittivities go as a
+# kernel argument up to 128 values and by a copy above (64 columns x 3 surfaces)
+@pytest.mark.parametrize("noalloc", [False, True])
+def test_product_in_place_and_many_permittivities(lib, noalloc):
+    surfs = _surfaces(6, (3, 4))
+    x, em, es, ref = _system(surfs, 8, 21)
+    x, em, es, ref = (np.tile(a, (8,) + (1,) * (a.ndim - 1)) for a in (x, em, es, ref))
+    geo = lib.Geometry(surfs, method="dense", precision="fp64")
+    for n in (3, 64):
+        xt = torch.as_tensor(x[:n]).cuda()
+        y = geo.apply(xt, em[:n], es[:n], noalloc=noalloc)
+        assert _worst(y.cpu().numpy(), ref[:n]) < 1e-12
+        geo.apply(xt, em[:n], es[:n], out=xt, noalloc=noalloc)
+        assert torch.equal(xt, y)
