@@ -147,6 +147,7 @@ constexpr size_t PINNED_KEEP_BYTES = 1ull << 30;
 }  // namespace
 
 PinnedBuf pinned_take(size_t bytes) {
+    PinnedBuf b;
     {
         // the smallest free buffer that holds the request
         std::lock_guard<std::mutex> lk(pinned_mu);
@@ -156,15 +157,39 @@ PinnedBuf pinned_take(size_t bytes) {
                 (best < 0 || pinned_free[i].cap < pinned_free[best].cap))
                 best = static_cast<int>(i);
         if (best >= 0) {
-            const PinnedBuf b = pinned_free[best];
+            b = pinned_free[best];
             pinned_free.erase(pinned_free.begin() + best);
-            return b;
         }
     }
-    PinnedBuf b;
+    if (b.p != nullptr) {
+        if (b.busy != nullptr) {  // its last kernel has finished, as a rule
+            const hipError_t e = hipEventSynchronize(b.busy);
+            (void)hipEventDestroy(b.busy);
+            b.busy = nullptr;
+            if (e != hipSuccess) {
+                pinned_put(b);
+                LSPR_HIP(e);
+            }
+        }
+        return b;
+    }
     b.cap = ((bytes > 0 ? bytes : 1) + (1u << 20) - 1) & ~static_cast<size_t>((1u << 20) - 1);
-    LSPR_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.p), b.cap, hipHostMallocPortable));
+    LSPR_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.p), b.cap,
+                           hipHostMallocPortable | hipHostMallocCoherent));
     return b;
+}
+
+void pinned_put(PinnedBuf b, hipStream_t s) {
+    if (b.p == nullptr) return;
+    hipEvent_t ev = nullptr;
+    if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess ||
+        hipEventRecord(ev, s) != hipSuccess) {
+        if (ev != nullptr) (void)hipEventDestroy(ev);
+        ev = nullptr;
+        (void)hipStreamSynchronize(s);
+    }
+    b.busy = ev;
+    pinned_put(b);
 }
 
 void pinned_put(PinnedBuf b) {
@@ -184,7 +209,13 @@ void pinned_put(PinnedBuf b) {
             pinned_free.erase(pinned_free.begin() + k);
         }
     }
-    for (const PinnedBuf& f : drop) (void)hipHostFree(f.p);
+    for (const PinnedBuf& f : drop) {
+        if (f.busy != nullptr) {
+            (void)hipEventSynchronize(f.busy);
+            (void)hipEventDestroy(f.busy);
+        }
+        (void)hipHostFree(f.p);
+    }
 }
 
 size_t reusable_bytes(hipMemPool_t pool) {

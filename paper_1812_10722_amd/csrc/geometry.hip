@@ -168,8 +168,23 @@ void build_geometry(Geometry& g, const lspr_surface* surfaces, int n_surf) {
     g.N = N;
     DevBuf<double> tri_in(static_cast<size_t>(N) * 9);
     DevBuf<int32_t> surf_in(N);
+    // far rule as (b0, b1, b2, w) rows
+    std::vector<double> bary, w;
+    LSPR_REQUIRE(triangle_rule(g.K, bary, w), LSPR_E_INVALID, "unsupported k_far");
+    std::vector<double> rule(4 * g.K);
+    for (int q = 0; q < g.K; ++q) {
+        rule[4 * q] = bary[3 * q];
+        rule[4 * q + 1] = bary[3 * q + 1];
+        rule[4 * q + 2] = bary[3 * q + 2];
+        rule[4 * q + 3] = w[q];
+    }
+    DevBuf<double> rule_d(rule.size());
     DevBuf<int> bad(1);
-    LSPR_HIP(hipMemsetAsync(bad.p, 0, sizeof(int), s));
+    const int zero = 0;
+    Uploads up(s);
+    up.add(rule_d.p, rule.data(), rule.size());
+    up.add(bad.p, &zero, 1);
+    up.flush();
     for (int k = 0; k < n_surf; ++k) {
         const int n = surfaces[k].n_tri;
         hipLaunchKernelGGL(k_gather, dim3((n + TPB - 1) / TPB), dim3(TPB), 0, s,
@@ -178,15 +193,16 @@ void build_geometry(Geometry& g, const lspr_surface* surfaces, int n_surf) {
         LSPR_HIP(hipGetLastError());
     }
     int bad_h = 0;
-    LSPR_HIP(hipMemcpyAsync(&bad_h, bad.p, sizeof(int), hipMemcpyDeviceToHost, s));
     // bounding cube
     const int nb = std::min(256, (N + TPB - 1) / TPB);
     DevBuf<double> part(6 * nb);
     hipLaunchKernelGGL(k_bbox, dim3(nb), dim3(TPB), 0, s, tri_in.p, N, part.p);
     LSPR_HIP(hipGetLastError());
     std::vector<double> ph(6 * nb);
-    LSPR_HIP(hipMemcpyAsync(ph.data(), part.p, ph.size() * sizeof(double), hipMemcpyDeviceToHost, s));
-    LSPR_HIP(hipStreamSynchronize(s));
+    Downloads down(s);
+    down.add(&bad_h, bad.p, 1);
+    down.add(ph.data(), part.p, ph.size());
+    down.fetch();
     LSPR_REQUIRE(!(bad_h & 1), LSPR_E_MESH, "triangle vertex index out of range");
     LSPR_REQUIRE(!(bad_h & 2), LSPR_E_MESH, "degenerate (zero-area) panel");
     double lo[3] = {DBL_MAX, DBL_MAX, DBL_MAX}, hi[3] = {-DBL_MAX, -DBL_MAX, -DBL_MAX};
@@ -213,19 +229,6 @@ void build_geometry(Geometry& g, const lspr_surface* surfaces, int n_surf) {
     radix_sort_pairs(keys.p, g.perm.p, N, 48 + sbits, s);
     g.morton = std::move(keys);
 
-    // far rule as (b0, b1, b2, w) rows
-    std::vector<double> bary, w;
-    LSPR_REQUIRE(triangle_rule(g.K, bary, w), LSPR_E_INVALID, "unsupported k_far");
-    std::vector<double> rule(4 * g.K);
-    for (int q = 0; q < g.K; ++q) {
-        rule[4 * q] = bary[3 * q];
-        rule[4 * q + 1] = bary[3 * q + 1];
-        rule[4 * q + 2] = bary[3 * q + 2];
-        rule[4 * q + 3] = w[q];
-    }
-    DevBuf<double> rule_d(rule.size());
-    LSPR_HIP(hipMemcpyAsync(rule_d.p, rule.data(), rule.size() * sizeof(double),
-                            hipMemcpyHostToDevice, s));
     g.tri.alloc(static_cast<size_t>(N) * 9);
     g.cen.alloc(static_cast<size_t>(N) * 3);
     g.nrm.alloc(static_cast<size_t>(N) * 3);

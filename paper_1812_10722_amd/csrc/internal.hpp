@@ -190,33 +190,44 @@ inline void copy_sync(void* dst, const void* src, size_t bytes, hipMemcpyKind ki
     LSPR_HIP(hipStreamSynchronize(s));
 }
 
-// Pinned (page-locked) host staging buffers, shared by all threads and reused: a transfer from
-// or to pinned memory is one DMA, where pageable memory goes through the runtime's own staging
-// at a few GB/s.  A buffer is put back only once no transfer uses it.
+// Pinned (page-locked), coherent host buffers, shared by all threads and reused: kernels read and
+// write them directly, where pageable memory goes through the runtime's own staging.
 struct PinnedBuf {
     uint8_t* p = nullptr;
     size_t cap = 0;
+    hipEvent_t busy = nullptr;  // (kept in the pool) its last use on the device
 };
-// A free buffer of at least `bytes` (a new one, a multiple of 1 MiB, if none is free).
+// A free buffer of at least `bytes` (a new one, a multiple of 1 MiB, if none is free), no longer
+// used by the device.
 PinnedBuf pinned_take(size_t bytes);
+// Back to the pool; `s`: a stream whose queued work still uses the buffer (or nothing does).
 void pinned_put(PinnedBuf b);
+void pinned_put(PinnedBuf b, hipStream_t s);
 
-// Batched host-to-device uploads of set-up code.  add() copies host data into one pinned
-// buffer (so temporaries may be passed); flush() moves the buffer to the device in one
-// transfer and queues a device-to-device copy to each destination on `s`, so the host waits
-// once rather than once per destination.  The device staging block is kept until the next
-// flush or the object's end, both of which first wait for `s`.
+// One block of bytes to move; addresses are multiples of 16, sizes of 4.
+struct Move {
+    void* dst;
+    const void* src;
+    size_t bytes;
+};
+// Moves every block, on the device's side: one launch per 16 blocks (device or pinned memory).
+void move_blocks(const Move* m, size_t n, hipStream_t s);
+
+// Batched host-to-device uploads of set-up code.  add() copies host data into one pinned buffer (so
+// temporaries may be passed); flush() queues one kernel that reads the buffer and writes every
+// destination, instead of a transfer, a wait and a copy per destination.  The buffer goes back to
+// the pool behind that kernel, so nothing waits for it.
 class Uploads {
   public:
     explicit Uploads(hipStream_t s) : s_(s) {}
     ~Uploads() {
-        if (stage_.p) (void)hipStreamSynchronize(s_);
-        if (buf_.p) pinned_put(buf_);
+        if (buf_.p) pinned_put(buf_);  // nothing of it was queued
     }
     Uploads(const Uploads&) = delete;
     Uploads& operator=(const Uploads&) = delete;
     template <class T>
     void add(T* dst, const T* src, size_t count) {
+        static_assert(sizeof(T) % 4 == 0, "blocks move in units of 4 bytes");
         const size_t bytes = count * sizeof(T);
         if (bytes == 0) return;
         const size_t at = (used_ + 255) & ~static_cast<size_t>(255);
@@ -227,17 +238,19 @@ class Uploads {
     }
     void flush() {
         if (items_.empty()) return;
-        if (stage_.p) {
-            LSPR_HIP(hipStreamSynchronize(s_));
-            stage_.release();
-        }
-        stage_.alloc(used_);
-        copy_sync(stage_.p, buf_.p, used_, hipMemcpyHostToDevice, s_);  // buf_ free again
-        for (const Item& it : items_)
-            LSPR_HIP(hipMemcpyAsync(it.dst, stage_.p + it.at, it.bytes, hipMemcpyDeviceToDevice,
-                                    s_));
+        std::vector<Move> m;
+        for (const Item& it : items_) m.push_back({it.dst, buf_.p + it.at, it.bytes});
         items_.clear();
         used_ = 0;
+        const PinnedBuf b = buf_;
+        buf_ = PinnedBuf{};
+        try {
+            move_blocks(m.data(), m.size(), s_);
+        } catch (...) {
+            pinned_put(b, s_);
+            throw;
+        }
+        pinned_put(b, s_);
     }
 
   private:
@@ -256,18 +269,17 @@ class Uploads {
     PinnedBuf buf_;
     size_t used_ = 0;
     std::vector<Item> items_;
-    DevBuf<uint8_t> stage_;
 };
 
-// Batched device-to-host downloads: add() records a destination; fetch() gathers the sources
-// into one device block (device-to-device copies queued on `s`), reads it back in one transfer
-// into a pinned buffer and fills every destination.  The sources must be ready in the stream
-// order of `s`.
+// Batched device-to-host downloads: add() records a destination; fetch() queues one kernel that
+// writes every source into a pinned buffer, waits once and fills every destination.  The sources
+// must be ready in the stream order of `s`.
 class Downloads {
   public:
     explicit Downloads(hipStream_t s) : s_(s) {}
     template <class T>
     void add(T* dst, const T* src, size_t count) {
+        static_assert(sizeof(T) % 4 == 0, "blocks move in units of 4 bytes");
         const size_t bytes = count * sizeof(T);
         if (bytes == 0) return;
         const size_t at = (total_ + 255) & ~static_cast<size_t>(255);
@@ -276,15 +288,14 @@ class Downloads {
     }
     void fetch() {
         if (items_.empty()) return;
-        DevBuf<uint8_t> stage(total_);
-        for (const Item& it : items_)
-            LSPR_HIP(hipMemcpyAsync(stage.p + it.at, it.src, it.bytes, hipMemcpyDeviceToDevice,
-                                    s_));
         const PinnedBuf host = pinned_take(total_);
         try {
-            copy_sync(host.p, stage.p, total_, hipMemcpyDeviceToHost, s_);
+            std::vector<Move> m;
+            for (const Item& it : items_) m.push_back({host.p + it.at, it.src, it.bytes});
+            move_blocks(m.data(), m.size(), s_);
+            LSPR_HIP(hipStreamSynchronize(s_));
         } catch (...) {
-            (void)hipStreamSynchronize(s_);  // no transfer into the buffer once it is put back
+            (void)hipStreamSynchronize(s_);  // no kernel writes the buffer once it is put back
             pinned_put(host);
             throw;
         }

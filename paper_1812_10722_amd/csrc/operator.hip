@@ -2328,7 +2328,9 @@ void build_p2m_tiles_p(Geometry& g, hipStream_t s, hipStream_t s2) {
         tot += 2ll * ((segs[k].end - segs[k].start + 3) / 4) * RT * 64;
     }
     g.p2m_aoff.alloc(g.n_seg);
-    copy_sync(g.p2m_aoff.p, off.data(), off.size() * sizeof(int64_t), hipMemcpyHostToDevice, s);
+    Uploads up(s);
+    up.add(g.p2m_aoff.p, off.data(), off.size());
+    up.flush();
     if (g.tileA.p != nullptr) g.p2mA.alloc(std::max<int64_t>(tot, 1));
     if (g.tileA64.p != nullptr) g.p2mA64.alloc(std::max<int64_t>(tot, 1));
     hipEvent_t ev = nullptr;
@@ -2511,7 +2513,10 @@ bool fold_near(Geometry& g, T* A, float* A32, const int32_t* dt_off, const int32
                const std::function<void()>& rebuild) {
     if (g.N == 0 || g.n_chunks == 0) return false;
     DevBuf<int32_t> miss(1);
-    LSPR_HIP(hipMemsetAsync(miss.p, 0, sizeof(int32_t), s));
+    const int32_t zero = 0;
+    Uploads up(s);
+    up.add(miss.p, &zero, 1);
+    up.flush();
     const int64_t n_fold = g.n_near + g.N;  // near-singular entries, then the self pairs
     hipLaunchKernelGGL(k_fold_near<T>, dim3(static_cast<unsigned>((n_fold + 255) / 256)), dim3(256),
                        0, s, g.chunks.p, g.n_chunks, dt_off, dt_row0, dt_tile, g.tiles.p,
@@ -2519,7 +2524,9 @@ bool fold_near(Geometry& g, T* A, float* A32, const int32_t* dt_off, const int32
                        static_cast<int64_t>(g.n_near), A, A32, miss.p);
     LSPR_HIP(hipGetLastError());
     int32_t h = 0;
-    copy_sync(&h, miss.p, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    Downloads down(s);
+    down.add(&h, miss.p, 1);
+    down.fetch();
     if (h == 0) return true;
     rebuild();
     return false;

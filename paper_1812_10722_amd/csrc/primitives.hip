@@ -1,5 +1,7 @@
 // Device primitives used by the geometry set-up: exclusive scan and a stable LSD radix sort
 // of 64-bit keys carrying 32-bit values.  Both are hand-written for 64-wide wavefronts.
+#include <algorithm>
+
 #include "primitives.hpp"
 
 namespace lspr {
@@ -137,7 +139,45 @@ __global__ void __launch_bounds__(RS_THREADS) k_rs_scatter(const uint64_t* keys_
     }
 }
 
+// Blocks of bytes moved by one launch: blockIdx.y = block, 16 bytes per thread and step.  Latency-
+// bound at set-up sizes (a copy per table cost a launch of 5-10 us each, 50 per 512-panel
+// geometry); from pinned memory it streams at the link's rate.
+constexpr int MOVES = 16;
+struct MoveArgs {
+    Move m[MOVES];
+};
+__global__ void __launch_bounds__(256) k_move(MoveArgs a) {
+    const Move m = a.m[blockIdx.y];
+    const size_t units = m.bytes / 16, step = static_cast<size_t>(gridDim.x) * 256;
+    const size_t first = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
+    const uint4* src = static_cast<const uint4*>(m.src);
+    uint4* dst = static_cast<uint4*>(m.dst);
+    for (size_t u = first; u < units; u += step) dst[u] = src[u];
+    const size_t rest = (m.bytes - 16 * units) / 4;  // the last, partial unit
+    if (first < rest)
+        reinterpret_cast<uint32_t*>(dst + units)[first] =
+            reinterpret_cast<const uint32_t*>(src + units)[first];
+}
+
 }  // namespace
+
+void move_blocks(const Move* m, size_t n, hipStream_t s) {
+    for (size_t i = 0; i < n; i += MOVES) {
+        MoveArgs a{};
+        const size_t k = std::min<size_t>(MOVES, n - i);
+        size_t most = 0;
+        for (size_t q = 0; q < k; ++q) {
+            a.m[q] = m[i + q];
+            LSPR_REQUIRE((reinterpret_cast<uintptr_t>(a.m[q].dst) | reinterpret_cast<uintptr_t>(a.m[q].src)) % 16 == 0 &&
+                             a.m[q].bytes % 4 == 0,
+                         LSPR_E_INVALID, "misaligned block");
+            most = std::max(most, a.m[q].bytes);
+        }
+        const unsigned gx = static_cast<unsigned>(std::min<size_t>(64, most / 4096 + 1));
+        hipLaunchKernelGGL(k_move, dim3(gx, static_cast<unsigned>(k)), dim3(256), 0, s, a);
+        LSPR_HIP(hipGetLastError());
+    }
+}
 
 void scan_exclusive(const int64_t* in, int64_t* out, int64_t n, hipStream_t s) {
     hipLaunchKernelGGL(k_scan_excl, dim3(1), dim3(SCAN_THREADS), 0, s, in, out, n);

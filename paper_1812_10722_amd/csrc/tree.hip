@@ -371,6 +371,13 @@ __global__ void __launch_bounds__(64) k_near_compact(const int32_t* __restrict__
     for (int q = e; q < n; q += 64) col[o + q] = slot[static_cast<size_t>(i) * cap + q];
 }
 
+// The table's size and the largest count, side by side for one read.
+__global__ void k_near_counts(const int64_t* __restrict__ nnz, const int32_t* __restrict__ most,
+                              int64_t* __restrict__ out) {
+    out[0] = *nnz;
+    out[1] = *most;
+}
+
 // Rule sums of one panel at point x (no 1/4pi): V = sum w/r, K = sum w n.(x - y)/r^3.
 __device__ inline void rule_sums(const double* v, const double* nrm, double A, const double* x,
                                  const double* rule, int K, double& sv, double& sk) {
@@ -478,11 +485,12 @@ void build_tree(Geometry& g) {
         }
     } pk;
     pk.b = pinned_take(static_cast<size_t>(g.N) * sizeof(uint64_t));
+    const Move read_keys{pk.b.p, g.morton.p, static_cast<size_t>(g.N) * sizeof(uint64_t)};
     try {
-        copy_sync(pk.b.p, g.morton.p, static_cast<size_t>(g.N) * sizeof(uint64_t),
-                  hipMemcpyDeviceToHost, s);
+        move_blocks(&read_keys, 1, s);
+        LSPR_HIP(hipStreamSynchronize(s));
     } catch (...) {
-        (void)hipStreamSynchronize(s);  // no transfer into the buffer once it is put back
+        (void)hipStreamSynchronize(s);  // no kernel writes the buffer once it is put back
         throw;
     }
     const uint64_t* keys = reinterpret_cast<const uint64_t*>(pk.b.p);
@@ -604,7 +612,9 @@ void build_lists(Geometry& g) {
     const int nc = g.n_chunks;
     // surface roots
     DevBuf<int32_t> roots(g.S);
-    LSPR_HIP(hipMemcpyAsync(roots.p, g.surf_root.data(), g.S * 4, hipMemcpyHostToDevice, s));
+    Uploads roots_up(s);
+    roots_up.add(roots.p, g.surf_root.data(), g.surf_root.size());
+    roots_up.flush();
     ListParams lp{g.method == LSPR_DENSE ? 0.0 : g.theta, 1.0 / g.threshold, g.m2p_min_panels,
                   g.S, roots.p};
     DevBuf<int32_t> mc(nc), pc(nc);
@@ -704,9 +714,19 @@ void build_near_table(Geometry& g) {
     scan_exclusive(cnt.p, cnt.p, N, s);
     int64_t nnz = 0;
     int32_t maxcnt = 0;  // largest count of a target
-    LSPR_HIP(hipMemcpyAsync(&nnz, cnt.p + N, 8, hipMemcpyDeviceToHost, s));
-    LSPR_HIP(hipMemcpyAsync(&maxcnt, np.maxcnt, 4, hipMemcpyDeviceToHost, s));
-    LSPR_HIP(hipStreamSynchronize(s));
+    struct NearCounts {
+        int64_t nnz;
+        int32_t most, pad;
+    } counts{};
+    DevBuf<NearCounts> counts_d(1);
+    hipLaunchKernelGGL(k_near_counts, dim3(1), dim3(1), 0, s, cnt.p + N, np.maxcnt,
+                       reinterpret_cast<int64_t*>(counts_d.p));
+    LSPR_HIP(hipGetLastError());
+    Downloads down(s);
+    down.add(&counts, counts_d.p, 1);
+    down.fetch();
+    nnz = counts.nnz;
+    maxcnt = counts.most;
     LSPR_REQUIRE(nnz < (1ll << 31), LSPR_E_INVALID, "near-singular table too large");
     g.n_near = nnz;
     g.near_col.alloc(std::max<int64_t>(nnz, 1));
