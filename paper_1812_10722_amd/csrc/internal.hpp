@@ -425,9 +425,7 @@ struct Geometry {
     int64_t tile_steps = 0, max_chunk_steps = 0;  // K-steps in all, and of the busiest chunk
     int64_t tile_elems = 0;  // elements of one tile store (the left factors of one precision)
     DevBuf<TileDesc> tiles;
-    DevBuf<int32_t> tile_off, tile_self;
-    DevBuf<int32_t> chunk_order;  // workgroup -> chunk of the matrix-core kernel (-1: none)
-    int n_order = 0;              // entries of chunk_order (a multiple of 8)
+    DevBuf<int32_t> tile_self;  // [n_chunks] own-surface tiles of each chunk
     // Work items of the one-operator far-field kernel, one set per launch class (0: up to 16
     // wavelengths, 1: 17 to 32, 2: more): chunks heavier than a share of the mean are cut into
     // pieces of about that cost, so that no workgroup holds the launch's tail alone.
@@ -570,15 +568,13 @@ FarSums apply_raw(Geometry& g, const Cols& c, const void* dens, double* out_self
 void finish_sums(Geometry& g, const Cols& c, const FarSums& f, double* out_self, double* out_all,
                  hipStream_t s);
 void precompute_rhs(Geometry& g);
-// Host part of the matrix-core tiles: descriptors, the tiles of each chunk, workgroup order and
-// the direct tiles sorted for the near-field fold.  Reads only host copies of the lists (and
-// sizes), so it may run on another host thread while the device builds the near-singular table.
+// Host part of the matrix-core tiles: the lengths of each chunk's tiles and the far-field work items
+// (the descriptors are written on the device, k_fill_tiles).  Reads only host copies of the lists
+// (and sizes), so it may run on another host thread while the device builds the near-singular table.
 struct TilePlan {
-    std::vector<TileDesc> tiles;
+    std::vector<uint8_t> steps;                  // K-steps of every tile, chunk by chunk
     std::vector<int32_t> toff, tself;            // per chunk: first tile, own-surface tiles
-    std::vector<int32_t> m2p_tile, m2p_chunk;    // per expansion entry: its tile and chunk
-    std::vector<int32_t> p2p_tile, p2p_chunk;    // per direct tile: its tile and chunk
-    std::vector<int32_t> order;                  // workgroup -> chunk
+    std::vector<int32_t> blk, doff;              // per chunk: 256-element blocks and direct tiles before it
     struct Items {                               // one launch class's work items
         std::vector<FarItem> items;
         std::vector<int32_t> order;
@@ -586,13 +582,12 @@ struct TilePlan {
         int n_slots = 0;
     } far[3], fine[3];                           // per launch class; fine: for few chunks
     bool has_fine[3] = {false, false, false};
-    std::vector<int32_t> dto, dtr, dti;          // per chunk: direct tiles by first panel
     int64_t aoff = 0;                            // elements of one tile store
     int64_t tile_steps = 0, max_chunk_steps = 0;
 };
 // Fills P (its vectors keep their capacity).
 void plan_tiles(const Geometry& g, TilePlan& P);
-bool plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off,
+bool plan_items(const std::vector<uint8_t>& steps, const std::vector<int32_t>& off,
                 const std::vector<int32_t>& self, double split, double tail, bool cut_self,
                 bool fine, TilePlan::Items& W);
 // Tile plans kept for reuse: a plan refilled in place keeps its host memory mapped from one

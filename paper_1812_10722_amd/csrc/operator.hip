@@ -1832,6 +1832,88 @@ k_p2m_mfma(const P2MSeg* __restrict__ segs, const int64_t* __restrict__ aoff,
 }
 
 // ---- geometry-only tiles of the far-field products (built once per geometry)
+// Descriptors of a chunk's tiles (one wave per chunk) in tile order: own surface first, each phase's
+// expansions (nsl slices of nsm K-steps) and then its direct ranges in pieces of up to 4 dmax
+// panels; the tile and chunk of every expansion entry and direct tile, for the builders; and the
+// chunk's direct tiles by first panel, for the near-field fold.  Ranges ascend within a phase and
+// the other surfaces' ranges lie before or behind the own surface's, so that order needs no sort:
+// the others before, the own, the others behind.  Latency-bound (about 10 us); on the host the
+// same work took 0.4-1.0 ms at 32768 panels, which nothing hid, and 2 MB of uploads.
+__global__ void __launch_bounds__(64)
+k_fill_tiles(const Chunk* __restrict__ chunks, const int32_t* __restrict__ m2p_off,
+             const int32_t* __restrict__ m2p_self, const int32_t* __restrict__ m2p_box,
+             const int32_t* __restrict__ p2p_off, const int32_t* __restrict__ p2p_self,
+             const Range* __restrict__ p2p_rng, const int32_t* __restrict__ mom_slot,
+             const int32_t* __restrict__ toff, const int32_t* __restrict__ blk0,
+             const int32_t* __restrict__ doff, int nsl, int nsm, int dmax, int n_terms,
+             TileDesc* __restrict__ tiles, int32_t* __restrict__ m2p_tile,
+             int32_t* __restrict__ m2p_chunk, int32_t* __restrict__ p2p_tile,
+             int32_t* __restrict__ p2p_chunk, int32_t* __restrict__ dt_row0,
+             int32_t* __restrict__ dt_tile) {
+    const int c = blockIdx.x, lane = threadIdx.x;
+    const int own0 = chunks[c].start;
+    const int mo = m2p_off[c], mm = mo + m2p_self[c], me = m2p_off[c + 1];
+    const int po = p2p_off[c], pm = po + p2p_self[c], pe = p2p_off[c + 1];
+    const int per = 4 * dmax, d0 = doff[c];
+    auto pieces = [&](const Range& R) { return (R.end - R.start + per - 1) / per; };
+    int n_own = 0, n_before = 0;  // direct tiles of the own surface, of the others before it
+    for (int e = po + lane; e < pe; e += 64) {
+        const Range R = p2p_rng[e];
+        if (e < pm) n_own += pieces(R);
+        else if (R.start < own0) n_before += pieces(R);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        n_own += __shfl_xor(n_own, off, 64);
+        n_before += __shfl_xor(n_before, off, 64);
+    }
+    int t = toff[c], blk = blk0[c], d = d0;
+    for (int phase = 0; phase < 2; ++phase) {
+        const int ma = phase == 0 ? mo : mm, mb = phase == 0 ? mm : me;
+        const int pa = phase == 0 ? po : pm, pb = phase == 0 ? pm : pe;
+        for (int e = ma + lane; e < mb; e += 64) {
+            const int first = t + (e - ma) * nsl, row = mom_slot[m2p_box[e]] * n_terms;
+            m2p_tile[e] = first;
+            m2p_chunk[e] = c;
+            for (int k = 0; k < nsl; ++k) {
+                TileDesc D;
+                D.kind = 0;
+                D.nstep = static_cast<int16_t>(nsm);
+                D.a_blk = blk + ((e - ma) * nsl + k) * nsm;
+                D.b_row0 = row + 4 * nsm * k;
+                D.b_rows = min(4 * nsm, n_terms - 4 * nsm * k);
+                tiles[first + k] = D;
+            }
+        }
+        t += (mb - ma) * nsl;
+        blk += (mb - ma) * nsl * nsm;
+        int idx = 0;  // direct tiles of this phase so far
+        for (int e = pa; e < pb; ++e) {
+            const Range R = p2p_rng[e];
+            const int n = pieces(R), len = R.end - R.start;
+            for (int q = lane; q < n; q += 64) {
+                const int p0 = R.start + per * q, rows = min(per, R.end - p0);
+                TileDesc D;
+                D.kind = 1;
+                D.nstep = static_cast<int16_t>((rows + 3) / 4);
+                D.a_blk = blk + 2 * dmax * q;
+                D.b_row0 = p0;
+                D.b_rows = rows;
+                tiles[t + q] = D;
+                p2p_tile[d + q] = t + q;
+                p2p_chunk[d + q] = c;
+                const int i = idx + q;
+                const int at = d0 + (phase == 0 ? n_before + i : (i < n_before ? i : i + n_own));
+                dt_row0[at] = p0;
+                dt_tile[at] = t + q;
+            }
+            t += n;
+            d += n;
+            idx += n;
+            blk += 2 * ((len / per) * dmax + (len % per + 3) / 4);
+        }
+    }
+}
+
 // Expansion tile of list entry e: Taylor coefficients of the chunk's 64 targets for its box.
 // tileA32 (FP64 builds, may be null): the same values rounded to FP32, at the same offsets.
 template <class T, int P>
@@ -2546,7 +2628,7 @@ int64_t estimate_tile_elems(const Geometry& g) {
     return e;
 }
 
-// Work items of the far-field kernels over one tile list (per chunk: first tile `off`, own-
+// Work items of the far-field kernels over one list of tiles (`steps`; per chunk: first tile `off`, own-
 // surface tiles `self`; a tile costs its K-steps + 4).  A chunk whose cost exceeds `split` x the
 // mean is cut at its own-surface boundary and into pieces of about equal cost (split 0: whole
 // chunks).  The items, in chunk order, are dealt to 8 XCD runs of consecutive items at equal
@@ -2568,14 +2650,14 @@ int64_t estimate_tile_elems(const Geometry& g) {
 // 262 -> 232; 12800 panels dense FP64, 64 wavelengths 1731 -> 1239; at 16200 panels it is 3 %
 // slower at 64 wavelengths, and at 512 panels 1-2 us of 12.
 constexpr double FINE_ITEMS = 512.0, FINE_COST = 120.0;
-bool plan_items(const std::vector<TileDesc>& tl, const std::vector<int32_t>& off,
+bool plan_items(const std::vector<uint8_t>& steps, const std::vector<int32_t>& off,
                 const std::vector<int32_t>& self, double split, double tail, bool cut_self,
                 bool fine, TilePlan::Items& W) {
     W.items.clear();
     W.red.clear();
     W.n_slots = 0;
     const int nc = static_cast<int>(self.size());
-    auto tcost = [&](int t) { return static_cast<double>(tl[t].nstep) + 4.0; };
+    auto tcost = [&](int t) { return static_cast<double>(steps[t]) + 4.0; };
     auto rcost = [&](int t0, int t1) {
         double cs = 0.0;
         for (int t = t0; t < t1; ++t) cs += tcost(t);
@@ -2721,116 +2803,56 @@ void plan_tiles(const Geometry& g, TilePlan& P) {
     const int nc = g.n_chunks;
     // the lists as the list builder left them on the host
     const std::vector<int32_t>&mo = g.m2p_off_h, &po = g.p2p_off_h, &ms = g.m2p_self_h,
-                                &ps = g.p2p_self_h, &mbox = g.m2p_box_h;
+                                &ps = g.p2p_self_h;
     const std::vector<Range>& rng = g.p2p_rng_h;
     LSPR_REQUIRE(static_cast<int>(mo.size()) == nc + 1 && static_cast<int>(po.size()) == nc + 1 &&
                      static_cast<int>(ms.size()) == nc && static_cast<int>(ps.size()) == nc &&
-                     static_cast<int64_t>(mbox.size()) == g.n_m2p &&
-                     static_cast<int64_t>(rng.size()) == g.n_p2p &&
-                     static_cast<int>(g.mom_slot_h.size()) == g.n_boxes,
+                     static_cast<int64_t>(rng.size()) == g.n_p2p,
                  LSPR_E_INVALID, "interaction lists missing on the host");
     const int nsl = expansion_slices(g.n_terms);      // tiles per expansion
     const int nsm = expansion_slice_steps(g.n_terms);  // K-steps of each
     const int dmax = direct_steps(g.n_terms);         // most K-steps of a direct tile
-    auto make_tile = [](int kind, int nstep, int64_t aoff, int r0, int rows) {
-        LSPR_REQUIRE(aoff % 256 == 0 && aoff / 256 < INT32_MAX, LSPR_E_INVALID,
-                     "tile store offset out of range");
-        TileDesc T;
-        T.kind = static_cast<int16_t>(kind);
-        T.nstep = static_cast<int16_t>(nstep);
-        T.a_blk = static_cast<int32_t>(aoff / 256);
-        T.b_row0 = r0;
-        T.b_rows = rows;
-        return T;
-    };
-    std::vector<TileDesc>& tiles = P.tiles;
-    std::vector<int32_t>&toff = P.toff, &tself = P.tself, &m2p_tile = P.m2p_tile,
-                         &m2p_chunk = P.m2p_chunk, &p2p_tile = P.p2p_tile, &p2p_chunk = P.p2p_chunk;
+    std::vector<uint8_t>& steps = P.steps;
+    std::vector<int32_t>&toff = P.toff, &tself = P.tself;
     toff.assign(nc + 1, 0);
     tself.assign(nc, 0);
-    m2p_tile.assign(g.n_m2p, 0);
-    m2p_chunk.assign(g.n_m2p, 0);
-    tiles.clear();
-    p2p_tile.clear();
-    p2p_chunk.clear();
-    P.aoff = 0;
-    {
-        int64_t nd = 0;  // direct tiles
-        for (const Range& r : rng) nd += (r.end - r.start + 4 * dmax - 1) / (4 * dmax);
-        tiles.reserve(static_cast<size_t>(g.n_m2p * nsl + nd));
-        p2p_tile.reserve(static_cast<size_t>(nd));
-        p2p_chunk.reserve(static_cast<size_t>(nd));
-    }
-    int64_t& aoff = P.aoff;
-    for (int c = 0; c < nc; ++c) {
-        toff[c] = static_cast<int32_t>(tiles.size());
-        for (int phase = 0; phase < 2; ++phase) {
-            const int ma = phase == 0 ? mo[c] : mo[c] + ms[c], mb = phase == 0 ? mo[c] + ms[c] : mo[c + 1];
-            const int pa = phase == 0 ? po[c] : po[c] + ps[c], pb = phase == 0 ? po[c] + ps[c] : po[c + 1];
-            for (int e = ma; e < mb; ++e) {
-                m2p_tile[e] = static_cast<int32_t>(tiles.size());  // its first slice
-                m2p_chunk[e] = c;
-                for (int k = 0; k < nsl; ++k) {
-                    const int t0 = 4 * nsm * k;
-                    tiles.push_back(make_tile(0, nsm, aoff,
-                                              g.mom_slot_h[mbox[e]] * g.n_terms + t0,
-                                              std::min(4 * nsm, g.n_terms - t0)));
-                    aoff += static_cast<int64_t>(nsm) * 256;
-                }
-            }
-            for (int e = pa; e < pb; ++e)
-                for (int p0 = rng[e].start; p0 < rng[e].end; p0 += 4 * dmax) {
-                    const int rows = std::min(4 * dmax, rng[e].end - p0), ns = (rows + 3) / 4;
-                    p2p_tile.push_back(static_cast<int32_t>(tiles.size()));
-                    p2p_chunk.push_back(c);
-                    tiles.push_back(make_tile(1, ns, aoff, p0, rows));
-                    aoff += 2 * static_cast<int64_t>(ns) * 256;
-                }
-            if (phase == 0) tself[c] = static_cast<int32_t>(tiles.size()) - toff[c];
-        }
-    }
-    toff[nc] = static_cast<int32_t>(tiles.size());
+    P.blk.assign(nc, 0);
+    P.doff.assign(nc + 1, 0);
+    steps.clear();
+    int64_t blk = 0, nd = 0;
     P.tile_steps = 0;
     P.max_chunk_steps = 0;
-    std::vector<int64_t> csteps(nc, 0);
     for (int c = 0; c < nc; ++c) {
-        for (int t = toff[c]; t < toff[c + 1]; ++t) csteps[c] += tiles[t].nstep;
-        P.tile_steps += csteps[c];
-        P.max_chunk_steps = std::max(P.max_chunk_steps, csteps[c]);
-    }
-    // Workgroup order: run x = b % 8 of consecutive chunks (the workgroups of one XCD), the runs
-    // cut at equal shares of the estimated work (K-steps plus 4 per tile for its fixed costs),
-    // heaviest chunk first within each run.
-    std::vector<double> ccost(nc);
-    double total = 0.0;
-    for (int c = 0; c < nc; ++c) {
-        ccost[c] = static_cast<double>(csteps[c]) + 4.0 * (toff[c + 1] - toff[c]);
-        total += ccost[c];
-    }
-    std::vector<std::vector<int32_t>> runs(8);
-    {
-        double acc = 0.0;
-        int x = 0;
-        for (int c = 0; c < nc; ++c) {
-            // move on to the next run once this one holds its share (every run gets a chunk
-            // while enough remain)
-            while (x < 7 && !runs[x].empty() &&
-                   (acc + 0.5 * ccost[c] > (x + 1) * total / 8.0 || nc - c <= 7 - x))
-                ++x;
-            runs[x].push_back(c);
-            acc += ccost[c];
+        toff[c] = static_cast<int32_t>(steps.size());
+        P.blk[c] = static_cast<int32_t>(blk);
+        P.doff[c] = static_cast<int32_t>(nd);
+        int64_t cs = 0;
+        for (int phase = 0; phase < 2; ++phase) {
+            const int nm = phase == 0 ? ms[c] : mo[c + 1] - mo[c] - ms[c];
+            const int pa = phase == 0 ? po[c] : po[c] + ps[c], pb = phase == 0 ? po[c] + ps[c] : po[c + 1];
+            steps.insert(steps.end(), static_cast<size_t>(nm) * nsl, static_cast<uint8_t>(nsm));
+            cs += static_cast<int64_t>(nm) * nsl * nsm;
+            blk += static_cast<int64_t>(nm) * nsl * nsm;
+            for (int e = pa; e < pb; ++e) {
+                const int n = rng[e].end - rng[e].start, full = n / (4 * dmax);
+                const int rest = (n % (4 * dmax) + 3) / 4;
+                steps.insert(steps.end(), full, static_cast<uint8_t>(dmax));
+                if (rest > 0) steps.push_back(static_cast<uint8_t>(rest));
+                const int64_t s = static_cast<int64_t>(full) * dmax + rest;
+                cs += s;
+                blk += 2 * s;
+                nd += full + (rest > 0);
+            }
+            if (phase == 0) tself[c] = static_cast<int32_t>(steps.size()) - toff[c];
         }
+        P.tile_steps += cs;
+        P.max_chunk_steps = std::max(P.max_chunk_steps, cs);
+        LSPR_REQUIRE(blk < INT32_MAX && steps.size() < static_cast<size_t>(INT32_MAX), LSPR_E_INVALID,
+                     "tile store offset out of range");
     }
-    size_t per_xcd = 0;
-    for (auto& run : runs) {
-        std::stable_sort(run.begin(), run.end(),
-                         [&](int32_t a, int32_t b) { return ccost[a] > ccost[b]; });
-        per_xcd = std::max(per_xcd, run.size());
-    }
-    std::vector<int32_t>& order = P.order;
-    order.assign(std::max<size_t>(per_xcd, 1) * 8, -1);
-    for (int x = 0; x < 8; ++x)
-        for (size_t i = 0; i < runs[x].size(); ++i) order[i * 8 + x] = runs[x][i];
+    toff[nc] = static_cast<int32_t>(steps.size());
+    P.doff[nc] = static_cast<int32_t>(nd);
+    P.aoff = blk * 256;
     // Work items per launch class (planned once for classes of equal parameters); no item spans
     // a chunk's own-surface boundary (k_far_wide needs it).
     for (int cls = 0; cls < 3; ++cls) {
@@ -2842,30 +2864,11 @@ void plan_tiles(const Geometry& g, TilePlan& P) {
             P.has_fine[cls] = P.has_fine[same];
             if (P.has_fine[cls]) P.fine[cls] = P.fine[same];
         } else {
-            plan_items(tiles, toff, tself, g.far_split[cls], g.far_tail[cls], true, false, P.far[cls]);
-            P.has_fine[cls] = plan_items(tiles, toff, tself, g.far_split[cls], g.far_tail[cls], true,
+            plan_items(steps, toff, tself, g.far_split[cls], g.far_tail[cls], true, false, P.far[cls]);
+            P.has_fine[cls] = plan_items(steps, toff, tself, g.far_split[cls], g.far_tail[cls], true,
                                          true, P.fine[cls]);
         }
     }
-    // each chunk's direct tiles sorted by first source panel, for the near-field fold
-    P.dto.assign(nc + 1, 0);
-    P.dtr.clear();
-    P.dti.clear();
-    P.dtr.reserve(p2p_tile.size());
-    P.dti.reserve(p2p_tile.size());
-    std::vector<std::pair<int32_t, int32_t>> d;
-    for (int c = 0; c < nc; ++c) {
-        P.dto[c] = static_cast<int32_t>(P.dti.size());
-        d.clear();
-        for (int t = toff[c]; t < toff[c + 1]; ++t)
-            if (tiles[t].kind == 1) d.emplace_back(tiles[t].b_row0, t);
-        std::sort(d.begin(), d.end());
-        for (auto& e : d) {
-            P.dtr.push_back(e.first);
-            P.dti.push_back(e.second);
-        }
-    }
-    P.dto[nc] = static_cast<int32_t>(P.dti.size());
 }
 
 void build_tiles(Geometry& g, const TilePlan& P) {
@@ -2876,9 +2879,7 @@ void build_tiles(Geometry& g, const TilePlan& P) {
     g.tile_steps = P.tile_steps;
     g.max_chunk_steps = P.max_chunk_steps;
     g.tile_elems = P.aoff;
-    const std::vector<int32_t>& order = P.order;
     const int64_t aoff = P.aoff;
-    g.n_order = static_cast<int>(order.size());
     // Tile stores within the budget: FP32 first (the GMRES products of the FP32 and refinement
     // modes), then FP64 with what is left.  A precision without tiles keeps the on-the-fly
     // vector-ALU kernel (e.g. a dense product on a big mesh).
@@ -2893,15 +2894,10 @@ void build_tiles(Geometry& g, const TilePlan& P) {
         g.n_tiles = 0;
         return;
     }
-    g.n_tiles = static_cast<int64_t>(P.tiles.size());
+    g.n_tiles = static_cast<int64_t>(P.steps.size());
     g.tiles.alloc(std::max<int64_t>(g.n_tiles, 1));
-    g.tile_off.alloc(nc + 1);
     g.tile_self.alloc(nc);
-    g.chunk_order.alloc(order.size());
     Uploads up(s);  // every table below in one transfer
-    up.add(g.chunk_order.p, order.data(), order.size());
-    up.add(g.tiles.p, P.tiles.data(), P.tiles.size());
-    up.add(g.tile_off.p, P.toff.data(), P.toff.size());
     up.add(g.tile_self.p, P.tself.data(), P.tself.size());
     for (int cls = 0; cls < 3; ++cls) {
         Geometry::FarPlan& fp = g.far_plan[cls];
@@ -2923,17 +2919,19 @@ void build_tiles(Geometry& g, const TilePlan& P) {
             up.add(fp.red.p, red.data(), red.size());
         }
     }
-    const int n_m2p = static_cast<int>(g.n_m2p), n_p2p = static_cast<int>(P.p2p_tile.size());
-    DevBuf<int32_t> mt(n_m2p), mc(n_m2p), pt(n_p2p), pc(n_p2p);
-    up.add(mt.p, P.m2p_tile.data(), n_m2p);
-    up.add(mc.p, P.m2p_chunk.data(), n_m2p);
-    up.add(pt.p, P.p2p_tile.data(), n_p2p);
-    up.add(pc.p, P.p2p_chunk.data(), n_p2p);
-    DevBuf<int32_t> dto_d(nc + 1), dtr_d(std::max<size_t>(P.dtr.size(), 1)), dti_d(std::max<size_t>(P.dti.size(), 1));
-    up.add(dto_d.p, P.dto.data(), P.dto.size());
-    up.add(dtr_d.p, P.dtr.data(), P.dtr.size());
-    up.add(dti_d.p, P.dti.data(), P.dti.size());
+    const int n_m2p = static_cast<int>(g.n_m2p), n_p2p = P.doff[nc];
+    DevBuf<int32_t> mt(n_m2p), mc(n_m2p), pt(n_p2p), pc(n_p2p), toff_d(nc + 1), blk_d(nc);
+    DevBuf<int32_t> dto_d(nc + 1), dtr_d(std::max(n_p2p, 1)), dti_d(std::max(n_p2p, 1));
+    up.add(toff_d.p, P.toff.data(), P.toff.size());
+    up.add(blk_d.p, P.blk.data(), P.blk.size());
+    up.add(dto_d.p, P.doff.data(), P.doff.size());
     up.flush();
+    hipLaunchKernelGGL(k_fill_tiles, dim3(nc), dim3(64), 0, s, g.chunks.p, g.m2p_off.p, g.m2p_self.p,
+                       g.m2p_box.p, g.p2p_off.p, g.p2p_self.p, g.p2p_rng.p, g.mom_slot.p, toff_d.p,
+                       blk_d.p, dto_d.p, expansion_slices(g.n_terms),
+                       expansion_slice_steps(g.n_terms), direct_steps(g.n_terms), g.n_terms,
+                       g.tiles.p, mt.p, mc.p, pt.p, pc.p, dtr_d.p, dti_d.p);
+    LSPR_HIP(hipGetLastError());
     if (keep32) g.tileA.alloc(std::max<int64_t>(aoff, 1));
     if (keep64) g.tileA64.alloc(std::max<int64_t>(aoff, 1));
     // the moments' tiles, for each precision with tiles, on a second stream beside the expansion
