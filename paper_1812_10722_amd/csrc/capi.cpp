@@ -5,7 +5,6 @@
 #include <map>
 #include <cmath>
 #include <complex>
-#include <future>
 #include <utility>
 
 #include "driver.hpp"
@@ -43,6 +42,47 @@ std::string& last_error() {
 AllocCtx& alloc_ctx() {
     thread_local AllocCtx ctx;
     return ctx;
+}
+
+uint8_t* slab_take(AllocCtx& c, size_t bytes, Slab** from) {
+    const size_t piece = (bytes + 255) & ~static_cast<size_t>(255);
+    if (c.slab == nullptr || c.slab->used + piece > c.slab->bytes) {
+        slab_close(c);
+        auto s = std::make_unique<Slab>();
+        s->bytes = c.slab_next;
+        s->stream = c.stream;
+        void* q = nullptr;
+        hipError_t e = hipMallocFromPoolAsync(&q, s->bytes, c.pool, c.stream);
+        if (e == hipErrorOutOfMemory && c.keep_big) {
+            (void)hipGetLastError();  // clear the recorded failure before retrying
+            if (big_block_flush(c.pool)) e = hipMallocFromPoolAsync(&q, s->bytes, c.pool, c.stream);
+        }
+        LSPR_HIP(e);
+        s->p = static_cast<uint8_t*>(q);
+        c.slab = s.release();
+        c.slab_next = std::min(2 * c.slab_next, SLAB_MOST);
+        c.live += static_cast<int64_t>(c.slab->bytes);
+        if (c.live > c.peak) c.peak = c.live;
+    }
+    Slab* s = c.slab;
+    uint8_t* p = s->p + s->used;
+    s->used += piece;
+    s->refs.fetch_add(1, std::memory_order_relaxed);
+    *from = s;
+    return p;
+}
+
+void slab_drop(Slab* s) {
+    if (s->refs.fetch_sub(1, std::memory_order_acq_rel) != 1) return;
+    AllocCtx& c = alloc_ctx();
+    (void)hipFreeAsync(s->p, c.free_on ? c.free_stream : s->stream);
+    c.live -= static_cast<int64_t>(s->bytes);
+    delete s;
+}
+
+void slab_close(AllocCtx& c) {
+    if (c.slab != nullptr) slab_drop(c.slab);
+    c.slab = nullptr;
 }
 
 hipMemPool_t library_pool() {
@@ -415,58 +455,62 @@ void create_geometry(Geometry& g, const lspr_surface* surfaces, int n_surf,
                      "expansion orders above 10 run only from matrix-core tiles, and they do not "
                      "fit the tile budget");
     }
-    // the host part of the tiles runs beside the moment set-up and the near-singular table
-    std::unique_ptr<lspr::TilePlan> plan_buf;
-    std::future<void> plan;
-    if (tiles) {
-        plan_buf = lspr::take_plan();
-        plan = std::async(std::launch::async,
-                          [&g, p = plan_buf.get()] { lspr::plan_tiles(g, *p); });
-    }
-    if (!g.mom_boxes.empty()) {
-        const std::vector<lspr::Range>& bh = g.box_rng_h;
-        g.mom_panels = 0;
-        for (int32_t b : g.mom_boxes) g.mom_panels += bh[b].end - bh[b].start;
-        // P2M work items: segments of at most 128 panels per expanded box
-        constexpr int SEG = 128;
-        std::vector<lspr::P2MSeg> segs;
-        std::vector<lspr::P2MRed> reds;
-        int slots = 0;
-        for (int32_t b : g.mom_boxes) {
-            const int n = bh[b].end - bh[b].start;
-            const int ns = (n + SEG - 1) / SEG;
-            const int slot0 = ns > 1 ? slots : -1;
-            const int ms = g.mom_slot_h[b];
-            for (int k = 0; k < ns; ++k)
-                segs.push_back({b, bh[b].start + k * SEG, std::min(bh[b].end, bh[b].start + (k + 1) * SEG),
-                                ns > 1 ? slots + k : -1, ms});
-            if (ns > 1) {
-                reds.push_back({b, slot0, slot0 + ns, ms});
-                slots += ns;
+    // the moment set-up and the lengths of the tiles, while the device counts near-singular pairs
+    std::unique_ptr<lspr::TilePlan> plan;
+    auto moments = [&] {
+        if (!g.mom_boxes.empty()) {
+            const std::vector<lspr::Range>& bh = g.box_rng_h;
+            g.mom_panels = 0;
+            for (int32_t b : g.mom_boxes) g.mom_panels += bh[b].end - bh[b].start;
+            // P2M work items: segments of at most 128 panels per expanded box
+            constexpr int SEG = 128;
+            std::vector<lspr::P2MSeg> segs;
+            std::vector<lspr::P2MRed> reds;
+            int slots = 0;
+            for (int32_t b : g.mom_boxes) {
+                const int n = bh[b].end - bh[b].start;
+                const int ns = (n + SEG - 1) / SEG;
+                const int slot0 = ns > 1 ? slots : -1;
+                const int ms = g.mom_slot_h[b];
+                for (int k = 0; k < ns; ++k)
+                    segs.push_back({b, bh[b].start + k * SEG, std::min(bh[b].end, bh[b].start + (k + 1) * SEG),
+                                    ns > 1 ? slots + k : -1, ms});
+                if (ns > 1) {
+                    reds.push_back({b, slot0, slot0 + ns, ms});
+                    slots += ns;
+                }
             }
+            g.n_seg = static_cast<int>(segs.size());
+            g.n_slots = slots;
+            g.n_red = static_cast<int>(reds.size());
+            g.p2m_seg.alloc(segs.size());
+            g.mom_slot.alloc(g.n_boxes);
+            lspr::Uploads up(g.stream);
+            up.add(g.p2m_seg.p, segs.data(), segs.size());
+            up.add(g.mom_slot.p, g.mom_slot_h.data(), g.mom_slot_h.size());
+            if (!reds.empty()) {
+                g.p2m_red.alloc(reds.size());
+                up.add(g.p2m_red.p, reds.data(), reds.size());
+            }
+            up.flush();
+            g.p2m_seg_h = std::move(segs);
         }
-        g.n_seg = static_cast<int>(segs.size());
-        g.n_slots = slots;
-        g.n_red = static_cast<int>(reds.size());
-        g.p2m_seg.alloc(segs.size());
-        g.mom_slot.alloc(g.n_boxes);
-        lspr::Uploads up(g.stream);
-        up.add(g.p2m_seg.p, segs.data(), segs.size());
-        up.add(g.mom_slot.p, g.mom_slot_h.data(), g.mom_slot_h.size());
-        if (!reds.empty()) {
-            g.p2m_red.alloc(reds.size());
-            up.add(g.p2m_red.p, reds.data(), reds.size());
+    };
+    lspr::build_near_table(g, [&] {
+        moments();
+        if (tiles) {
+            plan = lspr::take_plan();
+            lspr::plan_tiles(g, *plan);
         }
-        up.flush();
-        g.p2m_seg_h = std::move(segs);
-    }
-    lspr::build_near_table(g);
+    });
+    lspr::TileBuild build;
     if (tiles) {
-        plan.get();
-        lspr::build_tiles(g, *plan_buf);
-        lspr::put_plan(std::move(plan_buf));
+        lspr::build_tiles(g, *plan, build);
+        lspr::put_plan(std::move(plan));
     }
     lspr::precompute_rhs(g);
+    if (!lspr::finish_tiles(g, build)) lspr::precompute_rhs(g);
+    LSPR_HIP(hipStreamSynchronize(g.stream));
     // the host copies were only needed while building
     g.box_rng_h = {};
     g.p2p_rng_h = {};

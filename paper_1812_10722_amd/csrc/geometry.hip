@@ -251,7 +251,6 @@ void build_geometry(Geometry& g, const lspr_surface* surfaces, int n_surf) {
     }
     LSPR_HIP(hipGetLastError());
     g.surf_start = offs;
-    LSPR_HIP(hipStreamSynchronize(s));
 }
 
 }  // namespace lspr

@@ -4,8 +4,10 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <functional>
 #include <memory>
 #include <stdexcept>
 #include <string>
@@ -39,16 +41,36 @@ struct Error : std::runtime_error {
 // not synchronise the whole device on every free (the request server does this per worker; the
 // C entry points install the library's own pool for their call, see PoolScope).  While
 // `free_on` is set, pooled frees go to `free_stream` instead (a stream valid for the call).
-// live / peak count the bytes held by DevBufs allocated on this thread.
+// live / peak count the bytes held by DevBufs allocated on this thread (small ones by their slabs).
+// Small buffers share slabs: blocks of the pool that a context hands out piece by piece, never
+// again, and that go back when their last piece does (returning a pool block costs the host about
+// 10 us, and a geometry or a solve has 20 to 80 small buffers).  A piece may be released on any
+// thread; a slab is freed on the stream of the release that is its last.
+struct Slab {
+    uint8_t* p = nullptr;
+    size_t bytes = 0, used = 0;
+    hipStream_t stream = nullptr;  // allocated on
+    std::atomic<int> refs{1};      // pieces in use, and the context that still hands out pieces
+};
+constexpr size_t SLAB_PIECE = 1ull << 20;  // largest buffer taken from a slab
+constexpr size_t SLAB_FIRST = 1ull << 20, SLAB_MOST = 8ull << 20;  // slabs double up to SLAB_MOST
 struct AllocCtx {
     hipMemPool_t pool = nullptr;
     hipStream_t stream = nullptr;
     bool free_on = false;
     hipStream_t free_stream = nullptr;
     bool keep_big = false;  // large blocks of `pool` go to the block cache when released
+    Slab* slab = nullptr;   // the slab that small buffers come from
+    size_t slab_next = SLAB_FIRST;
     int64_t live = 0, peak = 0;
 };
 AllocCtx& alloc_ctx();
+// A piece of `bytes` of the context's slab (a new one when it is full); *from receives the slab.
+uint8_t* slab_take(AllocCtx& c, size_t bytes, Slab** from);
+// Gives a piece back.
+void slab_drop(Slab* s);
+// Ends the context's slab: later pieces come from another one (at the end of a call or request).
+void slab_close(AllocCtx& c);
 
 // The library's memory pool on the current device (created on first use; keeps up to 64 GiB of
 // freed memory for reuse instead of returning it at every synchronisation).
@@ -81,6 +103,8 @@ struct PoolScope {
         AllocCtx& c = alloc_ctx();
         if (c.pool != nullptr) return;
         saved = c;
+        c.slab = nullptr;
+        c.slab_next = SLAB_FIRST;
         c.pool = library_pool();
         c.stream = stream;
         c.free_on = true;
@@ -91,6 +115,7 @@ struct PoolScope {
     ~PoolScope() {
         if (!active) return;
         AllocCtx& c = alloc_ctx();
+        slab_close(c);
         const int64_t live = c.live, peak = c.peak;
         c = saved;
         c.live = live;
@@ -109,6 +134,7 @@ struct DevBuf {
     bool pooled = false;
     hipMemPool_t keep_pool = nullptr;  // set: the block goes back to the block cache
     size_t block = 0;                  // bytes of the underlying block
+    Slab* slab = nullptr;              // set: a piece of this slab
     DevBuf() = default;
     explicit DevBuf(size_t count) { alloc(count); }
     DevBuf(const DevBuf&) = delete;
@@ -124,6 +150,11 @@ struct DevBuf {
         if (count == 0) return;
         AllocCtx& c = alloc_ctx();
         const size_t b = count * sizeof(T);
+        if (c.pool && b <= SLAB_PIECE) {
+            p = reinterpret_cast<T*>(slab_take(c, b, &slab));
+            n = count;
+            return;
+        }
         if (c.pool) {
             block = b;
             void* q = nullptr;
@@ -155,7 +186,9 @@ struct DevBuf {
     // grow-only reallocation for workspaces
     void reserve(size_t count) { if (count > n) alloc(count); }
     void release() {
-        if (p) {
+        if (slab) {
+            slab_drop(slab);
+        } else if (p) {
             if (pooled) {
                 const AllocCtx& c = alloc_ctx();
                 hipStream_t fs = c.free_on ? c.free_stream : free_stream;
@@ -170,6 +203,7 @@ struct DevBuf {
         pooled = false;
         keep_pool = nullptr;
         block = 0;
+        slab = nullptr;
     }
     size_t bytes() const { return n * sizeof(T); }
     T* get() const { return p; }
@@ -177,8 +211,9 @@ struct DevBuf {
   private:
     void take(DevBuf& o) {
         p = o.p; n = o.n; free_stream = o.free_stream; pooled = o.pooled;
-        keep_pool = o.keep_pool; block = o.block;
+        keep_pool = o.keep_pool; block = o.block; slab = o.slab;
         o.p = nullptr; o.n = 0; o.pooled = false; o.keep_pool = nullptr; o.block = 0;
+        o.slab = nullptr;
     }
 };
 
@@ -549,7 +584,8 @@ void build_geometry(Geometry& g, const lspr_surface* surfaces, int n_surf);
 // ---------------------------------------------------------------- tree (tree.hip)
 void build_tree(Geometry& g);
 void build_lists(Geometry& g);
-void build_near_table(Geometry& g);
+// `meanwhile` runs on the host while the device counts the near-singular pairs.
+void build_near_table(Geometry& g, const std::function<void()>& meanwhile);
 
 // ---------------------------------------------------------------- operator (operator.hip)
 // Partial sums of the chunks a product cut into pieces, which the reader of the sums adds: per
@@ -570,7 +606,8 @@ void finish_sums(Geometry& g, const Cols& c, const FarSums& f, double* out_self,
 void precompute_rhs(Geometry& g);
 // Host part of the matrix-core tiles: the lengths of each chunk's tiles and the far-field work items
 // (the descriptors are written on the device, k_fill_tiles).  Reads only host copies of the lists
-// (and sizes), so it may run on another host thread while the device builds the near-singular table.
+// (and sizes), so it runs while the device works: the lengths while the near-singular pairs are
+// counted, the work items while the tiles are filled.
 struct TilePlan {
     std::vector<uint8_t> steps;                  // K-steps of every tile, chunk by chunk
     std::vector<int32_t> toff, tself;            // per chunk: first tile, own-surface tiles
@@ -585,8 +622,9 @@ struct TilePlan {
     int64_t aoff = 0;                            // elements of one tile store
     int64_t tile_steps = 0, max_chunk_steps = 0;
 };
-// Fills P (its vectors keep their capacity).
+// The tiles' lengths, then the work items (P's vectors keep their capacity).
 void plan_tiles(const Geometry& g, TilePlan& P);
+void plan_far(const Geometry& g, TilePlan& P);
 bool plan_items(const std::vector<uint8_t>& steps, const std::vector<int32_t>& off,
                 const std::vector<int32_t>& self, double split, double tail, bool cut_self,
                 bool fine, TilePlan::Items& W);
@@ -602,7 +640,15 @@ size_t far_part_bytes(const Geometry& g, int pad);
 bool noalloc_keeps_fitting(const Geometry& g, int cls, int before, int after);
 // Elements of one tile store, from the host lists (the size plan_tiles will find).
 int64_t estimate_tile_elems(const Geometry& g);
-// Geometry-only left factors of the matrix-core far-field product, in each needed precision.
-void build_tiles(Geometry& g, const TilePlan& plan);
+// Geometry-only left factors of the matrix-core far-field product, in each needed precision, queued
+// on g.stream (plan: plan_tiles; this calls plan_far).  The near-singular terms are folded into
+// the direct tiles; finish_tiles waits and returns false if some pair had no tile (the tiles are
+// then rebuilt without them, and results of products since are not to be used).
+struct TileBuild {
+    DevBuf<int32_t> m2p_tile, m2p_chunk, p2p_tile, p2p_chunk, missing;
+    bool folded = false;
+};
+void build_tiles(Geometry& g, TilePlan& plan, TileBuild& b);
+bool finish_tiles(Geometry& g, TileBuild& b);
 
 }  // namespace lspr

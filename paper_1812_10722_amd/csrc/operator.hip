@@ -2587,31 +2587,17 @@ void build_tiles_t(Geometry& g, T* A, float* A32, const int32_t* mt, const int32
 
 }  // namespace
 
-// Folds the near-field terms into freshly built direct tiles; false (and the tiles rebuilt
-// without them, so the separate near pass applies) if some pair had no tile.
+// Folds the near-field terms into freshly built direct tiles; pairs without a tile are counted in
+// `missing` (zeroed).
 template <class T>
-bool fold_near(Geometry& g, T* A, float* A32, const int32_t* dt_off, const int32_t* dt_row0,
-               const int32_t* dt_tile, hipStream_t s,
-               const std::function<void()>& rebuild) {
-    if (g.N == 0 || g.n_chunks == 0) return false;
-    DevBuf<int32_t> miss(1);
-    const int32_t zero = 0;
-    Uploads up(s);
-    up.add(miss.p, &zero, 1);
-    up.flush();
+void fold_near(Geometry& g, T* A, float* A32, const int32_t* dt_off, const int32_t* dt_row0,
+               const int32_t* dt_tile, int32_t* missing, hipStream_t s) {
     const int64_t n_fold = g.n_near + g.N;  // near-singular entries, then the self pairs
     hipLaunchKernelGGL(k_fold_near<T>, dim3(static_cast<unsigned>((n_fold + 255) / 256)), dim3(256),
                        0, s, g.chunks.p, g.n_chunks, dt_off, dt_row0, dt_tile, g.tiles.p,
                        g.near_off64.p, g.near_col.p, g.near_dv.p, g.near_dk.p, g.vself.p, g.N,
-                       static_cast<int64_t>(g.n_near), A, A32, miss.p);
+                       static_cast<int64_t>(g.n_near), A, A32, missing);
     LSPR_HIP(hipGetLastError());
-    int32_t h = 0;
-    Downloads down(s);
-    down.add(&h, miss.p, 1);
-    down.fetch();
-    if (h == 0) return true;
-    rebuild();
-    return false;
 }
 
 int64_t estimate_tile_elems(const Geometry& g) {
@@ -2853,6 +2839,11 @@ void plan_tiles(const Geometry& g, TilePlan& P) {
     toff[nc] = static_cast<int32_t>(steps.size());
     P.doff[nc] = static_cast<int32_t>(nd);
     P.aoff = blk * 256;
+}
+
+void plan_far(const Geometry& g, TilePlan& P) {
+    const std::vector<uint8_t>& steps = P.steps;
+    const std::vector<int32_t>&toff = P.toff, &tself = P.tself;
     // Work items per launch class (planned once for classes of equal parameters); no item spans
     // a chunk's own-surface boundary (k_far_wide needs it).
     for (int cls = 0; cls < 3; ++cls) {
@@ -2871,7 +2862,69 @@ void plan_tiles(const Geometry& g, TilePlan& P) {
     }
 }
 
-void build_tiles(Geometry& g, const TilePlan& P) {
+namespace {
+
+// Streams for the builders that run beside g.stream, kept for reuse (at most 4 idle ones; creating
+// one takes the host 200 us).
+std::mutex aux_mu;
+std::vector<std::pair<int, hipStream_t>> aux_idle;  // (device, stream)
+struct AuxStream {
+    int dev = 0;
+    hipStream_t s = nullptr;
+    bool joined = false;  // its work is ordered before the main stream's
+    AuxStream() {
+        LSPR_HIP(hipGetDevice(&dev));
+        {
+            std::lock_guard<std::mutex> lk(aux_mu);
+            for (size_t i = 0; i < aux_idle.size(); ++i)
+                if (aux_idle[i].first == dev) {
+                    s = aux_idle[i].second;
+                    aux_idle.erase(aux_idle.begin() + i);
+                    return;
+                }
+        }
+        LSPR_HIP(hipStreamCreateWithFlags(&s, hipStreamNonBlocking));
+    }
+    ~AuxStream() {
+        if (!joined) (void)hipStreamSynchronize(s);
+        {
+            std::lock_guard<std::mutex> lk(aux_mu);
+            if (aux_idle.size() < 4) {
+                aux_idle.emplace_back(dev, s);
+                return;
+            }
+        }
+        (void)hipStreamDestroy(s);
+    }
+    AuxStream(const AuxStream&) = delete;
+    AuxStream& operator=(const AuxStream&) = delete;
+    // what `to` queues from here on waits for this stream's work
+    void join(hipStream_t to) {
+        hipEvent_t ev = nullptr;
+        LSPR_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
+        const hipError_t e1 = hipEventRecord(ev, s);
+        const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(to, ev, 0) : e1;
+        (void)hipEventDestroy(ev);
+        LSPR_HIP(e2);
+        joined = true;
+    }
+};
+
+// The expansion and direct tiles of every store kept: with both, one FP64 pass fills both (the
+// FP32 tiles are the FP64 values rounded).
+void fill_stores(Geometry& g, const TileBuild& b) {
+    const int n_m2p = static_cast<int>(g.n_m2p), n_p2p = static_cast<int>(b.p2p_tile.n);
+    if (g.tileA64.p != nullptr)
+        build_tiles_t<double>(g, g.tileA64.p, g.tileA.p, b.m2p_tile.p, b.m2p_chunk.p, n_m2p,
+                              b.p2p_tile.p, b.p2p_chunk.p, n_p2p, g.stream);
+    else
+        build_tiles_t<float>(g, g.tileA.p, nullptr, b.m2p_tile.p, b.m2p_chunk.p, n_m2p, b.p2p_tile.p,
+                             b.p2p_chunk.p, n_p2p, g.stream);
+}
+
+}  // namespace
+
+void build_tiles(Geometry& g, TilePlan& P, TileBuild& b) {
     hipStream_t s = g.stream;
     const int nc = g.n_chunks;
     LSPR_REQUIRE(static_cast<int>(P.toff.size()) == nc + 1, LSPR_E_INVALID,
@@ -2897,8 +2950,60 @@ void build_tiles(Geometry& g, const TilePlan& P) {
     g.n_tiles = static_cast<int64_t>(P.steps.size());
     g.tiles.alloc(std::max<int64_t>(g.n_tiles, 1));
     g.tile_self.alloc(nc);
-    Uploads up(s);  // every table below in one transfer
+    const int n_m2p = static_cast<int>(g.n_m2p), n_p2p = P.doff[nc];
+    b.m2p_tile.alloc(n_m2p);
+    b.m2p_chunk.alloc(n_m2p);
+    b.p2p_tile.alloc(n_p2p);
+    b.p2p_chunk.alloc(n_p2p);
+    b.missing.alloc(1);
+    DevBuf<int32_t> toff_d(nc + 1), blk_d(nc);
+    DevBuf<int32_t> dto_d(nc + 1), dtr_d(std::max(n_p2p, 1)), dti_d(std::max(n_p2p, 1));
+    const int32_t zero = 0;
+    Uploads up(s);
     up.add(g.tile_self.p, P.tself.data(), P.tself.size());
+    up.add(toff_d.p, P.toff.data(), P.toff.size());
+    up.add(blk_d.p, P.blk.data(), P.blk.size());
+    up.add(dto_d.p, P.doff.data(), P.doff.size());
+    up.add(b.missing.p, &zero, 1);
+    up.flush();
+    hipLaunchKernelGGL(k_fill_tiles, dim3(nc), dim3(64), 0, s, g.chunks.p, g.m2p_off.p, g.m2p_self.p,
+                       g.m2p_box.p, g.p2p_off.p, g.p2p_self.p, g.p2p_rng.p, g.mom_slot.p, toff_d.p,
+                       blk_d.p, dto_d.p, expansion_slices(g.n_terms),
+                       expansion_slice_steps(g.n_terms), direct_steps(g.n_terms), g.n_terms,
+                       g.tiles.p, b.m2p_tile.p, b.m2p_chunk.p, b.p2p_tile.p, b.p2p_chunk.p, dtr_d.p,
+                       dti_d.p);
+    LSPR_HIP(hipGetLastError());
+    if (keep32) g.tileA.alloc(std::max<int64_t>(aoff, 1));
+    if (keep64) g.tileA64.alloc(std::max<int64_t>(aoff, 1));
+    // the moments' tiles, for each precision with tiles, on a second stream beside the expansion
+    // and direct tiles (a latency-bound builder next to two bandwidth-bound ones)
+    std::unique_ptr<AuxStream> aux;
+    if (g.n_seg > 0) {
+        aux = std::make_unique<AuxStream>();
+        switch (g.P) {
+            case 2: build_p2m_tiles_p<2>(g, s, aux->s); break;
+            case 4: build_p2m_tiles_p<4>(g, s, aux->s); break;
+            case 6: build_p2m_tiles_p<6>(g, s, aux->s); break;
+            case 8: build_p2m_tiles_p<8>(g, s, aux->s); break;
+            case 10: build_p2m_tiles_p<10>(g, s, aux->s); break;
+            case 12: build_p2m_tiles_p<12>(g, s, aux->s); break;
+            case 15: build_p2m_tiles_p<15>(g, s, aux->s); break;
+            default: throw Error(LSPR_E_INVALID, "expansion order must be 2, 4, 6, 8, 10, 12 or 15");
+        }
+    }
+    fill_stores(g, b);
+    if (g.N > 0 && nc > 0) {
+        if (keep64)
+            fold_near(g, g.tileA64.p, g.tileA.p, dto_d.p, dtr_d.p, dti_d.p, b.missing.p, s);
+        else
+            fold_near(g, g.tileA.p, static_cast<float*>(nullptr), dto_d.p, dtr_d.p, dti_d.p,
+                      b.missing.p, s);
+        b.folded = true;
+        g.near_in_tiles64 = keep64;
+        g.near_in_tiles32 = keep32;
+    }
+    // the work items, planned while the device fills the tiles
+    plan_far(g, P);
     for (int cls = 0; cls < 3; ++cls) {
         Geometry::FarPlan& fp = g.far_plan[cls];
         // (more partial sums must not make lspr_apply_noalloc refuse a product)
@@ -2919,59 +3024,20 @@ void build_tiles(Geometry& g, const TilePlan& P) {
             up.add(fp.red.p, red.data(), red.size());
         }
     }
-    const int n_m2p = static_cast<int>(g.n_m2p), n_p2p = P.doff[nc];
-    DevBuf<int32_t> mt(n_m2p), mc(n_m2p), pt(n_p2p), pc(n_p2p), toff_d(nc + 1), blk_d(nc);
-    DevBuf<int32_t> dto_d(nc + 1), dtr_d(std::max(n_p2p, 1)), dti_d(std::max(n_p2p, 1));
-    up.add(toff_d.p, P.toff.data(), P.toff.size());
-    up.add(blk_d.p, P.blk.data(), P.blk.size());
-    up.add(dto_d.p, P.doff.data(), P.doff.size());
     up.flush();
-    hipLaunchKernelGGL(k_fill_tiles, dim3(nc), dim3(64), 0, s, g.chunks.p, g.m2p_off.p, g.m2p_self.p,
-                       g.m2p_box.p, g.p2p_off.p, g.p2p_self.p, g.p2p_rng.p, g.mom_slot.p, toff_d.p,
-                       blk_d.p, dto_d.p, expansion_slices(g.n_terms),
-                       expansion_slice_steps(g.n_terms), direct_steps(g.n_terms), g.n_terms,
-                       g.tiles.p, mt.p, mc.p, pt.p, pc.p, dtr_d.p, dti_d.p);
-    LSPR_HIP(hipGetLastError());
-    if (keep32) g.tileA.alloc(std::max<int64_t>(aoff, 1));
-    if (keep64) g.tileA64.alloc(std::max<int64_t>(aoff, 1));
-    // the moments' tiles, for each precision with tiles, on a second stream beside the expansion
-    // and direct tiles (a latency-bound builder next to two bandwidth-bound ones)
-    struct AuxStream {
-        hipStream_t s = nullptr;
-        ~AuxStream() {
-            if (s) {
-                (void)hipStreamSynchronize(s);
-                (void)hipStreamDestroy(s);
-            }
-        }
-    } aux;
-    if (g.n_seg > 0) {
-        LSPR_HIP(hipStreamCreateWithFlags(&aux.s, hipStreamNonBlocking));
-        switch (g.P) {
-            case 2: build_p2m_tiles_p<2>(g, s, aux.s); break;
-            case 4: build_p2m_tiles_p<4>(g, s, aux.s); break;
-            case 6: build_p2m_tiles_p<6>(g, s, aux.s); break;
-            case 8: build_p2m_tiles_p<8>(g, s, aux.s); break;
-            case 10: build_p2m_tiles_p<10>(g, s, aux.s); break;
-            case 12: build_p2m_tiles_p<12>(g, s, aux.s); break;
-            case 15: build_p2m_tiles_p<15>(g, s, aux.s); break;
-            default: throw Error(LSPR_E_INVALID, "expansion order must be 2, 4, 6, 8, 10, 12 or 15");
-        }
-    }
-    // with both stores, one FP64 pass fills both (the FP32 tiles are the FP64 values rounded)
-    if (keep64) {
-        float* a32 = keep32 ? g.tileA.p : nullptr;
-        auto build = [&] { build_tiles_t<double>(g, g.tileA64.p, a32, mt.p, mc.p, n_m2p, pt.p, pc.p, n_p2p, s); };
-        build();
-        g.near_in_tiles64 = fold_near(g, g.tileA64.p, a32, dto_d.p, dtr_d.p, dti_d.p, s, build);
-        if (keep32) g.near_in_tiles32 = g.near_in_tiles64;
-    } else if (keep32) {
-        auto build = [&] { build_tiles_t<float>(g, g.tileA.p, nullptr, mt.p, mc.p, n_m2p, pt.p, pc.p, n_p2p, s); };
-        build();
-        g.near_in_tiles32 = fold_near(g, g.tileA.p, nullptr, dto_d.p, dtr_d.p, dti_d.p, s, build);
-    }
-    LSPR_HIP(hipStreamSynchronize(s));
-    if (aux.s) LSPR_HIP(hipStreamSynchronize(aux.s));
+    if (aux) aux->join(s);
+}
+
+bool finish_tiles(Geometry& g, TileBuild& b) {
+    if (!b.folded) return true;
+    int32_t h = 0;
+    Downloads down(g.stream);
+    down.add(&h, b.missing.p, 1);
+    down.fetch();
+    if (h == 0) return true;
+    fill_stores(g, b);
+    g.near_in_tiles64 = g.near_in_tiles32 = false;
+    return false;
 }
 
 Cols make_cols(const Geometry& g, int ncol, int prec) {

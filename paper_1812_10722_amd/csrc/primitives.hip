@@ -211,7 +211,6 @@ void radix_sort_pairs(uint64_t* keys, int32_t* vals, int64_t n, int key_bits, hi
         LSPR_HIP(hipMemcpyAsync(keys, ka, n * sizeof(uint64_t), hipMemcpyDeviceToDevice, s));
         LSPR_HIP(hipMemcpyAsync(vals, va, n * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
     }
-    LSPR_HIP(hipStreamSynchronize(s));  // temporaries are freed on return
 }
 
 }  // namespace lspr

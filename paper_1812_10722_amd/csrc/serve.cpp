@@ -143,6 +143,8 @@ void lspr_server::run(Request& r, hipStream_t s) {
         r.status = LSPR_E_INVALID;
         r.error = e.what();
     }
+    lspr::slab_close(ctx);
+    ctx.slab_next = lspr::SLAB_FIRST;
     // every buffer of the request has been released stream-ordered; wait for its work to end
     if (hipStreamSynchronize(s) != hipSuccess && r.status == LSPR_OK) {
         r.status = LSPR_E_DEVICE;

@@ -269,7 +269,6 @@ void precompute_rhs(Geometry& g) {
     hipLaunchKernelGGL(k_rhs_extract, dim3((nu + TPB - 1) / TPB), dim3(TPB), 0, s, oa.p, g.N,
                        g.S, c.pad, g.rhs_u.p);
     LSPR_HIP(hipGetLastError());
-    LSPR_HIP(hipStreamSynchronize(s));
 }
 
 std::vector<double2> ratio_values(const Geometry& g, const EpsSet& eps, int B) {

@@ -604,7 +604,6 @@ void build_tree(Geometry& g) {
     LSPR_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_chunk_stats, dim3(g.n_chunks), dim3(TPB), 0, s, g.chunks.p, g.cen.p);
     LSPR_HIP(hipGetLastError());
-    LSPR_HIP(hipStreamSynchronize(s));
 }
 
 void build_lists(Geometry& g) {
@@ -683,7 +682,7 @@ void build_lists(Geometry& g) {
     lists.fetch();
 }
 
-void build_near_table(Geometry& g) {
+void build_near_table(Geometry& g, const std::function<void()>& meanwhile) {
     hipStream_t s = g.stream;
     const int N = g.N;
     // one upload: surface roots, the fine rule and the Gauss-Legendre nodes of V_ii
@@ -722,6 +721,7 @@ void build_near_table(Geometry& g) {
     hipLaunchKernelGGL(k_near_counts, dim3(1), dim3(1), 0, s, cnt.p + N, np.maxcnt,
                        reinterpret_cast<int64_t*>(counts_d.p));
     LSPR_HIP(hipGetLastError());
+    meanwhile();
     Downloads down(s);
     down.add(&counts, counts_d.p, 1);
     down.fetch();
@@ -753,7 +753,6 @@ void build_near_table(Geometry& g) {
     hipLaunchKernelGGL(k_vself, grid, blk, 0, s, g.tri.p, g.cen.p, g.nrm.p, N, t_d.p, w_d.p,
                        g.Nk, g.vself.p);
     LSPR_HIP(hipGetLastError());
-    LSPR_HIP(hipStreamSynchronize(s));
 }
 
 }  // namespace lspr
