@@ -513,6 +513,7 @@ void create_geometry(Geometry& g, const lspr_surface* surfaces, int n_surf,
     LSPR_HIP(hipStreamSynchronize(g.stream));
     // the host copies were only needed while building
     g.box_rng_h = {};
+    g.leaf_h = {};
     g.p2p_rng_h = {};
     g.m2p_off_h = {};
     g.p2p_off_h = {};

@@ -429,6 +429,7 @@ struct Geometry {
     int max_depth = 0;
     std::vector<int> surf_start;  // S+1 offsets of each surface's panels in sorted order
     std::vector<int> surf_root;   // root box of each surface's tree
+    std::vector<int32_t> leaf_h;  // boxes of the leaves, in panel order (set-up)
     double origin[3] = {0, 0, 0}; // centre of the global bounding cube
     double half = 1.0;            // half side of the global bounding cube
 

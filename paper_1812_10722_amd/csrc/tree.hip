@@ -11,6 +11,8 @@
 // near-singular pairs (|x_i - c_j| <= L_j / threshold) and the singular self pair use other
 // rules; the table built here holds, per such pair, the fine-rule value minus the far-rule
 // value that the direct sum adds, so that the far-field kernels can treat all pairs alike.
+#include <cfloat>
+#include <climits>
 #include <cmath>
 
 #include "primitives.hpp"
@@ -252,46 +254,56 @@ __global__ void k_lists_count(const Box* __restrict__ boxes, const Chunk* __rest
     sub[t] = L;
 }
 
-// One thread per chunk: sub-list offsets in depth-first order, direct ranges merged across
-// sub-tree boundaries (within a surface), per-chunk counts.
-__global__ void k_lists_place(const SubList* __restrict__ sub, int n_chunks, int S,
-                              SubPlace* __restrict__ place, int32_t* __restrict__ m2p_cnt,
-                              int32_t* __restrict__ p2p_cnt, int32_t* __restrict__ m2p_selfc,
-                              int32_t* __restrict__ p2p_selfc, int64_t* __restrict__ pairs) {
-    const int c = blockIdx.x * blockDim.x + threadIdx.x;
-    if (c >= n_chunks) return;
+// One wave per chunk: sub-list offsets in depth-first order, direct ranges merged across
+// sub-tree boundaries (within a surface), per-chunk counts.  Lane k holds sub-tree k's part of a
+// surface, so that the walk over the sub-trees reads registers (one thread reading them one after
+// the other took 22 us, mostly memory latency).
+__global__ void __launch_bounds__(64)
+k_lists_place(const SubList* __restrict__ sub, int n_chunks, int S, SubPlace* __restrict__ place,
+              int32_t* __restrict__ m2p_cnt, int32_t* __restrict__ p2p_cnt,
+              int32_t* __restrict__ m2p_selfc, int32_t* __restrict__ p2p_selfc,
+              int64_t* __restrict__ pairs) {
+    static_assert(SUBS == 64, "one lane per sub-tree");
+    const int c = blockIdx.x, lane = threadIdx.x;
     int nm = 0, np = 0;
     int64_t pp = 0, mp = 0;
     for (int pass = 0; pass < S; ++pass) {
-        int64_t open = -1;  // sub-tree whose last direct range is still open
+        const int64_t t = (static_cast<int64_t>(c) * S + pass) * SUBS + lane;
+        const SubList L = sub[t];
+        SubPlace P{0, 0, 0, -1};
+        int open = -1;  // sub-tree whose last direct range is still open
         for (int k = 0; k < SUBS; ++k) {
-            const int64_t t = (static_cast<int64_t>(c) * S + pass) * SUBS + k;
-            const SubList L = sub[t];
-            SubPlace P{nm, np, 0, -1};
-            if (L.flags & 4) {
-                const bool join = open >= 0 && (L.flags & 1);
-                if (join) {
-                    P.skip = 1;
-                    place[open].end = L.first_end;
-                }
-                const bool only_range = L.nm == 0 && L.np == 1;
-                if (!(join && only_range)) open = (L.flags & 2) ? t : -1;
-                nm += L.nm;
-                np += L.np - P.skip;
-                pp += L.pp;
-                mp += L.mp;
-            }
-            place[t] = P;
+            const int flags = __builtin_amdgcn_readlane(L.flags, k);
+            const int km = __builtin_amdgcn_readlane(L.nm, k), kp = __builtin_amdgcn_readlane(L.np, k);
+            const int first_end = __builtin_amdgcn_readlane(L.first_end, k);
+            const bool join = (flags & 4) && open >= 0 && (flags & 1);
+            if (lane == k) P = SubPlace{nm, np, join ? 1 : 0, -1};
+            if (!(flags & 4)) continue;
+            if (join && lane == open) P.end = first_end;
+            if (!(join && km == 0 && kp == 1)) open = (flags & 2) ? k : -1;
+            nm += km;
+            np += kp - (join ? 1 : 0);
         }
-        if (pass == 0) {
+        place[t] = P;
+        if (L.flags & 4) {
+            pp += L.pp;
+            mp += L.mp;
+        }
+        if (pass == 0 && lane == 0) {
             m2p_selfc[c] = nm;
             p2p_selfc[c] = np;
         }
     }
-    m2p_cnt[c] = nm;
-    p2p_cnt[c] = np;
-    pairs[2 * c] = pp;
-    pairs[2 * c + 1] = mp;
+    for (int off = 32; off > 0; off >>= 1) {
+        pp += __shfl_xor(pp, off, 64);
+        mp += __shfl_xor(mp, off, 64);
+    }
+    if (lane == 0) {
+        m2p_cnt[c] = nm;
+        p2p_cnt[c] = np;
+        pairs[2 * c] = pp;
+        pairs[2 * c + 1] = mp;
+    }
 }
 
 __global__ void k_lists_fill(const Box* __restrict__ boxes, const Chunk* __restrict__ chunks,
@@ -312,53 +324,136 @@ __global__ void k_lists_fill(const Box* __restrict__ boxes, const Chunk* __restr
 
 struct NearParams {
     double inv_thr;
-    int S;
-    const int32_t* roots;
-    int32_t* maxcnt;    // largest count of a target (counting walk)
+    int n_leaves;
+    const int32_t* leaf;  // [n_leaves] boxes of the leaves, in panel order
+    int32_t* maxcnt;      // largest count of a target (counting walk)
 };
 
 // Near-singular source panels of every target panel, all surfaces, ascending index order.
-// Counting walk (fill false): cnt[i], and (slot not null) the first `cap` panels of target i in
-// slot[i cap ..]; filling walk: col[off[i] ..].
-__global__ void k_near(const Box* __restrict__ boxes, const double* __restrict__ cen,
-                       const double* __restrict__ area, int N, NearParams np, bool fill,
-                       int64_t* __restrict__ cnt, const int64_t* __restrict__ off,
-                       int32_t* __restrict__ col, int32_t* __restrict__ slot, int cap) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const double x = cen[3 * i], y = cen[3 * i + 1], z = cen[3 * i + 2];
-    int64_t k = fill ? off[i] : 0;
-    int n = 0;
-    for (int s = 0; s < np.S; ++s) {
-        // depth-first without a stack: into the first child, or past the box's subtree
-        int bi = np.roots[s];
-        while (bi >= 0) {
-            const Box B = boxes[bi];
-            const double dx = x - B.cx, dy = y - B.cy, dz = z - B.cz;
-            const double d = sqrt(dx * dx + dy * dy + dz * dz);
-            const bool far = d - B.rv > B.lmax * np.inv_thr * (1.0 + 1e-9) + 1e-12;
-            if (!far && B.nchild > 0) {
-                bi = B.child;
-                continue;
-            }
-            if (!far) {
-                for (int j = B.start; j < B.end; ++j) {
-                    if (j == i) continue;
-                    const double ex = x - cen[3 * j], ey = y - cen[3 * j + 1], ez = z - cen[3 * j + 2];
-                    const double dj = sqrt(ex * ex + ey * ey + ez * ez);
-                    if (dj <= sqrt(2.0 * area[j]) * np.inv_thr) {
-                        if (fill) col[k + n] = j;
-                        else if (slot != nullptr && n < cap) slot[static_cast<size_t>(i) * cap + n] = j;
-                        ++n;
+// Counting pass (fill false): cnt[i], and (slot not null) the first `cap` panels of target i in
+// slot[i cap ..]; filling pass: col[off[i] ..].
+// One workgroup per chunk, one target per lane of each of its waves.  The leaves of all trees, in
+// panel order, are tried against the bounding boxes of the chunk's targets, one per thread; the
+// workgroup makes a list of those that are left, and each wave takes a contiguous share of it: one
+// panel per lane tried against the same bounding boxes, then each panel that is left handed to all
+// lanes for the test itself.  The waves' counts, in order, are the places of their panels; a wave
+// holds up to NEAR_KEEP panels of a lane from its counting and goes through its share again only
+// where a lane has more.
+// Latency-bound.  A thread going down the trees for its own target took 303 us at 32768 panels and
+// 168 us at 512, a wave going down them for a chunk 266 and 127 us; this, with 1, 4, 8 and 16 waves:
+// 917, 316, 236, 240 and 193, 71, 43, 32 us.
+constexpr int NEAR_WAVES = 16;
+constexpr int NEAR_KEEP = 12;
+__device__ inline double from_lane(double v, int k) {
+    const long long b = __double_as_longlong(v);
+    return __hiloint2double(__builtin_amdgcn_readlane(static_cast<int>(b >> 32), k),
+                            __builtin_amdgcn_readlane(static_cast<int>(b), k));
+}
+__global__ void __launch_bounds__(64 * NEAR_WAVES)
+k_near(const Box* __restrict__ boxes, const Chunk* __restrict__ chunks,
+       const double* __restrict__ cen, const double* __restrict__ area, NearParams np, bool fill,
+       int64_t* __restrict__ cnt, const int64_t* __restrict__ off, int32_t* __restrict__ col,
+       int32_t* __restrict__ slot, int cap) {
+    __shared__ int found[NEAR_WAVES][64];
+    __shared__ int32_t keep[NEAR_WAVES][NEAR_KEEP][64];
+    __shared__ int2 list[64 * NEAR_WAVES];
+    __shared__ int left[NEAR_WAVES];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Chunk T = chunks[blockIdx.x];
+    const int i = T.start + lane;
+    const bool live = i < T.end;
+    const int ic = live ? i : T.end - 1;
+    const double x = cen[3 * ic], y = cen[3 * ic + 1], z = cen[3 * ic + 2];
+    int32_t* dst = fill ? col + (live ? off[i] : 0)
+                        : (slot != nullptr ? slot + static_cast<size_t>(ic) * cap : nullptr);
+    const int lim = fill ? INT_MAX : (slot != nullptr ? cap : 0);
+    // The targets' bounding boxes, per 8 of them: consecutive panels lie close together, but a
+    // chunk may hold two or three such runs far apart.
+    double lo[3] = {x, y, z}, hi[3] = {x, y, z};
+    for (int o = 1; o < 8; o <<= 1)
+        for (int c = 0; c < 3; ++c) {
+            lo[c] = fmin(lo[c], __shfl_xor(lo[c], o, 64));
+            hi[c] = fmax(hi[c], __shfl_xor(hi[c], o, 64));
+        }
+    // False only where no target is within r of the point.  All lanes of the wave call it together.
+    auto may_reach = [&](double px, double py, double pz, double r) {
+        double least = DBL_MAX;
+        for (int k = 0; k < 64; k += 8) {
+            const double dx = fmax(fmax(from_lane(lo[0], k) - px, px - from_lane(hi[0], k)), 0.0);
+            const double dy = fmax(fmax(from_lane(lo[1], k) - py, py - from_lane(hi[1], k)), 0.0);
+            const double dz = fmax(fmax(from_lane(lo[2], k) - pz, pz - from_lane(hi[2], k)), 0.0);
+            least = fmin(least, dx * dx + dy * dy + dz * dz);
+        }
+        return !(least > r * r * (1.0 + 1e-9));
+    };
+    int all = 0;  // this lane's panels in the rounds before
+    for (int l0 = 0; l0 < np.n_leaves; l0 += 64 * NEAR_WAVES) {
+        // leaves that may hold a panel near one of the chunk's targets
+        const int l = l0 + static_cast<int>(threadIdx.x);
+        const Box& B = boxes[np.leaf[min(l, np.n_leaves - 1)]];
+        const bool hit = may_reach(B.cx, B.cy, B.cz, B.lmax * np.inv_thr + B.rv);
+        const int2 lf = hit && l < np.n_leaves ? make_int2(B.start, B.end) : make_int2(0, 0);
+        const uint64_t take = __ballot(lf.y > lf.x);
+        if (lane == 0) left[wave] = __popcll(take);
+        __syncthreads();
+        int before = 0, n_list = 0;
+        for (int w = 0; w < NEAR_WAVES; ++w) {
+            before += w < wave ? left[w] : 0;
+            n_list += left[w];
+        }
+        if (lf.y > lf.x) list[before + __popcll(take & ((uint64_t(1) << lane) - 1))] = lf;
+        __syncthreads();
+        const int q0 = n_list * wave / NEAR_WAVES, q1 = n_list * (wave + 1) / NEAR_WAVES;
+        // calls put(j) for this lane's near panels j of the wave's share, ascending
+        auto each = [&](auto put) {
+            for (int q = q0; q < q1; ++q) {
+                const int ja = __builtin_amdgcn_readfirstlane(list[q].x);
+                const int jb = __builtin_amdgcn_readfirstlane(list[q].y);
+                for (int j0 = ja; j0 < jb; j0 += 64) {
+                    // one panel per lane: its centroid, and the reach that makes a target near it
+                    const int jl = min(j0 + lane, jb - 1);
+                    const double sx = cen[3 * jl], sy = cen[3 * jl + 1], sz = cen[3 * jl + 2];
+                    const double reach = sqrt(2.0 * area[jl]) * np.inv_thr;
+                    const bool hit = may_reach(sx, sy, sz, reach);
+                    uint64_t maybe = __ballot(hit && j0 + lane < jb);
+                    while (maybe != 0) {
+                        const int k = __builtin_ctzll(maybe);
+                        maybe &= maybe - 1;
+                        const int j = j0 + k;
+                        const double ex = x - from_lane(sx, k), ey = y - from_lane(sy, k), ez = z - from_lane(sz, k);
+                        const double dj = sqrt(ex * ex + ey * ey + ez * ez);
+                        if (live && j != i && dj <= from_lane(reach, k)) put(j);
                     }
                 }
             }
-            bi = B.next;
+        };
+        int n = 0;
+        each([&](int j) {
+            if (n < NEAR_KEEP) keep[wave][n][lane] = j;
+            ++n;
+        });
+        found[wave][lane] = n;
+        __syncthreads();
+        int at = all;
+        for (int w = 0; w < NEAR_WAVES; ++w) {
+            at += w < wave ? found[w][lane] : 0;
+            all += found[w][lane];
+        }
+        if (__ballot(n > NEAR_KEEP) == 0) {
+            for (int k = 0; k < n && at + k < lim; ++k) dst[at + k] = keep[wave][k][lane];
+        } else if (lim > 0) {
+            each([&](int j) {
+                if (at < lim) dst[at] = j;
+                ++at;
+            });
         }
     }
-    if (!fill) {
-        cnt[i] = n;
-        atomicMax(np.maxcnt, n);
+    if (!fill && wave == 0) {
+        if (live) cnt[i] = all;
+        int most = all;
+        for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
+        if (lane == 0) atomicMax(np.maxcnt, most);
     }
 }
 
@@ -564,8 +659,11 @@ void build_tree(Geometry& g) {
         for (int k = 0; k < bx[b].nchild; ++k)
             bx[bx[b].child + k].next = k + 1 < bx[b].nchild ? bx[b].child + k + 1 : bx[b].next;
     g.n_boxes = static_cast<int>(bx.size());
-    g.n_leaves = 0;
-    for (const Box& b : bx) g.n_leaves += b.nchild == 0;
+    g.leaf_h.clear();
+    for (size_t b = 0; b < bx.size(); ++b)
+        if (bx[b].nchild == 0) g.leaf_h.push_back(static_cast<int32_t>(b));
+    g.n_leaves = static_cast<int>(g.leaf_h.size());
+    std::sort(g.leaf_h.begin(), g.leaf_h.end(), [&](int32_t a, int32_t b) { return bx[a].start < bx[b].start; });
     g.box_rng_h.resize(bx.size());
     for (size_t b = 0; b < bx.size(); ++b) g.box_rng_h[b] = Range{bx[b].start, bx[b].end};
     // target chunks: consecutive panels of one surface
@@ -626,7 +724,7 @@ void build_lists(Geometry& g) {
     DevBuf<SubPlace> place(ntask);
     const dim3 grid((ntask + 63) / 64), blk(64);
     hipLaunchKernelGGL(k_lists_count, grid, blk, 0, s, g.boxes.p, g.chunks.p, nc, lp, sub.p);
-    hipLaunchKernelGGL(k_lists_place, dim3((nc + 63) / 64), dim3(64), 0, s, sub.p, nc, g.S,
+    hipLaunchKernelGGL(k_lists_place, dim3(nc), dim3(64), 0, s, sub.p, nc, g.S,
                        place.p, mc.p, pc.p, g.m2p_self.p, g.p2p_self.p, pairs.p);
     LSPR_HIP(hipGetLastError());
     std::vector<int32_t> mh(nc), ph(nc);
@@ -685,21 +783,21 @@ void build_lists(Geometry& g) {
 void build_near_table(Geometry& g, const std::function<void()>& meanwhile) {
     hipStream_t s = g.stream;
     const int N = g.N;
-    // one upload: surface roots, the fine rule and the Gauss-Legendre nodes of V_ii
+    // one upload: leaves, the fine rule and the Gauss-Legendre nodes of V_ii
     const std::vector<double> fine_h = rule_rows(g.Kf);
     std::vector<double> t, w;
     gauss_legendre(g.Nk, t, w);
-    std::vector<int32_t> roots_h(g.surf_root.begin(), g.surf_root.end());
-    roots_h.push_back(0);  // largest count
-    DevBuf<int32_t> roots(g.S + 1);
+    std::vector<int32_t> leaf_h = g.leaf_h;
+    leaf_h.push_back(0);  // largest count
+    DevBuf<int32_t> leaf(leaf_h.size());
     DevBuf<double> fine(fine_h.size()), t_d(t.size()), w_d(w.size());
     Uploads up(s);
-    up.add(roots.p, roots_h.data(), g.S + 1);
+    up.add(leaf.p, leaf_h.data(), leaf_h.size());
     up.add(fine.p, fine_h.data(), fine_h.size());
     up.add(t_d.p, t.data(), t.size());
     up.add(w_d.p, w.data(), w.size());
     up.flush();
-    NearParams np{1.0 / g.threshold, g.S, roots.p, roots.p + g.S};
+    NearParams np{1.0 / g.threshold, g.n_leaves, leaf.p, leaf.p + g.n_leaves};
     DevBuf<int64_t> cnt(N + 1);
     const dim3 grid((N + TPB - 1) / TPB), blk(TPB);
     // The counting walk keeps the first NEAR_CAP panels of each target; when no target has
@@ -707,8 +805,11 @@ void build_near_table(Geometry& g, const std::function<void()>& meanwhile) {
     constexpr int NEAR_CAP = 64;
     DevBuf<int32_t> slot;
     if (static_cast<size_t>(N) * NEAR_CAP * 4 <= (size_t(512) << 20)) slot.alloc(static_cast<size_t>(N) * NEAR_CAP);
-    hipLaunchKernelGGL(k_near, grid, blk, 0, s, g.boxes.p, g.cen.p, g.area.p, N, np, false,
-                       cnt.p, nullptr, nullptr, slot.p, NEAR_CAP);
+    auto walk = [&](bool fill, int64_t* count, const int64_t* off, int32_t* col) {
+        hipLaunchKernelGGL(k_near, dim3(g.n_chunks), dim3(64 * NEAR_WAVES), 0, s, g.boxes.p, g.chunks.p,
+                           g.cen.p, g.area.p, np, fill, count, off, col, fill ? nullptr : slot.p, NEAR_CAP);
+    };
+    walk(false, cnt.p, nullptr, nullptr);
     LSPR_HIP(hipGetLastError());
     scan_exclusive(cnt.p, cnt.p, N, s);
     int64_t nnz = 0;
@@ -736,8 +837,7 @@ void build_near_table(Geometry& g, const std::function<void()>& meanwhile) {
         hipLaunchKernelGGL(k_near_compact, dim3(N), dim3(64), 0, s, slot.p, NEAR_CAP, cnt.p,
                            g.near_col.p);
     else
-        hipLaunchKernelGGL(k_near, grid, blk, 0, s, g.boxes.p, g.cen.p, g.area.p, N, np, true,
-                           nullptr, cnt.p, g.near_col.p, nullptr, 0);
+        walk(true, nullptr, cnt.p, g.near_col.p);
     LSPR_HIP(hipGetLastError());
     g.near_off64 = std::move(cnt);
     DevBuf<int32_t> row_of(std::max<int64_t>(nnz, 1));

@@ -122,3 +122,16 @@ def test_product_in_place_and_many_permittivities(lib, noalloc):
         assert _worst(y.cpu().numpy(), ref[:n]) < 1e-12
         geo.apply(xt, em[:n], es[:n], out=xt, noalloc=noalloc)
         assert torch.equal(xt, y)
+
+
+# the search for near-singular panels: leaves of one panel (more leaves than one round of a
+# workgroup tries) and the default's, and reaches at which targets have a few, dozens (more than a
+# wave holds from its counting) and over 64 near panels (a filling pass); small meshes beside a
+# sphere, so that chunks hold panels of several shapes and sizes
+@pytest.mark.parametrize("nu,threshold,ncrit", [(1, 0.5, 0), (13, 0.5, 1), (13, 0.2, 1), (9, 0.2, 0), (9, 0.1, 3)])
+def test_near_panels_of_every_target(lib, nu, threshold, ncrit):
+    surfs = _surfaces(nu, (2, 3) if nu > 1 else ())
+    x, em, es, ref = _system(surfs, 1, 5, threshold=threshold)
+    geo = lib.Geometry(surfs, method="dense", precision="fp64", threshold=threshold, ncrit=ncrit)
+    y = geo.apply(torch.as_tensor(x).cuda(), em, es).cpu().numpy()
+    assert _worst(y, ref) < 1e-12
