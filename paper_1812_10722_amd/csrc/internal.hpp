@@ -572,6 +572,7 @@ struct Cols {
     int pad = 0;   // ncol rounded up to cpt
     bool mfma = false;  // matrix-core far-field kernel
     int prec = LSPR_FP32;  // LSPR_FP32 or LSPR_FP64 products
+    bool v_only = false;   // the K columns' results are not used (may be left unwritten)
 };
 
 // ---------------------------------------------------------------- quadrature (quadrature.cpp)

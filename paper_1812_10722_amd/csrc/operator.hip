@@ -570,7 +570,7 @@ k_far_tiles_op(const Chunk* __restrict__ chunks, const FarItem* __restrict__ ite
                const int32_t* __restrict__ item_order, const int32_t* __restrict__ tile_self,
                const TileDesc* __restrict__ tiles,
                const T* __restrict__ tileA, const T* __restrict__ dens, const T* __restrict__ mom,
-               int pad, int nwc, int halves, double* __restrict__ out_self,
+               int pad, int nwc, int halves, int nops, double* __restrict__ out_self,
                double* __restrict__ out_all, double* __restrict__ part) {
     static_assert(OPS == 1 || OPS == 2, "one or both operators per workgroup");
     constexpr int NTHR = 256 * OPS;
@@ -582,12 +582,12 @@ k_far_tiles_op(const Chunk* __restrict__ chunks, const FarItem* __restrict__ ite
     const int c16 = lane & 15, grp = lane >> 4;
     const int ncols = 2 * pad;
     // OPS = 1: 2 * halves workgroups per chunk, at b, b + 8, ...: operator j & 1, column half
-    // j >> 1.  OPS = 2: halves workgroups per chunk, column half j, operator wave / 4.
+    // j >> 1 (nops = 1, V columns only: halves workgroups, column half j).  OPS = 2: halves workgroups per chunk, column half j, operator wave / 4.
     const int b = blockIdx.x;
-    const int per = OPS == 2 ? halves : 2 * halves;
+    const int per = OPS == 2 ? halves : nops * halves;
     const int j = (b >> 3) % per;
-    const int opr = OPS == 2 ? wave >> 2 : j & 1;  // 0: K columns, 1: V columns
-    const int hj = OPS == 2 ? j : j >> 1;          // column half
+    const int opr = OPS == 2 ? wave >> 2 : (nops == 2 ? j & 1 : 1);  // 0: K columns, 1: V columns
+    const int hj = OPS == 2 || nops == 1 ? j : j >> 1;               // column half
     constexpr int G = 4 / S;                // column groups per workgroup and operator
     // wave-uniform values in scalar registers, so that the branches on them are scalar
     const int kpart = __builtin_amdgcn_readfirstlane((wave & 3) % S);  // share of the K-steps
@@ -862,7 +862,7 @@ __global__ void __launch_bounds__(512, 2)
 k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
            const int32_t* __restrict__ item_order, const int32_t* __restrict__ tile_self,
            const TileDesc* __restrict__ tiles, const float* __restrict__ tileA,
-           const float* __restrict__ dens, const float* __restrict__ mom, int pad, int nwc,
+           const float* __restrict__ dens, const float* __restrict__ mom, int pad, int nwc, int nops,
            double* __restrict__ out_self, double* __restrict__ out_all,
            double* __restrict__ part) {
     static_assert(S == 1 || S == 4 || S == 8, "waves per column group");
@@ -879,10 +879,10 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
     const int wg = wave / S, kpart = wave % S;  // column group, share of the K-steps
     const int c16 = lane & 15, grp = lane >> 4;
     const int ncols = 2 * pad;
-    // two workgroups per work item, at b and b + 8: operator (b >> 3) & 1
+    // two workgroups per work item, at b and b + 8: operator (b >> 3) & 1; nops = 1: one, the V columns
     const int b = blockIdx.x;
-    const int opr = (b >> 3) & 1;
-    const int item = item_order[(b >> 4) * 8 + (b & 7)];
+    const int opr = nops == 2 ? (b >> 3) & 1 : 1;
+    const int item = item_order[nops == 2 ? (b >> 4) * 8 + (b & 7) : b];
     if (item < 0) return;
     const FarItem I = items[item];
     const int chunk = I.chunk;
@@ -1796,11 +1796,11 @@ k_build_p2m_tiles(const Box* __restrict__ boxes, const P2MSeg* __restrict__ segs
 template <class T, int RT, int NR>
 __global__ void __launch_bounds__(256)
 k_p2m_mfma(const P2MSeg* __restrict__ segs, const int64_t* __restrict__ aoff,
-           const T* __restrict__ A, const T* __restrict__ dens, int pad, int nwc,
+           const T* __restrict__ A, const T* __restrict__ dens, int pad, int nwc, int nops,
            T* __restrict__ mom, T* __restrict__ part) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c16 = lane & 15, grp = lane >> 4;
-    const int opr = blockIdx.y & 1, wg = wave + 4 * (blockIdx.y >> 1);
+    const int opr = nops == 2 ? blockIdx.y & 1 : 1, wg = wave + 4 * (blockIdx.y / nops);
     if (wg >= nwc) return;
     const int ncols = 2 * pad;
     const int col = opr * pad + 16 * wg + c16;
@@ -2202,11 +2202,11 @@ double* far_scratch(Geometry& g, int pad) {
 }
 
 template <class T, int NSM, int S, int OPS = 1>
-void launch_far_tiles_op_s(Geometry& g, int pad, int abuf, const T* dens, const T* mom,
+void launch_far_tiles_op_s(Geometry& g, int pad, int nops, int abuf, const T* dens, const T* mom,
                            double* os, double* oa, double* part, hipStream_t s) {
     const int halves = pad > 64 ? 2 : 1;
     const Geometry::FarPlan& fp = far_plan_for(g, pad);
-    const int nblk = fp.n_order * (OPS == 2 ? 1 : 2) * halves;
+    const int nblk = fp.n_order * (OPS == 2 ? 1 : nops) * halves;
     // the left factor (OPS = 2: a direct tile's two), then (S > 1) one slot of FP64 sums per
     // column group for the final additions
     const size_t ab = OPS == 2 ? 2 * static_cast<size_t>(abuf) : abuf;
@@ -2217,7 +2217,7 @@ void launch_far_tiles_op_s(Geometry& g, int pad, int abuf, const T* dens, const 
                                   static_cast<int>(lds));
     hipLaunchKernelGGL((k_far_tiles_op<T, NSM, S, OPS>), dim3(nblk), dim3(256 * OPS), lds, s,
                        g.chunks.p, fp.items.p, fp.order.p, g.tile_self.p, g.tiles.p,
-                       tiles_of<T>(g), dens, mom, pad, pad / 16, halves, os, oa, part);
+                       tiles_of<T>(g), dens, mom, pad, pad / 16, halves, nops, os, oa, part);
     LSPR_HIP(hipGetLastError());
 }
 
@@ -2233,12 +2233,12 @@ void launch_far_stream(Geometry& g, int pad, const T* dens, const T* mom, double
 }
 
 template <int NSM, int S>
-void launch_far_wide(Geometry& g, int pad, const float* dens, const float* mom, double* os,
+void launch_far_wide(Geometry& g, int pad, int nops, const float* dens, const float* mom, double* os,
                      double* oa, double* part, hipStream_t s) {
     const Geometry::FarPlan& fp = far_plan_for(g, pad);
-    const int nblk = fp.n_order * 2;
+    const int nblk = fp.n_order * nops;
     hipLaunchKernelGGL((k_far_wide<NSM, S>), dim3(nblk), dim3(512), 0, s, g.chunks.p, fp.items.p,
-                       fp.order.p, g.tile_self.p, g.tiles.p, g.tileA.p, dens, mom, pad, pad / 16,
+                       fp.order.p, g.tile_self.p, g.tiles.p, g.tileA.p, dens, mom, pad, pad / 16, nops,
                        os, oa, part);
     LSPR_HIP(hipGetLastError());
 }
@@ -2269,7 +2269,7 @@ void launch_far_wide64(Geometry& g, int pad, const double* dens, const double* m
 // Narrow products stage their left factors in LDS, or stream their operands (k_far_stream)
 // when the geometry asks for it.
 template <class T, int NSM>
-void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T* mom,
+void launch_far_tiles_op(Geometry& g, int pad, int nops, int abuf, const T* dens, const T* mom,
                          double* os, double* oa, double* part, hipStream_t s) {
     const int groups = pad / 16;
     // FP32 products of up to 32 columns per operator at P = 8 or 15: eight-wave workgroups that
@@ -2277,21 +2277,21 @@ void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T*
     // per group, for three or four groups, need more than four waves' registers per SIMD)
     if constexpr (std::is_same<T, float>::value && (NSM == 21 || NSM == 16)) {
         if (!g.four_wave && !g.stream_narrow && !g.pair_narrow && groups <= 2) {
-            if (groups == 1) launch_far_wide<NSM, 8>(g, pad, dens, mom, os, oa, part, s);
-            else launch_far_wide<NSM, 4>(g, pad, dens, mom, os, oa, part, s);
+            if (groups == 1) launch_far_wide<NSM, 8>(g, pad, nops, dens, mom, os, oa, part, s);
+            else launch_far_wide<NSM, 4>(g, pad, nops, dens, mom, os, oa, part, s);
             return;
         }
     }
     if (groups == 1) {
         if (g.stream_narrow) launch_far_stream<T, NSM, 4>(g, pad, dens, mom, os, oa, part, s);
-        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 4, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
-        else launch_far_tiles_op_s<T, NSM, 4>(g, pad, abuf, dens, mom, os, oa, part, s);
+        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 4, 2>(g, pad, nops, abuf, dens, mom, os, oa, part, s);
+        else launch_far_tiles_op_s<T, NSM, 4>(g, pad, nops, abuf, dens, mom, os, oa, part, s);
     } else if (groups == 2) {
         if (g.stream_narrow) launch_far_stream<T, NSM, 2>(g, pad, dens, mom, os, oa, part, s);
-        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 2, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
-        else launch_far_tiles_op_s<T, NSM, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
+        else if (g.pair_narrow) launch_far_tiles_op_s<T, NSM, 2, 2>(g, pad, nops, abuf, dens, mom, os, oa, part, s);
+        else launch_far_tiles_op_s<T, NSM, 2>(g, pad, nops, abuf, dens, mom, os, oa, part, s);
     } else if (g.pair_ops) {
-        launch_far_tiles_op_s<T, NSM, 1, 2>(g, pad, abuf, dens, mom, os, oa, part, s);
+        launch_far_tiles_op_s<T, NSM, 1, 2>(g, pad, nops, abuf, dens, mom, os, oa, part, s);
     } else {
         // FP32 from P = 6: half tiles, workgroups of as many column groups as there are; two waves
         // per group at five and six groups (measured at P = 6, 8, 10 and 15: one wave is 1-20 %
@@ -2314,7 +2314,7 @@ void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T*
             // FP32 above 64 columns per operator: both column halves in one workgroup (up to
             // P = 8: at longer slices its registers exceed four waves per SIMD)
             if (groups > 4 && !g.four_wave) {
-                launch_far_wide<NSM, 1>(g, pad, dens, mom, os, oa, part, s);
+                launch_far_wide<NSM, 1>(g, pad, nops, dens, mom, os, oa, part, s);
                 return;
             }
         }
@@ -2325,18 +2325,18 @@ void launch_far_tiles_op(Geometry& g, int pad, int abuf, const T* dens, const T*
                 return;
             }
         }
-        launch_far_tiles_op_s<T, NSM, 1>(g, pad, abuf, dens, mom, os, oa, part, s);
+        launch_far_tiles_op_s<T, NSM, 1>(g, pad, nops, abuf, dens, mom, os, oa, part, s);
     }
 }
 
 template <class T>
-void launch_far_tiles(Geometry& g, int pad, const T* dens, const T* mom, double* os,
+void launch_far_tiles(Geometry& g, int pad, int nops, const T* dens, const T* mom, double* os,
                       double* oa, double* part, hipStream_t s) {
     const int nsm = expansion_slice_steps(g.n_terms);
     const int abuf = direct_steps(g.n_terms) * 256;  // largest part a workgroup stages
 #define LSPR_FAR_OP(NSM_)                                                                    \
     case NSM_:                                                                               \
-        launch_far_tiles_op<T, NSM_>(g, pad, abuf, dens, mom, os, oa, part, s);                    \
+        launch_far_tiles_op<T, NSM_>(g, pad, nops, abuf, dens, mom, os, oa, part, s);                    \
         return;
     switch (nsm) {  // K-steps of an expansion slice for P = 2, 4, 6, 12, 15, 8, 10
         LSPR_FAR_OP(3)
@@ -2355,7 +2355,7 @@ inline const float* p2m_tiles_of(const Geometry& g, const float*) { return g.p2m
 inline const double* p2m_tiles_of(const Geometry& g, const double*) { return g.p2mA64.p; }
 
 template <class T, int P>
-void launch_p2m_mfma(Geometry& g, int pad, const T* dens, T* mom, hipStream_t s) {
+void launch_p2m_mfma(Geometry& g, int pad, int nops, const T* dens, T* mom, hipStream_t s) {
     if (g.n_seg == 0) return;
     constexpr int NR = Expansion<P>::NR, RT = p2m_row_tiles<P>();
     const int ncols = 2 * pad;
@@ -2365,8 +2365,8 @@ void launch_p2m_mfma(Geometry& g, int pad, const T* dens, T* mom, hipStream_t s)
             workspace(g, g.ws_part, static_cast<size_t>(g.n_slots) * NR * ncols * sizeof(T)));
     }
     const int halves = pad > 64 ? 2 : 1;
-    hipLaunchKernelGGL((k_p2m_mfma<T, RT, NR>), dim3(g.n_seg, 2 * halves), dim3(256), 0, s,
-                       g.p2m_seg.p, g.p2m_aoff.p, p2m_tiles_of(g, dens), dens, pad, pad / 16,
+    hipLaunchKernelGGL((k_p2m_mfma<T, RT, NR>), dim3(g.n_seg, nops * halves), dim3(256), 0, s,
+                       g.p2m_seg.p, g.p2m_aoff.p, p2m_tiles_of(g, dens), dens, pad, pad / 16, nops,
                        mom, part);
     LSPR_HIP(hipGetLastError());
     if (g.n_red > 0) {
@@ -2382,14 +2382,15 @@ void launch_p2m_mfma(Geometry& g, int pad, const T* dens, T* mom, hipStream_t s)
 template <class T>
 bool launch_p2m_tiles(Geometry& g, const Cols& c, const T* dens, T* mom, hipStream_t s) {
     if (!c.mfma || p2m_tiles_of(g, dens) == nullptr) return false;
+    const int nops = c.v_only ? 1 : 2;
     switch (g.P) {
-        case 2: launch_p2m_mfma<T, 2>(g, c.pad, dens, mom, s); break;
-        case 4: launch_p2m_mfma<T, 4>(g, c.pad, dens, mom, s); break;
-        case 6: launch_p2m_mfma<T, 6>(g, c.pad, dens, mom, s); break;
-        case 8: launch_p2m_mfma<T, 8>(g, c.pad, dens, mom, s); break;
-        case 10: launch_p2m_mfma<T, 10>(g, c.pad, dens, mom, s); break;
-        case 12: launch_p2m_mfma<T, 12>(g, c.pad, dens, mom, s); break;
-        case 15: launch_p2m_mfma<T, 15>(g, c.pad, dens, mom, s); break;
+        case 2: launch_p2m_mfma<T, 2>(g, c.pad, nops, dens, mom, s); break;
+        case 4: launch_p2m_mfma<T, 4>(g, c.pad, nops, dens, mom, s); break;
+        case 6: launch_p2m_mfma<T, 6>(g, c.pad, nops, dens, mom, s); break;
+        case 8: launch_p2m_mfma<T, 8>(g, c.pad, nops, dens, mom, s); break;
+        case 10: launch_p2m_mfma<T, 10>(g, c.pad, nops, dens, mom, s); break;
+        case 12: launch_p2m_mfma<T, 12>(g, c.pad, nops, dens, mom, s); break;
+        case 15: launch_p2m_mfma<T, 15>(g, c.pad, nops, dens, mom, s); break;
         default: throw Error(LSPR_E_INVALID, "expansion order must be 2, 4, 6, 8, 10, 12 or 15");
     }
     return true;
@@ -2529,7 +2530,7 @@ FarSums apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, doubl
                          LSPR_E_INVALID, "matrix-core tiles were not built");
             sums.part = far_scratch(g, c.pad);
             if (sums.part != nullptr) sums.red = far_plan_for(g, c.pad).red.p;
-            launch_far_tiles<T>(g, c.pad, dens, mom, os, oa, const_cast<double*>(sums.part), s);
+            launch_far_tiles<T>(g, c.pad, c.v_only ? 1 : 2, dens, mom, os, oa, const_cast<double*>(sums.part), s);
         } else if (!launch_direct(g, c, dens, os, oa, s)) {
             switch (c.cpt) {
                 case 2: launch_far_cpt<T, 2>(g, c.pad, dens, mom, os, oa, s); break;

@@ -250,7 +250,11 @@ __global__ void k_rhs_extract(const double* __restrict__ out, int N, int S, int 
 void precompute_rhs(Geometry& g) {
     hipStream_t s = g.stream;
     // in FP64 whenever the geometry runs FP64 products
-    const Cols c = make_cols(g, 3 * g.S, g.need64 ? LSPR_FP64 : LSPR_FP32);
+    Cols c = make_cols(g, 3 * g.S, g.need64 ? LSPR_FP64 : LSPR_FP32);
+    // Only V is applied: a K half of the launch would read its own factors of all direct tiles (at
+    // 32768 panels, P = 8 in FP64, far field and moments took 688 and 63 us with it; without 500
+    // and 46).
+    c.v_only = true;
     const size_t nd = static_cast<size_t>(g.N) * 2 * c.pad;
     const size_t esz = c.prec == LSPR_FP32 ? 4 : 8;
     DevBuf<uint8_t> dens(nd * esz);

@@ -135,3 +135,23 @@ def test_near_panels_of_every_target(lib, nu, threshold, ncrit):
     geo = lib.Geometry(surfs, method="dense", precision="fp64", threshold=threshold, ncrit=ncrit)
     y = geo.apply(torch.as_tensor(x).cuda(), em, es).cpu().numpy()
     assert _worst(y, ref) < 1e-12
+
+
+# the right-hand side's columns run through V alone: one and two column groups per operator (3, 6 and
+# 18 columns) and both precisions, at orders whose narrow products have their own kernels; with
+# theta 0.05 every pair is summed directly (tolerances as above), with 0.5 the expansions' relative
+# truncation, theta^(p + 1), bounds the error
+@pytest.mark.parametrize("precision,tol", [("fp64", 1e-12), ("fp32", 2e-6)])
+@pytest.mark.parametrize("p", [6, 8, 15])
+@pytest.mark.parametrize("blobs", [(), (4,), (3, 4, 3, 4, 3)])
+def test_right_hand_side_through_v_alone(lib, precision, tol, p, blobs):
+    surfs = _surfaces(10, blobs)
+    v, t, sid = merge_surfaces(surfs)
+    V, K = oracle.dense_operators(v, t)
+    em, es = 1.7733, np.array([-3.38 + 0.2j] + [2.5] * len(blobs))
+    e = np.array([0.3, -0.5, 1.2])
+    _, ref = oracle.assemble_system(V, K, sid, oracle.panel_geometry(v, t)["normal"], em, es, e)
+    for theta, bound in ((0.05, tol), (0.5, max(tol, 0.5 ** (p + 1)))):
+        geo = lib.Geometry(surfs, method="treecode", precision=precision, p=p, theta=theta)
+        b = geo.rhs(np.array([em]), es[None], e).cpu().numpy()[0]
+        assert np.abs(b - ref).max() / np.abs(ref).max() < bound, theta
