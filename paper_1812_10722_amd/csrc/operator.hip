@@ -33,15 +33,13 @@ template <class T> constexpr int tile_panels() { return sizeof(T) == 8 ? 16 : 32
 
 template <class T> __device__ __forceinline__ T rsqrt_t(T x);
 template <> __device__ __forceinline__ float rsqrt_t<float>(float x) { return rsqrtf(x); }
-// FP64: the hardware estimate (about 23 correct bits) refined by two Newton steps
-// y <- y + y (1 - x y^2) / 2, each of which about doubles the correct bits (to within 1-2 ulp),
-// instead of a square root followed by a division
+// FP64: the hardware estimate (relative error below 2^-22) and one third-order step,
+// y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2: its truncation, 5 e^3 / 16 < 2^-64, is below the
+// rounding, as after two Newton steps, in five operations instead of eight.
 template <> __device__ __forceinline__ double rsqrt_t<double>(double x) {
-    double y = __builtin_amdgcn_rsq(x);
-    double e = fma(-x * y, y, 1.0);
-    y = fma(0.5 * y, e, y);
-    e = fma(-x * y, y, 1.0);
-    return fma(0.5 * y, e, y);
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = fma(-x * y, y, 1.0);
+    return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
 // Knuth's TwoSum: hi + lo += part exactly up to the final rounding.
@@ -326,15 +324,6 @@ k_far(const Chunk* __restrict__ chunks, const Box* __restrict__ boxes,
 constexpr int DW = 16;  // waves per workgroup
 constexpr int DT = 16;  // panels per partial
 
-// FP64 inverse square root: the hardware estimate (relative error below 2^-22) and one third-order
-// step, y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2: its truncation, 5 e^3 / 16 < 2^-64, is below
-// the rounding, as after two Newton steps, in five operations instead of eight.
-__device__ __forceinline__ double rsqrt_cubic(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
-    return fma(y * e, fma(0.375, e, 0.5), y);
-}
-
 template <int K, int CPT>
 __global__ void __launch_bounds__(64 * DW)
 k_direct64(const Chunk* __restrict__ chunks, const int32_t* __restrict__ p2p_off,
@@ -367,7 +356,7 @@ k_direct64(const Chunk* __restrict__ chunks, const int32_t* __restrict__ p2p_off
 #pragma unroll
         for (int g = 0; g < K; ++g) {
             const double ex = dx - r[4 + 4 * g], ey = dy - r[5 + 4 * g], ez = dz - r[6 + 4 * g];
-            const double ri = rsqrt_cubic(ex * ex + ey * ey + ez * ez);
+            const double ri = rsqrt_t<double>(ex * ex + ey * ey + ez * ez);
             const double t = r[7 + 4 * g] * ri;
             sv += t;
             sk += t * ri * ri;
@@ -1673,12 +1662,39 @@ __device__ __forceinline__ int full_term(int x, int y, int z) {
     return n * (n + 1) * (n + 2) / 6 + a * (a + 1) / 2 + (a - y);
 }
 
-// One block per segment, PB panels at a time with TPP threads each: the node polynomials of a
-// panel go to LDS (each thread a share of the terms, nodes summed in order), the kz >= 2 terms
-// are folded level by level (each destination gathers its two sources in the order of the
-// sequential fold), and the folded terms are stored.
+// Workgroup = one wave: batches of PB panels of a segment, every gridDim.y-th, TPP lanes per panel.
+// The node polynomials of a panel go to LDS (each lane a share of the terms, nodes summed in
+// order), the kz >= 2 terms are folded level by level (each destination gathers its two sources in
+// the order of the sequential fold), and the folded terms are stored, zeros past the segment's last
+// panel and the last term.  A lane's terms and fold steps are the same for every batch and are kept
+// in registers; per node and axis LDS holds the powers and their normal derivatives (the x axis
+// scaled by the node's weight) side by side, so that a term costs three reads and six operations
+// per node.  Bound by the latency of LDS and by how many panels fit there, so 32 lanes work on a
+// panel (64 where a panel's polynomials take 16 KB); with 16 lanes per panel, two waves per
+// workgroup and one workgroup per segment, 32768 panels at P = 8 took 1040 us beside the other
+// builders: 145 us.
+constexpr int P2M_PARTS = 8;  // workgroups per segment
+template <int P>
+constexpr int p2m_lanes() { return P <= 10 ? 32 : 64; }
+// fold steps of a lane at level z
+template <int P>
+constexpr int p2m_fold_steps(int z) {
+    return ((P - z + 3) * (P - z + 4) / 2 + p2m_lanes<P>() - 1) / p2m_lanes<P>();
+}
+template <int P>
+constexpr int p2m_fold_steps() {
+    int n = 0;
+    for (int z = 2; z <= P; ++z) n += p2m_fold_steps<P>(z);
+    return n;
+}
+// dynamic LDS of the builder for K far-rule nodes
+template <int P>
+constexpr size_t p2m_build_lds(int K) {
+    return sizeof(double2) * (64 / p2m_lanes<P>()) * K * 3 * (P + 1);
+}
+
 template <class S, int P>
-__global__ void __launch_bounds__(128)
+__global__ void __launch_bounds__(64)
 k_build_p2m_tiles(const Box* __restrict__ boxes, const P2MSeg* __restrict__ segs,
                   const int64_t* __restrict__ aoff, const double* __restrict__ cen,
                   const S* __restrict__ src, int K, float* __restrict__ A32,
@@ -1686,106 +1702,130 @@ k_build_p2m_tiles(const Box* __restrict__ boxes, const P2MSeg* __restrict__ segs
     using E = Expansion<P>;
     constexpr E ex{};
     constexpr int NF = E::NF, NR = E::NR, RT = p2m_row_tiles<P>();
-    constexpr int PB = P <= 10 ? 8 : 4, TPP = 128 / PB;  // LDS at most 65 KB up to P = 15
+    constexpr int TPP = p2m_lanes<P>(), PB = 64 / TPP;
+    constexpr int IT = (NF + TPP - 1) / TPP, IQ = (16 * RT + TPP - 1) / TPP, IF = p2m_fold_steps<P>();
     __shared__ double poly[PB][2][NF];  // V then K polynomial of each panel of the batch
-    // powers d^0..d^P of each node's offset from the box centre, per axis (at most 8 nodes)
-    __shared__ double pw[PB][8][3][P + 1];
+    __shared__ double cf[(P - 1) * (P + 1)];  // fold factors -(k - 1) k / ((z - 1) z) of (z - 2, k)
+    // per panel, node and axis: (d^q, n q d^(q - 1)), q = 0 .. P, of the node's offset d from the
+    // box centre, the x axis times the node's weight
+    extern __shared__ double2 pw[];
     const P2MSeg sg = segs[blockIdx.x];
     const Box B = boxes[sg.box];
     const int lp = threadIdx.x / TPP, lt = threadIdx.x % TPP;
     const int rs = 4 + 4 * K;
-    const int steps = (sg.end - sg.start + 3) / 4;
+    const int np = sg.end - sg.start, steps = (np + 3) / 4;
     const size_t a0 = aoff[blockIdx.x], kb = static_cast<size_t>(steps) * RT * 64;
-    double* pv = poly[lp][0];
-    double* pk = poly[lp][1];
-    for (int base = sg.start; base < sg.end; base += PB) {
-        const int j = base + lp;
-        const bool live = j < sg.end;
+    double* const pv = poly[lp][0];
+    double* const pk = poly[lp][1];
+    for (int u = threadIdx.x; u < (P - 1) * (P + 1); u += 64) {
+        const int z = u / (P + 1) + 2, k = u % (P + 1);
+        cf[u] = -double(k - 1) * double(k) / (double(z - 1) * double(z));
+    }
+    int term[IT];  // kx, ky, kz
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+        const int t = min(lt + TPP * it, NF - 1);
+        term[it] = ex.fx[t] | ex.fy[t] << 8 | ex.fz[t] << 16;
+    }
+    int out_term[IQ];
+#pragma unroll
+    for (int it = 0; it < IQ; ++it) out_term[it] = ex.rfull[min(lt + TPP * it, NR - 1)];
+    // level z feeds level z - 2, whose term (x, y) receives c_y M(x, y - 2, z) and then
+    // c_x M(x - 2, y, z): destination and sources (the destination itself where a factor is zero),
+    // and y, x; -1: no step
+    int at[IF], yx[IF];
+    {
+        int f = 0;
+#pragma unroll
+        for (int z = P; z >= 2; --z)
+#pragma unroll
+            for (int i = 0; i < p2m_fold_steps<P>(z); ++i, ++f) {
+                const int L = P - z + 2;  // x + y <= L at level z - 2
+                const int u = lt + TPP * i;
+                int x = 0, rem = u;
+                while (x < L && rem > L - x) {
+                    rem -= L - x + 1;
+                    ++x;
+                }
+                const int y = rem;
+                const bool any = u < (L + 1) * (L + 2) / 2;
+                const int dst = any ? full_term(x, y, z - 2) : 0;
+                at[f] = dst | (any && y >= 2 ? full_term(x, y - 2, z) : dst) << 10 |
+                        (any && x >= 2 ? full_term(x - 2, y, z) : dst) << 20;
+                yx[f] = any ? y | x << 8 : -1;
+            }
+    }
+    for (int base = PB * blockIdx.y; base < 4 * steps; base += PB * gridDim.y) {
+        const int p = base + lp, j = sg.start + p;
+        const bool live = p < np;
         const S* r = src + static_cast<size_t>(live ? j : sg.start) * rs;
         if (live) {
             // powers of each node's offset by successive products from 1, once per node and axis
             const double cc[3] = {cen[3 * j] - B.cx, cen[3 * j + 1] - B.cy, cen[3 * j + 2] - B.cz};
             for (int u = lt; u < 3 * K; u += TPP) {
                 const int gq = u / 3, ax = u % 3;
-                const double d = cc[ax] + r[4 + 4 * gq + ax];
-                double* pp = pw[lp][gq][ax];
-                double X = 1.0;
-                pp[0] = X;
-                for (int q = 1; q <= P; ++q) {
+                const double d = (ax == 0 ? cc[0] : (ax == 1 ? cc[1] : cc[2])) + r[4 + 4 * gq + ax];
+                const double w = ax == 0 ? r[7 + 4 * gq] : 1.0, nrm = r[ax];
+                double2* pp = pw + ((lp * K + gq) * 3 + ax) * (P + 1);
+                double X = w, G = 0.0;
+                for (int q = 0; q <= P; ++q) {
+                    pp[q] = make_double2(X, G);
+                    G = nrm * (q + 1) * X;
                     X *= d;
-                    pp[q] = X;
                 }
             }
         }
         __syncthreads();
         if (live) {
-            for (int t = lt; t < NF; t += TPP) {
-                const int kx = ex.fx[t], ky = ex.fy[t], kz = ex.fz[t];
+#pragma unroll
+            for (int it = 0; it < IT; ++it) {
+                const double2* px = pw + lp * K * 3 * (P + 1) + (term[it] & 255);
+                const double2* py = pw + (lp * K * 3 + 1) * (P + 1) + (term[it] >> 8 & 255);
+                const double2* pz = pw + (lp * K * 3 + 2) * (P + 1) + (term[it] >> 16);
                 double v = 0.0, k = 0.0;
                 for (int gq = 0; gq < K; ++gq) {
-                    const double* px = pw[lp][gq][0];
-                    const double* py = pw[lp][gq][1];
-                    const double* pz = pw[lp][gq][2];
-                    const double w = r[7 + 4 * gq];
-                    const double X = px[kx], Y = py[ky], Z = pz[kz];
-                    v += w * X * Y * Z;
-                    double gs = 0.0;
-                    if (kx > 0) gs += r[0] * kx * px[kx - 1] * Y * Z;
-                    if (ky > 0) gs += r[1] * ky * X * py[ky - 1] * Z;
-                    if (kz > 0) gs += r[2] * kz * X * Y * pz[kz - 1];
-                    k += w * gs;
+                    const double2 X = px[gq * 3 * (P + 1)], Y = py[gq * 3 * (P + 1)], Z = pz[gq * 3 * (P + 1)];
+                    const double yz = Y.x * Z.x;
+                    v += X.x * yz;
+                    k += X.y * yz + X.x * (Y.y * Z.x + Y.x * Z.y);
                 }
-                pv[t] = v;
-                pk[t] = k;
+                if (lt + TPP * it < NF) {
+                    pv[lt + TPP * it] = v;
+                    pk[lt + TPP * it] = k;
+                }
             }
         }
         __syncthreads();
-        // fold: level z feeds level z - 2, whose term (x, y) receives c_y M(x, y - 2, z) and
-        // then c_x M(x - 2, y, z), c = -(k - 1) k / ((z - 1) z)
+        int f = 0;
+#pragma unroll
         for (int z = P; z >= 2; --z) {
-            const int L = P - z + 2;  // x + y <= L at level z - 2
-            const double den = double(z - 1) * double(z);
-            for (int u = lt; u < (L + 1) * (L + 2) / 2; u += TPP) {
-                int x = 0, rem = u;
-                while (rem > L - x) {
-                    rem -= L - x + 1;
-                    ++x;
-                }
-                const int y = rem;
-                if (!live) continue;
-                const int dst = full_term(x, y, z - 2);
-                double v = pv[dst], k = pk[dst];
-                if (y >= 2) {
-                    const double c = -double(y - 1) * double(y) / den;
-                    const int sidx = full_term(x, y - 2, z);
-                    v += c * pv[sidx];
-                    k += c * pk[sidx];
-                }
-                if (x >= 2) {
-                    const double c = -double(x - 1) * double(x) / den;
-                    const int sidx = full_term(x - 2, y, z);
-                    v += c * pv[sidx];
-                    k += c * pk[sidx];
-                }
-                pv[dst] = v;
-                pk[dst] = k;
+#pragma unroll
+            for (int i = 0; i < p2m_fold_steps<P>(z); ++i, ++f) {
+                if (!live || yx[f] < 0) continue;
+                const int dst = at[f] & 1023, sy = at[f] >> 10 & 1023, sx = at[f] >> 20;
+                const double cy = cf[(z - 2) * (P + 1) + (yx[f] & 255)];
+                const double cx = cf[(z - 2) * (P + 1) + (yx[f] >> 8)];
+                const double v = pv[dst], k = pk[dst];
+                pv[dst] = v + cy * pv[sy] + cx * pv[sx];
+                pk[dst] = k + cy * pk[sy] + cx * pk[sx];
             }
             __syncthreads();
         }
-        if (live) {
-            const int p = j - sg.start, st = p >> 2, kk = p & 3;
-            for (int q = lt; q < NR; q += TPP) {
-                const int rt = q >> 4, lane = (q & 15) + 16 * kk;
-                const size_t idx = a0 + (static_cast<size_t>(st) * RT + rt) * 64 + lane;
-                const double v = pv[ex.rfull[q]], k = pk[ex.rfull[q]];
-                if (A32 != nullptr) {
-                    A32[idx] = static_cast<float>(v);
-                    A32[idx + kb] = static_cast<float>(k);
-                }
-                if (A64 != nullptr) {
-                    A64[idx] = v;
-                    A64[idx + kb] = k;
-                }
+        const int st = p >> 2, kk = p & 3;
+#pragma unroll
+        for (int it = 0; it < IQ; ++it) {
+            const int q = lt + TPP * it;
+            if (q >= 16 * RT) continue;
+            const bool set = live && q < NR;
+            const double v = set ? pv[out_term[it]] : 0.0, k = set ? pk[out_term[it]] : 0.0;
+            const size_t idx = a0 + (static_cast<size_t>(st) * RT + (q >> 4)) * 64 + (q & 15) + 16 * kk;
+            if (A32 != nullptr) {
+                A32[idx] = static_cast<float>(v);
+                A32[idx + kb] = static_cast<float>(k);
+            }
+            if (A64 != nullptr) {
+                A64[idx] = v;
+                A64[idx + kb] = k;
             }
         }
         __syncthreads();
@@ -1914,10 +1954,71 @@ k_fill_tiles(const Chunk* __restrict__ chunks, const int32_t* __restrict__ m2p_o
     }
 }
 
+// Values of a K-step's four rows g for target 16 mt + r16, in lane 16 mt + r16, to the tiles' order:
+// row g's values of the four targets in lane 16 g + r16 (a 4 x 4 transpose of the rows of 16 lanes).
+__device__ __forceinline__ void rows_to_quads(uint32_t (&v)[4]) {
+    auto pair16 = [](uint32_t& a, uint32_t& b) {  // odd rows of a <-> even rows of b
+        const auto r = __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    };
+    auto pair32 = [](uint32_t& a, uint32_t& b) {  // upper half of a <-> lower half of b
+        const auto r = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    };
+    pair16(v[0], v[1]);
+    pair16(v[2], v[3]);
+    pair32(v[0], v[2]);
+    pair32(v[1], v[3]);
+}
+__device__ __forceinline__ void rows_to_quads(float (&v)[4]) {
+    uint32_t u[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) u[g] = __float_as_uint(v[g]);
+    rows_to_quads(u);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) v[g] = __uint_as_float(u[g]);
+}
+__device__ __forceinline__ void rows_to_quads(double (&v)[4]) {
+    uint32_t lo[4], hi[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const uint2 b = __builtin_bit_cast(uint2, v[g]);
+        lo[g] = b.x;
+        hi[g] = b.y;
+    }
+    rows_to_quads(lo);
+    rows_to_quads(hi);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) v[g] = __builtin_bit_cast(double, make_uint2(lo[g], hi[g]));
+}
+
+// Stores K-step st of a tile, lane 16 g + r16 holding row g's values of targets 16 mt + r16: 16
+// contiguous bytes per lane and store (values stored one by one fill a quarter, FP64 half, of each
+// line that a store touches).  A32 (FP64, may be null): the same values rounded.
+__device__ __forceinline__ void store_step(float* A, float*, int st, int lane, const float (&v)[4]) {
+    reinterpret_cast<float4*>(A)[st * 64 + lane] = make_float4(v[0], v[1], v[2], v[3]);
+}
+__device__ __forceinline__ void store_step(double* A, float* A32, int st, int lane, const double (&v)[4]) {
+    double2* const q = reinterpret_cast<double2*>(A) + st * 128 + lane;
+    q[0] = make_double2(v[0], v[1]);
+    q[64] = make_double2(v[2], v[3]);
+    if (A32 != nullptr)
+        reinterpret_cast<float4*>(A32)[st * 64 + lane] =
+            make_float4(static_cast<float>(v[0]), static_cast<float>(v[1]), static_cast<float>(v[2]),
+                        static_cast<float>(v[3]));
+}
+
 // Expansion tile of list entry e: Taylor coefficients of the chunk's 64 targets for its box.
 // tileA32 (FP64 builds, may be null): the same values rounded to FP32, at the same offsets.
+// One wave per workgroup, whose registers hold the target's (P + 1)^2 coefficients up to P = 10
+// (at the 128 registers of larger workgroups, FP64 at P = 8 spilled 155 of them to memory: 1.3 GB
+// beside the 2.2 GB of the tiles at 32768 panels).  Bound by the stores: 440 us there; 590 us
+// with the spills and the values stored one by one.
 template <class T, int P>
-__global__ void k_build_m2p_tiles(const Chunk* __restrict__ chunks, const Box* __restrict__ boxes,
+__global__ void __launch_bounds__(64)
+k_build_m2p_tiles(const Chunk* __restrict__ chunks, const Box* __restrict__ boxes,
                                   const TileDesc* __restrict__ tiles,
                                   const int32_t* __restrict__ m2p_tile,
                                   const int32_t* __restrict__ m2p_chunk,
@@ -1943,37 +2044,35 @@ __global__ void k_build_m2p_tiles(const Chunk* __restrict__ chunks, const Box* _
 #pragma unroll
         for (int q = 0; q < NR; ++q) F[q] = T(0);
     }
-    const int mt = t >> 4, r16 = t & 15;
     // slice k holds terms [4 SST k, 4 SST (k + 1)) as SST K-steps, its tile right after slice
     // k - 1's in the store (zero past the last term)
-    constexpr int SST = expansion_slice_steps(NR), PER = 4 * SST;
-    constexpr int TOT = expansion_slices(NR) * PER;
+    constexpr int TOT = expansion_slices(NR) * expansion_slice_steps(NR);
+    float* A32 = tileA32 != nullptr ? tileA32 + TD.a_off() : nullptr;
 #pragma unroll
-    for (int q = 0; q < TOT; ++q) {
-        const int k = q / PER, st = (q % PER) >> 2, g = q & 3;
-        const size_t base = static_cast<size_t>(k) * SST * 256;
-        const T v = q < NR ? F[q] : T(0);
-        A[base + tile_index<T>(st, 16 * g + r16, mt)] = v;
-        if (tileA32 != nullptr)
-            tileA32[TD.a_off() + base + tile_index<float>(st, 16 * g + r16, mt)] = static_cast<float>(v);
+    for (int st = 0; st < TOT; ++st) {
+        T v[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) v[g] = 4 * st + g < NR ? F[min(4 * st + g, NR - 1)] : T(0);
+        rows_to_quads(v);
+        store_step(A, A32, st, t, v);
     }
 }
 
-
 // Direct tile: far-rule single- and double-layer kernel values of the chunk's 64 targets for
 // up to 4 direct_steps() consecutive source panels (zero for the target's own panel and past the
-// range).  The tile's source records and centroids are staged in LDS by one contiguous copy;
-// each thread keeps its target's centroid (thread t of every wave: target t).
-constexpr int P2P_MAXP = 4 * 31;    // panels of a direct tile: direct_steps() <= 31
-constexpr int P2P_MAXR = 4 + 4 * 8;  // record length for up to 8 far-rule nodes
-template <class T>
+// range).  Each wave forms a K-step at a time: lane 16 g + r16 the values of panel 4 st + g for
+// targets 16 mt + r16, which is how the tile holds them.  Bound by the FP64 vector units (about 78
+// operations per pair at four nodes) and by the stores, 16 or 24 bytes per pair.  FP64 and FP32
+// stores of 32768 panels at P = 8, beside the moments' builder: 499 us.  With one target per lane
+// 716 us where the records were staged in LDS (23 reads per pair, 39 KB, four workgroups per CU)
+// and 735 us where they came by scalar loads (no record is used twice in a tile, so every load
+// misses the scalar cache).
+template <class T, int K>
 __global__ void __launch_bounds__(256)
 k_build_p2p_tiles(const Chunk* __restrict__ chunks, const TileDesc* __restrict__ tiles,
                   const int32_t* __restrict__ p2p_tile, const int32_t* __restrict__ p2p_chunk,
-                  int n, const double* __restrict__ cen, const T* __restrict__ src, int K,
+                  int n, const double* __restrict__ cen, const T* __restrict__ src,
                   T* __restrict__ tileA, float* __restrict__ tileA32) {
-    __shared__ T rec[P2P_MAXP * P2P_MAXR];
-    __shared__ double cj[P2P_MAXP * 3];
     const int e = blockIdx.x;
     if (e >= n) return;
     const TileDesc TD = tiles[p2p_tile[e]];
@@ -1981,47 +2080,56 @@ k_build_p2p_tiles(const Chunk* __restrict__ chunks, const TileDesc* __restrict__
     T* AK = tileA + TD.a_off();
     T* AV = AK + static_cast<size_t>(TD.nstep) * 256;
     float* BK = tileA32 != nullptr ? tileA32 + TD.a_off() : nullptr;
-    const int rs = 4 + 4 * K, np = TD.b_rows;
-    const T* rsrc = src + static_cast<size_t>(TD.b_row0) * rs;
-    for (int u = threadIdx.x; u < np * rs; u += blockDim.x) rec[u] = rsrc[u];
-    for (int u = threadIdx.x; u < np * 3; u += blockDim.x) cj[u] = cen[3 * static_cast<size_t>(TD.b_row0) + u];
-    const int t = threadIdx.x & 63, i = C.start + t;  // every pr below has pr & 63 == t
-    const bool tin = i < C.end;
-    const double xi = tin ? cen[3 * i] : 0.0, yi = tin ? cen[3 * i + 1] : 0.0,
-                 zi = tin ? cen[3 * i + 2] : 0.0;
-    __syncthreads();
-    for (int pr = threadIdx.x; pr < 64 * 4 * TD.nstep; pr += blockDim.x) {
-        const int p = pr >> 6;  // panel within the tile
-        const int j = TD.b_row0 + p;
-        T kv = 0, kk = 0;
-        if (tin && p < np && j != i) {
-            const T* r = rec + p * rs;
-            const T dx = static_cast<T>(xi - cj[3 * p]);
-            const T dy = static_cast<T>(yi - cj[3 * p + 1]);
-            const T dz = static_cast<T>(zi - cj[3 * p + 2]);
-            const T sh = r[0] * dx + r[1] * dy + r[2] * dz;
-            T sv = 0, sk = 0;
-            for (int gq = 0; gq < K; ++gq) {
-                const T ex_ = dx - r[4 + 4 * gq];
-                const T ey_ = dy - r[5 + 4 * gq];
-                const T ez_ = dz - r[6 + 4 * gq];
-                const T w = r[7 + 4 * gq];
+    constexpr int rs = 4 + 4 * K;
+    const int np = TD.b_rows;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int g = lane >> 4, r16 = lane & 15;
+    double x[4][3];  // this lane's targets
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) {
+        const int i = min(C.start + 16 * mt + r16, C.end - 1);
+#pragma unroll
+        for (int c = 0; c < 3; ++c) x[mt][c] = cen[3 * static_cast<size_t>(i) + c];
+    }
+    for (int st = wave; st < TD.nstep; st += 4) {
+        const int p = 4 * st + g;  // panel within the tile
+        const int j = TD.b_row0 + min(p, np - 1);
+        const Quad<T>* r = reinterpret_cast<const Quad<T>*>(src + static_cast<size_t>(j) * rs);
+        const Quad<T> nrm = r[0];
+        const double* cj = cen + 3 * static_cast<size_t>(j);
+        const double c0 = cj[0], c1 = cj[1], c2 = cj[2];
+        T dx[4], dy[4], dz[4], sv[4], sk[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            dx[mt] = static_cast<T>(x[mt][0] - c0);
+            dy[mt] = static_cast<T>(x[mt][1] - c1);
+            dz[mt] = static_cast<T>(x[mt][2] - c2);
+            sv[mt] = sk[mt] = T(0);
+        }
+#pragma unroll
+        for (int gq = 0; gq < K; ++gq) {
+            const Quad<T> nd = r[1 + gq];
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt) {
+                const T ex_ = dx[mt] - nd.x;
+                const T ey_ = dy[mt] - nd.y;
+                const T ez_ = dz[mt] - nd.z;
                 const T ri = rsqrt_t<T>(ex_ * ex_ + ey_ * ey_ + ez_ * ez_);
-                sv += w * ri;
-                sk += w * ri * ri * ri;
+                sv[mt] += nd.w * ri;
+                sk[mt] += nd.w * ri * ri * ri;
             }
-            kv = sv;
-            kk = sh * sk;
         }
-        const int st = p >> 2, g = p & 3, mt = t >> 4, r16 = t & 15;
-        const size_t idx = tile_index<T>(st, 16 * g + r16, mt);
-        AK[idx] = kk;
-        AV[idx] = kv;
-        if (BK != nullptr) {
-            const size_t i32 = tile_index<float>(st, 16 * g + r16, mt);
-            BK[i32] = static_cast<float>(kk);
-            BK[static_cast<size_t>(TD.nstep) * 256 + i32] = static_cast<float>(kv);
+        T kk[4], kv[4];
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt) {
+            const int i = C.start + 16 * mt + r16;
+            const T sh = nrm.x * dx[mt] + nrm.y * dy[mt] + nrm.z * dz[mt];
+            const bool set = i < C.end && p < np && j != i;
+            kv[mt] = set ? sv[mt] : T(0);
+            kk[mt] = set ? sh * sk[mt] : T(0);
         }
+        store_step(AK, BK, st, lane, kk);
+        store_step(AV, BK != nullptr ? BK + static_cast<size_t>(TD.nstep) * 256 : nullptr, st, lane, kv);
     }
 }
 
@@ -2396,7 +2504,7 @@ bool launch_p2m_tiles(Geometry& g, const Cols& c, const T* dens, T* mom, hipStre
     return true;
 }
 
-// Allocations and the offset table in the order of s; the fills and the builder on s2, after
+// Allocations and the offset table in the order of s; the builder on s2, after
 // that point of s (the caller waits for s2).
 template <int P>
 void build_p2m_tiles_p(Geometry& g, hipStream_t s, hipStream_t s2) {
@@ -2422,16 +2530,14 @@ void build_p2m_tiles_p(Geometry& g, hipStream_t s, hipStream_t s2) {
     const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(s2, ev, 0) : e1;
     (void)hipEventDestroy(ev);
     LSPR_HIP(e2);
-    if (g.p2mA.p != nullptr) LSPR_HIP(hipMemsetAsync(g.p2mA.p, 0, g.p2mA.bytes(), s2));
-    if (g.p2mA64.p != nullptr) LSPR_HIP(hipMemsetAsync(g.p2mA64.p, 0, g.p2mA64.bytes(), s2));
+    const dim3 grid(g.n_seg, P2M_PARTS);
+    const size_t lds = p2m_build_lds<P>(g.K);
     if (g.src64.p != nullptr)
-        hipLaunchKernelGGL((k_build_p2m_tiles<double, P>), dim3(g.n_seg), dim3(128), 0, s2,
-                           g.boxes.p, g.p2m_seg.p, g.p2m_aoff.p, g.cen.p, g.src64.p, g.K,
-                           g.p2mA.p, g.p2mA64.p);
+        hipLaunchKernelGGL((k_build_p2m_tiles<double, P>), grid, dim3(64), lds, s2, g.boxes.p,
+                           g.p2m_seg.p, g.p2m_aoff.p, g.cen.p, g.src64.p, g.K, g.p2mA.p, g.p2mA64.p);
     else
-        hipLaunchKernelGGL((k_build_p2m_tiles<float, P>), dim3(g.n_seg), dim3(128), 0, s2,
-                           g.boxes.p, g.p2m_seg.p, g.p2m_aoff.p, g.cen.p, g.src32.p, g.K,
-                           g.p2mA.p, g.p2mA64.p);
+        hipLaunchKernelGGL((k_build_p2m_tiles<float, P>), grid, dim3(64), lds, s2, g.boxes.p,
+                           g.p2m_seg.p, g.p2m_aoff.p, g.cen.p, g.src32.p, g.K, g.p2mA.p, g.p2mA64.p);
     LSPR_HIP(hipGetLastError());
 }
 
@@ -2578,10 +2684,17 @@ void build_tiles_t(Geometry& g, T* A, float* A32, const int32_t* mt, const int32
         }
     }
     if (n_p2p > 0) {
-        LSPR_REQUIRE(4 * direct_steps(g.n_terms) <= P2P_MAXP && 4 + 4 * g.K <= P2P_MAXR,
-                     LSPR_E_INVALID, "direct tile larger than the tile builder's staging");
-        hipLaunchKernelGGL(k_build_p2p_tiles<T>, dim3(n_p2p), dim3(256), 0, s, g.chunks.p,
-                           g.tiles.p, pt, pc, n_p2p, g.cen.p, src_of<T>(g), g.K, A, A32);
+        auto launch = [&](auto k) {
+            hipLaunchKernelGGL((k_build_p2p_tiles<T, decltype(k)::value>), dim3(n_p2p), dim3(256), 0, s,
+                               g.chunks.p, g.tiles.p, pt, pc, n_p2p, g.cen.p, src_of<T>(g), A, A32);
+        };
+        switch (g.K) {
+            case 1: launch(std::integral_constant<int, 1>{}); break;
+            case 3: launch(std::integral_constant<int, 3>{}); break;
+            case 4: launch(std::integral_constant<int, 4>{}); break;
+            case 7: launch(std::integral_constant<int, 7>{}); break;
+            default: throw Error(LSPR_E_INVALID, "k_far must be 1, 3, 4 or 7");
+        }
         LSPR_HIP(hipGetLastError());
     }
 }

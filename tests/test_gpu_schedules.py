@@ -155,3 +155,19 @@ def test_right_hand_side_through_v_alone(lib, precision, tol, p, blobs):
         geo = lib.Geometry(surfs, method="treecode", precision=precision, p=p, theta=theta)
         b = geo.rhs(np.array([em]), es[None], e).cpu().numpy()[0]
         assert np.abs(b - ref).max() / np.abs(ref).max() < bound, theta
+
+
+# tiles against the same far field evaluated on the fly by kernels of their own, for every order that
+# has both (tiles of one and of several slices) and every far rule; both in FP64, where (p + 1)^2 terms of
+# products of rounded powers and folded moments stay below 1e-11 of the largest entry
+@pytest.mark.parametrize("p,k_far", [(2, 4), (4, 1), (6, 3), (8, 4), (8, 7), (10, 4)])
+def test_tiles_equal_sums_on_the_fly(lib, p, k_far):
+    surfs = _surfaces(14, (5, 6))
+    n = sum(len(t) for _, t in surfs)
+    kw = dict(method="treecode", precision="fp64", p=p, theta=0.5, k_far=k_far, ncrit=10, m2p_min_panels=1)
+    tiles, fly = lib.Geometry(surfs, **kw), lib.Geometry(surfs, matrix_cores=False, **kw)
+    rng = np.random.default_rng(p)
+    x = torch.as_tensor(rng.standard_normal((3, 2 * n)) + 1j * rng.standard_normal((3, 2 * n))).cuda()
+    em, es = np.full(3, 1.7733), np.tile([-3.0 + 0.3j, 2.5, 2.0 + 0.1j], (3, 1))
+    a, b = tiles.apply(x, em, es).cpu().numpy(), fly.apply(x, em, es).cpu().numpy()
+    assert _worst(a, b) < 1e-11
