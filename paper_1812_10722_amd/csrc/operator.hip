@@ -312,97 +312,147 @@ k_far(const Chunk* __restrict__ chunks, const Box* __restrict__ boxes,
 // ------------------------------------------------------------------------------- direct sums
 // FP64 sums of one or two wavelengths over direct ranges alone, every kernel value formed on the
 // fly: a dense product on a mesh whose factors do not fit the device.  Bound by the FP64 vector
-// units: about 19 operations per far-rule node and 10 per pair (about 88 at K = 4).
-// One workgroup per chunk, one target per lane; DW waves take tiles of DT panels of each range in
-// turn.  A panel's record, centroid and densities are the same for the whole wave, so they come
-// by scalar loads and enter the arithmetic from scalar registers: no LDS, barrier or vector load
-// in the loop, and up to 32 waves stay resident per CU (k_far, with 29 KB of LDS per one-wave
-// workgroup, holds five).  Each tile's partial joins a compensated sum; the waves' sums are added
-// (compensated) through LDS after the own-surface ranges and at the end.
-// 111392 panels, one wavelength, K = 4: 41 ms (k_far: 232 ms), 0.30 T pairs/s; the operations
-// above take 28 ms at the FP64 vector peak.
+// units: 16 operations per far-rule node, one of them at quarter rate, and 13 per pair (77 at K = 4).
+// One target of a chunk per lane; DW waves take tiles of DT panels of each range in turn.  A panel's
+// record, centroid and densities are the same for the whole wave, so they come by scalar loads and
+// enter the arithmetic from scalar registers: no LDS, barrier or vector load in the loop (k_far,
+// with 29 KB of LDS per one-wave workgroup, holds five waves per CU).  Each tile's partial joins a
+// compensated sum; the waves' sums are added (compensated) through LDS after the own-surface ranges
+// and at the end.  For one wavelength a workgroup takes two chunks where their ranges are equal, so
+// that a panel's values serve two targets per lane.
+// 111392 panels, one wavelength, K = 4: 39.1 ms (one chunk per workgroup: 41.0, k_far: 232 ms),
+// 0.32 T pairs/s; the vector units issue 75 % of the time, 29 ms.
 constexpr int DW = 16;  // waves per workgroup
 constexpr int DT = 16;  // panels per partial
+constexpr int DCUS = 256;  // compute units
 
-template <int K, int CPT>
-__global__ void __launch_bounds__(64 * DW)
-k_direct64(const Chunk* __restrict__ chunks, const int32_t* __restrict__ p2p_off,
-           const Range* __restrict__ p2p_rng, const int32_t* __restrict__ p2p_self,
-           const double* __restrict__ cen, const double* __restrict__ src,
-           const double* __restrict__ dens, double* __restrict__ out_self,
-           double* __restrict__ out_all) {
+// Sums of TG consecutive chunks with equal range lists, one target of each per lane.
+template <int K, int CPT, int TG>
+__device__ __forceinline__ void direct_sums(const Chunk* __restrict__ chunks, const int32_t* __restrict__ p2p_off,
+                                            const Range* __restrict__ p2p_rng,
+                                            const int32_t* __restrict__ p2p_self,
+                                            const double* __restrict__ cen, const double* __restrict__ src,
+                                            const double* __restrict__ dens, double* __restrict__ out_self,
+                                            double* __restrict__ out_all, int chunk,
+                                            double (&red)[2 * CPT][DW][64]) {
     constexpr int NC = 2 * CPT, RS = 4 + 4 * K;
     static_assert(NC <= DW, "one wave per column adds the waves' sums");
-    __shared__ double red[NC][DW][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const Chunk C = chunks[blockIdx.x];
-    const int i = C.start + lane;
-    const bool valid = i < C.end;
-    const int it = valid ? i : C.start;
-    const double x0 = cen[3 * it], x1 = cen[3 * it + 1], x2 = cen[3 * it + 2];
-    double hi[NC], lo[NC];
+    const int own0 = chunks[chunk].start, own1 = chunks[chunk + TG - 1].end;
+    int i[TG];
+    bool valid[TG];
+    double x0[TG], x1[TG], x2[TG], hi[TG][NC], lo[TG][NC];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) hi[c] = lo[c] = 0.0;
+    for (int a = 0; a < TG; ++a) {
+        const Chunk C = chunks[chunk + a];
+        i[a] = C.start + lane;
+        valid[a] = i[a] < C.end;
+        const int it = valid[a] ? i[a] : C.start;
+        x0[a] = cen[3 * it];
+        x1[a] = cen[3 * it + 1];
+        x2[a] = cen[3 * it + 2];
+#pragma unroll
+        for (int c = 0; c < NC; ++c) hi[a][c] = lo[a][c] = 0.0;
+    }
     // adds panel j (uniform); SELF: the lane whose target it is adds nothing
-    auto panel = [&](int j, double (&part)[NC], auto self) {
+    auto panel = [&](int j, double (&part)[TG][NC], auto self) {
         const double* r = src + static_cast<size_t>(j) * RS;
         const double* dj = dens + static_cast<size_t>(j) * NC;
-        const double dx = x0 - cen[3 * static_cast<size_t>(j)];
-        const double dy = x1 - cen[3 * static_cast<size_t>(j) + 1];
-        const double dz = x2 - cen[3 * static_cast<size_t>(j) + 2];
-        const double s = r[0] * dx + r[1] * dy + r[2] * dz;  // height above the plane
-        double sv = 0.0, sk = 0.0;
+        const double c0 = cen[3 * static_cast<size_t>(j)], c1 = cen[3 * static_cast<size_t>(j) + 1],
+                     c2 = cen[3 * static_cast<size_t>(j) + 2];
 #pragma unroll
-        for (int g = 0; g < K; ++g) {
-            const double ex = dx - r[4 + 4 * g], ey = dy - r[5 + 4 * g], ez = dz - r[6 + 4 * g];
-            const double ri = rsqrt_t<double>(ex * ex + ey * ey + ez * ez);
-            const double t = r[7 + 4 * g] * ri;
-            sv += t;
-            sk += t * ri * ri;
-        }
-        double kk = s * sk;
-        if constexpr (decltype(self)::value) {
-            sv = j == i ? 0.0 : sv;
-            kk = j == i ? 0.0 : kk;
-        }
+        for (int a = 0; a < TG; ++a) {
+            const double dx = x0[a] - c0, dy = x1[a] - c1, dz = x2[a] - c2;
+            const double s = r[0] * dx + r[1] * dy + r[2] * dz;  // height above the plane
+            double sv = 0.0, sk = 0.0;
 #pragma unroll
-        for (int c = 0; c < CPT; ++c) {
-            part[c] += kk * dj[c];
-            part[CPT + c] += sv * dj[CPT + c];
+            for (int g = 0; g < K; ++g) {
+                const double ex = dx - r[4 + 4 * g], ey = dy - r[5 + 4 * g], ez = dz - r[6 + 4 * g];
+                const double ri = rsqrt_t<double>(ex * ex + ey * ey + ez * ez);
+                const double t = r[7 + 4 * g] * ri;
+                sv += t;
+                sk += t * ri * ri;
+            }
+            double kk = s * sk;
+            if constexpr (decltype(self)::value) {
+                sv = j == i[a] ? 0.0 : sv;
+                kk = j == i[a] ? 0.0 : kk;
+            }
+#pragma unroll
+            for (int c = 0; c < CPT; ++c) {
+                part[a][c] += kk * dj[c];
+                part[a][CPT + c] += sv * dj[CPT + c];
+            }
         }
     };
-    const int p_beg = p2p_off[blockIdx.x], p_end = p2p_off[blockIdx.x + 1];
-    const int p_mid = p_beg + p2p_self[blockIdx.x];
+    const int p_beg = p2p_off[chunk], p_end = p2p_off[chunk + 1];
+    const int p_mid = p_beg + p2p_self[chunk];
     for (int phase = 0; phase < 2; ++phase) {
         const int pa = phase == 0 ? p_beg : p_mid, pb = phase == 0 ? p_mid : p_end;
         for (int e = pa; e < pb; ++e) {
             const Range R = p2p_rng[e];
             for (int p0 = R.start + wave * DT; p0 < R.end; p0 += DW * DT) {
                 const int p1 = min(p0 + DT, R.end);
-                double part[NC];
+                double part[TG][NC];
 #pragma unroll
-                for (int c = 0; c < NC; ++c) part[c] = 0.0;
-                if (p0 < C.end && p1 > C.start)
+                for (int a = 0; a < TG; ++a)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) part[a][c] = 0.0;
+                if (p0 < own1 && p1 > own0)
                     for (int j = p0; j < p1; ++j) panel(j, part, std::true_type{});
                 else
                     for (int j = p0; j < p1; ++j) panel(j, part, std::false_type{});
 #pragma unroll
-                for (int c = 0; c < NC; ++c) two_sum_add(hi[c], lo[c], part[c]);
+                for (int a = 0; a < TG; ++a)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) two_sum_add(hi[a][c], lo[a][c], part[a][c]);
             }
         }
         double* o = phase == 0 ? out_self : out_all;
         if (o == nullptr) continue;
 #pragma unroll
-        for (int c = 0; c < NC; ++c) red[c][wave][lane] = hi[c] + lo[c];
-        __syncthreads();
-        if (wave < NC) {
-            double h = 0.0, l = 0.0;
-            for (int w = 0; w < DW; ++w) two_sum_add(h, l, red[wave][w][lane]);
-            if (valid) o[static_cast<size_t>(i) * NC + wave] = h + l;
+        for (int a = 0; a < TG; ++a) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) red[c][wave][lane] = hi[a][c] + lo[a][c];
+            __syncthreads();
+            if (wave < NC) {
+                double h = 0.0, l = 0.0;
+                for (int w = 0; w < DW; ++w) two_sum_add(h, l, red[wave][w][lane]);
+                if (valid[a]) o[static_cast<size_t>(i[a]) * NC + wave] = h + l;
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
+}
+
+// The first n_pairs workgroups take two chunks each, the others one.
+template <int K, int CPT>
+__global__ void __launch_bounds__(64 * DW)
+k_direct64(const Chunk* __restrict__ chunks, const int32_t* __restrict__ p2p_off,
+           const Range* __restrict__ p2p_rng, const int32_t* __restrict__ p2p_self,
+           const double* __restrict__ cen, const double* __restrict__ src,
+           const double* __restrict__ dens, double* __restrict__ out_self,
+           double* __restrict__ out_all, int n_pairs) {
+    __shared__ double red[2 * CPT][DW][64];
+    const int b = blockIdx.x;
+    const int chunk = b < n_pairs ? 2 * b : n_pairs + b;
+    if constexpr (CPT == 2) {
+        if (b < n_pairs) {
+            const int e0 = p2p_off[chunk], e1 = p2p_off[chunk + 1], n = e1 - e0;
+            bool same = p2p_off[chunk + 2] - e1 == n && p2p_self[chunk] == p2p_self[chunk + 1] &&
+                        chunks[chunk].end == chunks[chunk + 1].start;
+            for (int e = 0; same && e < n; ++e)
+                same = p2p_rng[e0 + e].start == p2p_rng[e1 + e].start && p2p_rng[e0 + e].end == p2p_rng[e1 + e].end;
+            if (same) {
+                direct_sums<K, CPT, 2>(chunks, p2p_off, p2p_rng, p2p_self, cen, src, dens, out_self, out_all,
+                                       chunk, red);
+                return;
+            }
+        }
+    }
+    for (int c = chunk; c < chunk + (b < n_pairs ? 2 : 1); ++c)
+        direct_sums<K, CPT, 1>(chunks, p2p_off, p2p_rng, p2p_self, cen, src, dens, out_self, out_all, c, red);
 }
 
 // ------------------------------------------------------------------------------- far field, MFMA
@@ -2561,9 +2611,18 @@ bool launch_direct(Geometry& g, const Cols& c, const double* dens, double* os, d
                    hipStream_t s) {
     if (g.n_m2p > 0 || c.pad != c.cpt || c.cpt > 4) return false;
     auto launch = [&](auto k, auto cpt) {
-        hipLaunchKernelGGL((k_direct64<decltype(k)::value, decltype(cpt)::value>), dim3(g.n_chunks),
-                           dim3(64 * DW), 0, s, g.chunks.p, g.p2p_off.p, g.p2p_rng.p, g.p2p_self.p,
-                           g.cen.p, g.src64.p, dens, os, oa);
+        constexpr int CPT = decltype(cpt)::value;
+        // Two chunks per workgroup, one workgroup per CU; the chunks of the last round go one by one
+        // where there is a CU for each, which halves that round.  Two wavelengths' sums of two
+        // chunks would exceed the 128 registers of these workgroups.
+        int n_pairs = 0;
+        if (CPT == 2) {
+            n_pairs = g.n_chunks / 2 / DCUS * DCUS;
+            if (g.n_chunks - 2 * n_pairs > DCUS) n_pairs = g.n_chunks / 2;
+        }
+        hipLaunchKernelGGL((k_direct64<decltype(k)::value, CPT>), dim3(g.n_chunks - n_pairs), dim3(64 * DW),
+                           0, s, g.chunks.p, g.p2p_off.p, g.p2p_rng.p, g.p2p_self.p, g.cen.p, g.src64.p,
+                           dens, os, oa, n_pairs);
         LSPR_HIP(hipGetLastError());
     };
     auto width = [&](auto k) {

@@ -67,6 +67,28 @@ def test_direct_sums_on_the_fly(lib, nu, blobs, ncol, k_far):
     assert (again == y).all()
 
 
+# the same sums with more chunks than CUs: chunks in pairs (an odd one over, pairs across surfaces whose
+# ranges differ) against rows of the oracle
+@pytest.mark.parametrize("nu,blobs", [(47, ()), (46, (5, 4))])
+def test_direct_sums_of_chunk_pairs(lib, nu, blobs):
+    surfs = _surfaces(nu, blobs)
+    v, t, sid = merge_surfaces(surfs)
+    n = len(t)
+    rows = np.unique(np.r_[0:5, np.linspace(0, n - 1, 23).astype(int), n - 180:n:20, n - 1])
+    V, K = oracle.operators.operator_rows(v, t, rows, 4, 19, 9, 0.5)
+    rng = np.random.default_rng(nu)
+    x = rng.standard_normal((1, 2 * n)) + 1j * rng.standard_normal((1, 2 * n))
+    em, es = np.array([1.7733]), np.array([[-3.38 + 0.2j] + [2.5] * len(blobs)])
+    geo = lib.Geometry(surfs, method="dense", precision="fp64", matrix_cores=False)
+    y = geo.apply(torch.as_tensor(x).cuda(), em, es).cpu().numpy()[0]
+    phi, sig = x[0, :n], x[0, n:]
+    same = sid[rows][:, None] == sid[None, :]
+    top = 0.5 * phi[rows] + np.where(same, K, 0) @ phi - np.where(same, V, 0) @ sig
+    low = 0.5 * phi[rows] - K @ phi + (V * (es[0][sid] / em[0])[None, :]) @ sig
+    for got, ref in ((y[rows], top), (y[n + rows], low)):
+        assert np.abs(got - ref).max() / np.abs(y).max() < 2e-12  # (17672 products per sum)
+
+
 # FP32 products of more than 16 wavelengths in half tiles: every number of column groups (3 .. 8),
 # each number of waves per group, odd and even K-steps per tile (P = 6, 8, 10, 15) and direct
 # tiles of one step (short remainders).  The arithmetic per output is that of the four-wave
