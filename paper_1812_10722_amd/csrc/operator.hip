@@ -1500,6 +1500,216 @@ k_far_wide64(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items
     write_sums(o_all);
 }
 
+// FP64 products of 17 to 64 columns per operator: workgroups of W waves for one operator's W / S
+// column groups, S waves each, wave k of a group taking K-steps k, k + S, ... of every tile, the S
+// waves' sums added in wave order through LDS at the end: the products, their order and the sums of
+// k_far_tiles_op<double, NSM, S>.  Tiles run as halves, as in k_far_wide64, in three LDS buffers: at
+// the start of half u every wave requests its share of half u + 2 (1 KB pieces by buffer loads that
+// write LDS; zeros past the half's steps) into the buffer that half u - 1 used; at its end each wave
+// waits for its own requests of half u + 1 and one barrier ends the half.  Two workgroups per CU keep
+// 88 KB of requests in flight at P = 8.  At 13 wavelengths the matrix cores need about 390 us of the
+// 410 us that the tiles of 25992 panels (P = 8) take to read; staged through registers between two
+// barriers the two did not overlap (724 us), here they do (602 us).
+// Requires work items that do not span a chunk's own-surface boundary (plan_items, cut_self).
+template <int NSM, int S, int W>
+__global__ void __launch_bounds__(64 * W, 2)
+k_far_narrow64(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
+               const int32_t* __restrict__ item_order, const int32_t* __restrict__ tile_self,
+               const TileDesc* __restrict__ tiles, const double* __restrict__ tileA,
+               const double* __restrict__ dens, const double* __restrict__ mom, int pad, int nwc, int nops,
+               double* __restrict__ out_self, double* __restrict__ out_all,
+               double* __restrict__ part) {
+    static_assert((S == 1 || S == 2) && W % S == 0, "waves per column group");
+    constexpr int NB = NSM > DSTEPS ? NSM : DSTEPS;
+    constexpr int NH = (NB + 1) / 2;       // most K-steps of a half tile
+    constexpr int NHS = (NH + S - 1) / S;  // K-steps (B operands) per wave and half
+    constexpr int NREQ = (2 * NH + W - 1) / W;  // 1 KB pieces each wave requests per half
+    constexpr int G = W / S;               // column groups per workgroup
+    typedef __attribute__((address_space(3))) void* lds_ptr;
+    __shared__ float4 lb0[NH * 128];
+    __shared__ float4 lb1[NH * 128];
+    __shared__ float4 lb2[NH * 128];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wg = wave / S, kpart = wave % S;  // column group, share of the K-steps
+    const int c16 = lane & 15, grp = lane >> 4;
+    const int ncols = 2 * pad;
+    // two workgroups per work item, at b and b + 8: operator (b >> 3) & 1; nops = 1: one, the V columns
+    const int b = blockIdx.x;
+    const int opr = nops == 2 ? (b >> 3) & 1 : 1;
+    const int item = item_order[nops == 2 ? (b >> 4) * 8 + (b & 7) : b];
+    if (item < 0) return;
+    const FarItem I = items[item];
+    const int chunk = I.chunk;
+    const Chunk C = chunks[chunk];
+    const int ntg = C.end - C.start;
+    const bool mma = wg < nwc;
+    const int col = opr * pad + 16 * wg + c16;
+    const uint32_t boff = static_cast<uint32_t>(grp * ncols + (mma ? col : 0)) * 8u;
+    const uint32_t bstep = 32u * static_cast<uint32_t>(ncols);
+    v4d acc[4];
+#pragma unroll
+    for (int a = 0; a < 4; ++a) acc[a] = v4d{0, 0, 0, 0};
+    const bool whole = I.slot < 0;
+    const int t_beg = I.t0, t_end = I.t1;
+    const int t_mid = whole ? t_beg + tile_self[chunk] : t_beg;
+    double* const o_self = whole ? out_self : nullptr;
+    double* const o_all = whole ? out_all + static_cast<size_t>(C.start) * ncols
+                                : part + static_cast<size_t>(I.slot) * NT * ncols;
+    // sums of the S waves of each column group in the group's first wave (all waves call it, once,
+    // when no request is outstanding any more)
+    auto add_waves = [&]() {
+        constexpr int SPB = NH * 2048 / 8192;  // 8 KB slots per buffer
+        static_assert(S == 1 || G <= 3 * SPB, "reduction slots");
+        float4* const base = wg < SPB ? lb0 : (wg < 2 * SPB ? lb1 : lb2);
+        double* red = reinterpret_cast<double*>(base) + (wg % SPB) * 16 * 64;
+        for (int k = 1; k < S; ++k) {
+            if (kpart == k)
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) red[(4 * mt + q) * 64 + lane] = acc[mt][q];
+            __syncthreads();
+            if (kpart == 0)
+#pragma unroll
+                for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[mt][q] += red[(4 * mt + q) * 64 + lane];
+            __syncthreads();
+        }
+    };
+    auto write_sums = [&](double* out) {
+        if (!mma || kpart != 0) return;
+#pragma unroll
+        for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int t = 16 * mt + out_row<double>(grp, q);
+                if (t < ntg) out[static_cast<size_t>(t) * ncols + col] = acc[mt][q];
+            }
+    };
+    auto b_rsrc = [&](const TileDesc& D, bool more) {
+        const double* bsrc = D.kind == 0 ? mom : dens;
+        return buffer_rsrc(bsrc + static_cast<size_t>(D.b_row0) * ncols,
+                           more ? static_cast<uint32_t>(D.b_rows) * static_cast<uint32_t>(ncols) * 8u : 0u);
+    };
+    auto to_desc = [](const v4u& w) {
+        const uint32_t w0 = __builtin_amdgcn_readfirstlane(w[0]);
+        TileDesc D;
+        D.kind = static_cast<int16_t>(w0 & 0xffffu);
+        D.nstep = static_cast<int16_t>(w0 >> 16);
+        D.a_blk = static_cast<int32_t>(__builtin_amdgcn_readfirstlane(w[1]));
+        D.b_row0 = static_cast<int32_t>(__builtin_amdgcn_readfirstlane(w[2]));
+        D.b_rows = static_cast<int32_t>(__builtin_amdgcn_readfirstlane(w[3]));
+        return D;
+    };
+    // this wave's requests for K-steps [s0, s0 + n) of tile D's left factor (its own operator's
+    // factor of a direct tile) into L: pieces wave, wave + W, ... (the last piece may be requested
+    // by more than one wave, with the same data), zeros past n
+    auto request = [&](const TileDesc& D, int s0, int n, float4* L) {
+        const int64_t off = D.a_off() + (D.kind == 1 ? static_cast<int64_t>(opr) * D.nstep * 256 : 0) +
+                            static_cast<int64_t>(s0) * 256;
+        const __amdgpu_buffer_rsrc_t ra =
+            buffer_rsrc(tileA + off, n > 0 ? static_cast<uint32_t>(n) * 2048u : 0u);
+#pragma unroll
+        for (int k = 0; k < NREQ; ++k) {
+            const int q = wave + W * k < 2 * NH ? wave + W * k : 2 * NH - 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(ra, (lds_ptr)(L + q * 64), 16, lane * 16, q * 1024, 0, 0);
+        }
+    };
+    // The work items of these launches never span the own-surface boundary: a whole chunk's
+    // own-surface sums are its sums over all its tiles, or zero when it has no own-surface tiles.
+    if (o_self != nullptr && t_mid == t_beg) write_sums(o_self + static_cast<size_t>(C.start) * ncols);
+    const __amdgpu_buffer_rsrc_t rt =
+        buffer_rsrc(tiles + t_beg, static_cast<uint32_t>(t_end - t_beg) * 16u);
+    TileDesc Te = tiles[t_beg < t_end ? t_beg : 0];
+    TileDesc Tn = tiles[t_beg + 1 < t_end ? t_beg + 1 : 0];
+    double bc[NHS];
+    {
+        const int n = t_beg < t_end ? Te.nstep : 0, h = (n + 1) / 2;
+        request(Te, 0, h, lb0);
+        request(Te, h, n - h, lb1);
+        const __amdgpu_buffer_rsrc_t rb = b_rsrc(Te, t_beg < t_end);
+#pragma unroll
+        for (int i = 0; i < NHS; ++i) bc[i] = load_elem<double>(rb, boff, (kpart + S * i) * bstep);
+    }
+    __syncthreads();  // waits for every load: the first tile is complete
+    // the products of one half: n K-steps from Lc, of which this wave takes k0, k0 + S, ..., with the
+    // operands in bc, each operand register then refilled with the next half's operand (steps k1,
+    // k1 + S, ... after byte offset b1 of rbn)
+    auto products = [&](const float4* Lc, int n, int k0, __amdgpu_buffer_rsrc_t rbn, int k1, uint32_t b1) {
+        const int ns = mma ? n : 0;
+        Quad<double> a = lds_quad<double>(Lc, k0 < NH ? k0 : NH - 1, lane);
+#pragma unroll
+        for (int i = 0; i < NHS; ++i) {
+            const int st = k0 + S * i;
+            Quad<double> an = a;
+            if (i + 1 < NHS) an = lds_quad<double>(Lc, st + S < NH ? st + S : NH - 1, lane);
+            if (st < ns) {
+                acc[0] = Mma<double>::op(a.x, bc[i], acc[0]);
+                acc[1] = Mma<double>::op(a.y, bc[i], acc[1]);
+                acc[2] = Mma<double>::op(a.z, bc[i], acc[2]);
+                acc[3] = Mma<double>::op(a.w, bc[i], acc[3]);
+            }
+            bc[i] = load_elem<double>(rbn, boff, b1 + (k1 + S * i) * bstep);
+            a = an;
+        }
+    };
+    // this wave's requests of half u + 1 (made at the start of half u - 1) are complete when no more
+    // than the loads issued after them are outstanding: the NHS B operands of half u - 1, half u's
+    // requests and NHS B operands, less one to spare (vmcnt field split over bits 3:0 and 15:14;
+    // expcnt and lgkmcnt not waited for); the barrier then makes every wave's part visible and frees
+    // the buffer just read
+    auto end_half = [&]() {
+        constexpr int VM = 2 * NHS + NREQ - 1;
+        static_assert(VM < 64, "vmcnt range");
+        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
+        // (the empty statements keep the compiler from moving memory accesses across the
+        // barrier, which itself orders none)
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    // one tile: its halves are in buffers P and P + 1; the next tile's go to P + 2 and P
+    auto tile = [&](int e, auto par) {
+        constexpr int P = decltype(par)::value;
+        float4* const L0 = P == 0 ? lb0 : (P == 1 ? lb1 : lb2);
+        float4* const L1 = P == 0 ? lb1 : (P == 1 ? lb2 : lb0);
+        float4* const L2 = P == 0 ? lb2 : (P == 1 ? lb0 : lb1);
+        const v4u dn = __builtin_amdgcn_raw_buffer_load_b128(
+            rt, 0, static_cast<uint32_t>(e + 2 - t_beg) * 16u, 0);
+        const bool more = e + 1 < t_end;
+        const int n = Te.nstep, h = (n + 1) / 2;
+        const int nn = more ? Tn.nstep : 0, hn = (nn + 1) / 2;
+        request(Tn, 0, hn, L2);
+        // (the second half's first step is step h of the tile)
+        const int k1 = S == 1 ? 0 : (kpart ^ (h & 1));
+        products(L0, h, kpart, b_rsrc(Te, true), k1, static_cast<uint32_t>(h) * bstep);
+        end_half();
+        request(Tn, hn, nn - hn, L0);
+        products(L1, n - h, k1, b_rsrc(Tn, more), kpart, 0u);
+        end_half();
+        Te = Tn;
+        Tn = to_desc(dn);
+    };
+    // the buffers cycle with the tile's position in the item: three copies of the tile in
+    // sequence, so that no branch selects among them
+    for (int e = t_beg; e < t_end;) {
+        tile(e++, std::integral_constant<int, 0>{});
+        if (e >= t_end) break;
+        tile(e++, std::integral_constant<int, 2>{});
+        if (e >= t_end) break;
+        tile(e++, std::integral_constant<int, 1>{});
+    }
+    asm volatile("" ::"v"(bc[NHS - 1]));  // its load stays before the wait, as in k_far_wide
+    __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // every request into LDS has landed
+    __syncthreads();
+    add_waves();
+    if (o_self != nullptr && t_mid == t_end && t_mid > t_beg)
+        write_sums(o_self + static_cast<size_t>(C.start) * ncols);
+    write_sums(o_all);
+}
+
 // Sums of the chunks cut into pieces: for each target row and column, the pieces' FP64 partial
 // sums added in piece order (own-surface pieces first; their sum is the own-surface result).  A
 // product's row combination adds them itself; this pass serves the readers of plain sums.
@@ -2412,6 +2622,16 @@ void launch_far_half(Geometry& g, int pad, const float* dens, const float* mom, 
     LSPR_HIP(hipGetLastError());
 }
 
+template <int NSM, int S, int W>
+void launch_far_narrow64(Geometry& g, int pad, int nops, const double* dens, const double* mom, double* os,
+                         double* oa, double* part, hipStream_t s) {
+    const Geometry::FarPlan& fp = far_plan_for(g, pad);
+    hipLaunchKernelGGL((k_far_narrow64<NSM, S, W>), dim3(fp.n_order * nops), dim3(64 * W), 0, s, g.chunks.p,
+                       fp.items.p, fp.order.p, g.tile_self.p, g.tiles.p, g.tileA64.p, dens, mom, pad,
+                       pad / 16, nops, os, oa, part);
+    LSPR_HIP(hipGetLastError());
+}
+
 template <int NSM>
 void launch_far_wide64(Geometry& g, int pad, const double* dens, const double* mom, double* os,
                        double* oa, double* part, hipStream_t s) {
@@ -2438,6 +2658,19 @@ void launch_far_tiles_op(Geometry& g, int pad, int nops, int abuf, const T* dens
             if (groups == 1) launch_far_wide<NSM, 8>(g, pad, nops, dens, mom, os, oa, part, s);
             else launch_far_wide<NSM, 4>(g, pad, nops, dens, mom, os, oa, part, s);
             return;
+        }
+    }
+    // FP64 products of 17 to 64 columns per operator in half tiles, at P = 6 to 15 but 10 (whose three
+    // buffers would leave one workgroup per CU).  Far field with k_far_tiles_op and with these, us, at 13,
+    // 21 and 32 wavelengths: 72, 94, 103 -> 58, 85, 89 (4672 panels, P = 6); 171, 239, 247 -> 138, 197,
+    // 207 (8192, P = 8); 724, 950, 964 -> 602, 874, 912 (25992, P = 8); 251, 390, 397 -> 240, 304, 311
+    // (8712, P = 15).  One column group is bound by the tiles' bytes and gains nothing from eight waves in
+    // half tiles (507 and 515 at 25992 panels); at P = 4 they cost 1 us of 9 (512 panels).
+    if constexpr (std::is_same<T, double>::value && NSM >= 13 && NSM <= 21) {
+        if (!g.four_wave && !g.stream_narrow && !g.pair_narrow && !g.pair_ops) {
+            if (groups == 2) return launch_far_narrow64<NSM, 2, 4>(g, pad, nops, dens, mom, os, oa, part, s);
+            if (groups == 3) return launch_far_narrow64<NSM, 1, 3>(g, pad, nops, dens, mom, os, oa, part, s);
+            if (groups == 4) return launch_far_narrow64<NSM, 1, 4>(g, pad, nops, dens, mom, os, oa, part, s);
         }
     }
     if (groups == 1) {

@@ -111,6 +111,25 @@ def test_half_tile_products_equal_four_wave_products(lib, p):
             assert torch.equal(half.apply(x, em, es), want), (p, nl)
 
 
+# FP64 products of 9 to 32 wavelengths in half tiles: two to four column groups at every order that has
+# them, odd and even halves, direct tiles of one step and three surfaces; the same products in the same
+# order as the four-wave workgroups, so equal bit for bit, on every repeat
+@pytest.mark.parametrize("p", [6, 8, 12, 15])
+def test_half_tile_fp64_products_equal_four_wave_products(lib, p):
+    surfs = _surfaces(13, (5, 6))
+    n = sum(len(t) for _, t in surfs)
+    kw = dict(method="treecode", precision="fp64", p=p, theta=0.5)
+    four, half = lib.Geometry(surfs, four_wave=True, **kw), lib.Geometry(surfs, **kw)
+    rng = np.random.default_rng(p)
+    for nl in (9, 13, 16, 17, 24, 25, 32):
+        x = torch.as_tensor(rng.standard_normal((nl, 2 * n)) + 1j * rng.standard_normal((nl, 2 * n))).cuda()
+        em = np.full(nl, 1.7733)
+        es = np.stack([-3.0 + 0.3j + rng.standard_normal(nl)] + [np.full(nl, 2.5)] * 2, 1)
+        want = four.apply(x, em, es)
+        for _ in range(4):
+            assert torch.equal(half.apply(x, em, es), want), nl
+
+
 # a mesh of few chunks, whose far field is cut into pieces of a few tiles: every launch class (1-16,
 # 17-32 and 33-64 wavelengths), several surfaces (own-surface pieces apart) and a ragged last
 # chunk; FP32 sums of whole tiles round as before, so 2e-6 of the largest entry bounds them (single
