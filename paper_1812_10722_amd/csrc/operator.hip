@@ -2916,9 +2916,12 @@ FarSums apply_far_t(Geometry& g, const Cols& c, const T* dens, double* os, doubl
         // are geometry-only factors computed once at set-up, and the launch reads them instead
         // (the tile store, once).
         const bool pre = c.mfma && tiles_of<T>(g) != nullptr;
-        const double f = double(g.p2p_pairs) * (4.0 * nc + (pre ? 0.0 : 15.0 * g.K + 9.0)) +
-                         double(g.m2p_pairs) * g.n_terms * (4.0 * nc + (pre ? 0.0 : 10.0));
-        const double tile_bytes = pre ? double(g.tile_elems) * esz : 0.0;
+        // (a product of the V columns alone: one operator's flops, one factor of a direct tile)
+        const double ncc = (c.v_only ? 2.0 : 4.0) * nc;
+        const double f = double(g.p2p_pairs) * (ncc + (pre ? 0.0 : 15.0 * g.K + 9.0)) +
+                         double(g.m2p_pairs) * g.n_terms * (ncc + (pre ? 0.0 : 10.0));
+        const double tile_bytes =
+            pre ? (double(g.tile_elems) - (c.v_only ? double(g.p2p_pairs) : 0.0)) * esz : 0.0;
         prof::Scope sc(fp64 ? "far64" : "far", s, f,
                        tile_bytes + dens_bytes + mom_bytes + out_bytes,
                        (double(g.p2p_pairs) * g.K + double(g.m2p_pairs)) * (nc / 2),
