@@ -329,7 +329,8 @@ typedef struct {
     int64_t submitted, completed, queued, active;
     int64_t max_active;           /* most requests on the device at once so far */
     int64_t budget_bytes, reserved_bytes, peak_reserved_bytes;
-    int64_t estimate_violations;  /* requests whose measured peak exceeded their estimate */
+    int64_t estimate_violations;  /* requests whose measured peak exceeded their estimate, or what
+                                   * they still had reserved after their set-up */
 } lspr_server_stats;
 
 /* Creates a server on the current device (worker threads, one non-blocking stream per slot at

@@ -589,12 +589,11 @@ int64_t solve_bytes(int64_t N, int S, int B, const lspr_op_params& op,
     const int64_t nvec = 2 * N, m1 = gm.restart + 1;
     const int64_t esz = op.precision == LSPR_FP32 ? 4 : 8;  // largest product precision
     const int64_t pad = (2 * B + 15) / 16 * 16;
-    const int64_t nblk = (nvec + 4095) / 4096 + 1;  // Arnoldi blocks of 4096 elements
     int64_t b = 0;
     b += static_cast<int64_t>(B) * m1 * nvec * 16;                 // Krylov basis
     b += static_cast<int64_t>(B) * nvec * 16 * 3;                  // x, w, b
-    // partial inner products (one per wave of each block), Hessenberg matrices, coefficients
-    b += static_cast<int64_t>(B) * (2 * m1 + 3) * 4 * nblk * 16;
+    // partial inner products, Hessenberg matrices, coefficients
+    b += arnoldi_partials(nvec, B, gm.restart) * 16;
     b += 2 * static_cast<int64_t>(B) * m1 * m1 * 16 + static_cast<int64_t>(B) * (8 * m1 + 64) * 16;
     if (op.precision == LSPR_FP32_REFINE64)
         b += static_cast<int64_t>(B) * nvec * 16 * 4;              // refinement b, r, d, w
@@ -606,6 +605,8 @@ int64_t solve_bytes(int64_t N, int S, int B, const lspr_op_params& op,
     for (int64_t n = N; n > terms; n /= 4) ++levels;
     const int64_t rows = levels * (N / std::max<int64_t>(terms, 1) + S) * terms;
     b += 2 * rows * 2 * pad * esz;
+    // small buffers: the slab in use, and the unused ends of the slabs before it
+    b += 3 * static_cast<int64_t>(SLAB_MOST);
     return b;
 }
 
@@ -626,7 +627,7 @@ int64_t request_footprint(int64_t N, int S, int n_lambda, const lspr_op_params& 
     int64_t b = N * (1024 + 24 * S + (4 + 4 * op.k_far) * esz + 96 * 20) + (64 << 20);
     b += N * 32 * (esz + 16);
     if ((op.flags & LSPR_NO_MATRIX_CORES) == 0)
-        b += tile_cap_bytes(N, op);
+        b += tile_cap_bytes(N, op) + static_cast<int64_t>(far_part_bound(N, S, B));
     return b + solve_bytes(N, S, B, op, gm);
 }
 

@@ -58,8 +58,8 @@ bool solve_geometry(Geometry& g, int n_lambda, const double* lambda_nm,
                     lspr_c64* phi, lspr_c64* dphi, lspr_c64* p_sensor, lspr_c64* p_total,
                     double* cext_sensor, double* cext_total, int32_t* iters, double* rel_resid);
 
-// Device bytes the solve phase allocates (GMRES state and operator workspaces) for one batch of
-// B wavelengths on a geometry of N panels and S surfaces.
+// Device bytes the solve phase allocates (GMRES state and operator workspaces, without the far-field
+// pieces' partial sums) for one batch of B wavelengths on a geometry of N panels and S surfaces.
 int64_t solve_bytes(int64_t N, int S, int B, const lspr_op_params& op,
                     const lspr_gmres_params& gm);
 // Upper bound of the matrix-core tile store kept for a geometry of N panels in the given

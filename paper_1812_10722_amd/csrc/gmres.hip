@@ -699,10 +699,10 @@ ArnoldiShape arnoldi_shape(int64_t nvec, int ns, int nq) {
 }
 // Blocks (over all vectors) of the largest launch for up to B vectors: at most 4 SMALL_BLOCKS,
 // or those of 16 elements per thread.
-size_t arnoldi_blocks(int64_t nvec, int B) {
-    const int nb = blocks_for(nvec), small = std::min(B, (SMALL_BLOCKS - 1) / nb);
-    return std::max<size_t>(static_cast<size_t>(B) * nb,
-                            static_cast<size_t>(small) * small_blocks_for(nvec));
+int64_t arnoldi_blocks(int64_t nvec, int B) {
+    const int64_t nb = std::max<int64_t>(1, (nvec + GSLICE - 1) / GSLICE);
+    const int64_t small = std::min<int64_t>(B, (SMALL_BLOCKS - 1) / nb);
+    return std::max(B * nb, small * ((nvec + GT * GE_SMALL - 1) / (GT * GE_SMALL)));
 }
 
 // Pinned, coherent host memory for the residual estimates, which the finishing kernel writes
@@ -765,6 +765,10 @@ struct Event {
 
 }  // namespace
 
+int64_t arnoldi_partials(int64_t nvec, int B, int restart) {
+    return (2ll * (restart + 1) + 3) * 4 * arnoldi_blocks(nvec, B);
+}
+
 SolveResult gmres_solve(Geometry& g, int prec, int B, const double2* ratio_d,
                         const double* e_field, const lspr_gmres_params& gm, const double2* b_in,
                         double2* x, hipStream_t s) {
@@ -777,8 +781,7 @@ SolveResult gmres_solve(Geometry& g, int prec, int B, const double2* ratio_d,
     DevBuf<double2> Hr(static_cast<size_t>(B) * m * m1), H(static_cast<size_t>(B) * m * m1);
     DevBuf<double2> hp(B * (m1 + 1)), cs(B * m), sn(B * m), gv(B * m1), y(B * m);
     DevBuf<double2> coef(B * kmax);
-    // one partial sum per inner product and wave
-    DevBuf<double2> part(kmax * 4 * arnoldi_blocks(nvec, B));
+    DevBuf<double2> part(arnoldi_partials(nvec, B, m));
     DevBuf<double> part2(static_cast<size_t>(B) * nblk), inv(B), nrm(B);
     DevBuf<double> nu(B), r_fin(B);
     DevBuf<int32_t> cols_d(B), jn_d(B), fin(B);

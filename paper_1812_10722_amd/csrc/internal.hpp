@@ -637,6 +637,10 @@ void put_plan(std::unique_ptr<TilePlan> p);
 // Scratch bytes the far-field pieces of a product of pad columns per operator write.
 size_t far_part_bytes(int n_slots, int pad);
 size_t far_part_bytes(const Geometry& g, int pad);
+// The most of them for products of up to B wavelengths: of this geometry's plans, and of any
+// geometry of N panels and S surfaces.
+size_t far_part_most(const Geometry& g, int B);
+size_t far_part_bound(int64_t N, int S, int B);
 // Whether every product of launch class `cls` that lspr_apply_noalloc runs with `before` partial-
 // sum slots fits its scratch with `after` too.
 bool noalloc_keeps_fitting(const Geometry& g, int cls, int before, int after);

@@ -2560,6 +2560,11 @@ size_t far_part_bytes(int n_slots, int pad) {
 size_t far_part_bytes(const Geometry& g, int pad) {
     return far_part_bytes(far_plan_for(g, pad).n_slots, pad);
 }
+size_t far_part_most(const Geometry& g, int B) {
+    size_t most = 0;
+    for (int pad = 16; pad < 2 * B + 16; pad += 16) most = std::max(most, far_part_bytes(g, pad));
+    return most;
+}
 
 namespace {
 
@@ -3173,6 +3178,18 @@ bool plan_items(const std::vector<uint8_t>& steps, const std::vector<int32_t>& o
     for (int r = 0; r < 8; ++r)
         for (size_t i = 0; i < runs[r].size(); ++i) W.order[i * 8 + r] = runs[r][i];
     return true;
+}
+
+// Slots of plan_items for nc chunks.  A first cut into pieces of a limit l makes at most total / l
+// pieces and one more for either side of each chunk's own-surface boundary, and cutting the runs'
+// ends by l / 4 adds 4 (tail total + 8 (l + a tile)) / l: with the first limit (total / l = nc)
+// 3 nc + 0.8 nc + 32 and the tiles, with the fine one (total / l <= FINE_ITEMS, l >= FINE_COST; up
+// to 0.45 FINE_ITEMS chunks) 2 nc + 512 + 452.
+size_t far_part_bound(int64_t N, int S, int B) {
+    const int64_t nc = N / NT + S;
+    int64_t slots = 4 * nc + 128;
+    if (nc <= static_cast<int64_t>(0.45 * FINE_ITEMS)) slots = std::max<int64_t>(slots, 2 * nc + 968);
+    return static_cast<size_t>(slots) * NT * 2 * ((2 * B + 15) / 16 * 16) * sizeof(double);
 }
 
 namespace {

@@ -48,6 +48,7 @@ struct Request {
     std::vector<int32_t> iters;
     double t_submit = 0, t_admit = 0, t_done = 0;
     int64_t peak = 0;
+    bool over = false;  // the solve held more than the request still had reserved
     bool done = false;
 };
 
@@ -82,6 +83,7 @@ void lspr_server::run(Request& r, hipStream_t s) {
     lspr::AllocCtx& ctx = lspr::alloc_ctx();
     const int64_t base = ctx.live;
     ctx.peak = ctx.live;
+    int64_t setup_peak = 0;
     try {
         std::vector<lspr_surface> host(r.S), dev(r.S);
         for (int k = 0; k < r.S; ++k)
@@ -109,10 +111,13 @@ void lspr_server::run(Request& r, hipStream_t s) {
             lspr::set_charges(g, static_cast<int>(r.qval.size()), r.qpos.data(), r.qval.data(),
                               r.qsurf.data(), s);
         // the set-up is done: keep only what the solve still needs reserved
+        setup_peak = ctx.peak;
+        ctx.peak = ctx.live;
         {
+            // what the geometry holds, its slabs in whole, and the solve on top
             const int64_t need =
-                static_cast<int64_t>(g.device_bytes()) +
-                lspr::solve_bytes(r.n_panels, r.S, r.B, r.op, r.gm);
+                ctx.live - base + lspr::solve_bytes(r.n_panels, r.S, r.B, r.op, r.gm) +
+                static_cast<int64_t>(lspr::far_part_most(g, r.B));
             std::lock_guard<std::mutex> lk(mu);
             if (need < r.reserved) {
                 reserved -= r.reserved - need;
@@ -150,7 +155,8 @@ void lspr_server::run(Request& r, hipStream_t s) {
         r.status = LSPR_E_DEVICE;
         r.error = "stream synchronisation failed";
     }
-    r.peak = ctx.peak - base;
+    r.over = ctx.peak - base > r.reserved;
+    r.peak = std::max(setup_peak, ctx.peak) - base;
 }
 
 void lspr_server::worker(int w) {
@@ -193,7 +199,7 @@ void lspr_server::worker(int w) {
             r->reserved = 0;
             --active;
             ++completed;
-            if (r->peak > r->est) ++violations;
+            if (r->peak > r->est || r->over) ++violations;
             r->t_done = now();
             r->done = true;
         }

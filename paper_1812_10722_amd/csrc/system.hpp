@@ -45,6 +45,10 @@ struct SolveResult {
     bool all_converged = true;
 };
 
+// Partial inner products of a solve of B columns (double2): one per inner product and wave of the
+// largest launch.
+int64_t arnoldi_partials(int64_t nvec, int B, int restart);
+
 // Batched GMRES for columns 0..B-1 with far-field products in precision prec; b_in holds the
 // right-hand sides [B][2N] (sorted order), or is null for the system's own (e_field);
 // x_out receives the solutions [B][2N] (sorted order).

@@ -247,3 +247,27 @@ def test_burst_of_large_requests_all_succeed(lib):
     assert all(r["status"] == lib.LSPR_OK for r in out), [(r["status"], r["error"]) for r in out]
     assert st["estimate_violations"] == 0
     assert all(0 < r["peak_bytes"] <= r["est_bytes"] for r in out)
+
+
+@pytest.mark.parametrize("nu,p,precision,restart", [(22, 15, "fp32", 40), (16, 15, "fp64", 60),
+                                                    (16, 8, "fp32", 512), (22, 15, "fp32_lead64", 40),
+                                                    (11, 2, "fp32", 40)])
+def test_solve_stays_within_what_is_reserved(lib, nu, p, precision, restart):
+    """After its set-up a request keeps only what its solve needs reserved, and the solve of a small
+    mesh at the widest batch (far-field pieces cut finely, Arnoldi passes in small blocks, small
+    buffers in slabs) holds no more than that: the server counts a violation otherwise."""
+    lam = np.linspace(350.0, 420.0, 64)
+    em = np.full(64, EPS_WATER + 0j)
+    es = eps_silver_drude(lam)[:, None]
+    sv = lib.Server(max_slots=1)
+    try:
+        r = sv.poll(sv.submit([octasphere(nu, 10.0)], lam, em, es,
+                              op=lib.op_params(p=p, precision=precision),
+                              gmres=lib.gmres_params(tol=1e-5, restart=restart, max_iter=600)),
+                    wait=True)
+        st = sv.stats()
+    finally:
+        sv.close()
+    assert r["status"] == lib.LSPR_OK, r["error"]
+    assert 0 < r["peak_bytes"] <= r["est_bytes"]
+    assert st["estimate_violations"] == 0
