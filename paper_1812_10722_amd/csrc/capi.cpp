@@ -186,23 +186,44 @@ std::vector<lspr::PinnedBuf> pinned_free;  // staging buffers not in use
 constexpr size_t PINNED_KEEP_BYTES = 1ull << 30;
 }  // namespace
 
+// Whether the device has finished with f (whose event is then gone).
+static bool pinned_idle(PinnedBuf& f) {
+    if (f.busy == nullptr) return true;
+    const hipError_t e = hipEventQuery(f.busy);
+    if (e != hipSuccess) {
+        (void)hipGetLastError();  // "not ready" is no failure of the next call's
+        return false;
+    }
+    (void)hipEventDestroy(f.busy);
+    f.busy = nullptr;
+    return true;
+}
+
 PinnedBuf pinned_take(size_t bytes) {
+    const size_t cap = ((bytes > 0 ? bytes : 1) + (1u << 20) - 1) & ~static_cast<size_t>((1u << 20) - 1);
     PinnedBuf b;
     {
-        // the smallest free buffer that holds the request
+        // The smallest free buffer that holds the request and that the device has finished with.  A
+        // buffer still in use may be behind a whole set-up, or on another request's stream: it is
+        // waited for only where a new one would exceed what the pool keeps.  (Nor does a small
+        // request take a list's buffer, which the next list would then allocate anew.)
         std::lock_guard<std::mutex> lk(pinned_mu);
-        int best = -1;
-        for (size_t i = 0; i < pinned_free.size(); ++i)
-            if (pinned_free[i].cap >= bytes &&
-                (best < 0 || pinned_free[i].cap < pinned_free[best].cap))
-                best = static_cast<int>(i);
-        if (best >= 0) {
-            b = pinned_free[best];
-            pinned_free.erase(pinned_free.begin() + best);
+        int idle = -1, other = -1;
+        size_t total = cap;
+        for (size_t i = 0; i < pinned_free.size(); ++i) {
+            total += pinned_free[i].cap;
+            if (pinned_free[i].cap < bytes) continue;
+            int& best = pinned_free[i].cap <= 16 * cap && pinned_idle(pinned_free[i]) ? idle : other;
+            if (best < 0 || pinned_free[i].cap < pinned_free[best].cap) best = static_cast<int>(i);
+        }
+        const int take = idle >= 0 ? idle : (total > PINNED_KEEP_BYTES ? other : -1);
+        if (take >= 0) {
+            b = pinned_free[take];
+            pinned_free.erase(pinned_free.begin() + take);
         }
     }
     if (b.p != nullptr) {
-        if (b.busy != nullptr) {  // its last kernel has finished, as a rule
+        if (b.busy != nullptr) {
             const hipError_t e = hipEventSynchronize(b.busy);
             (void)hipEventDestroy(b.busy);
             b.busy = nullptr;
@@ -213,7 +234,7 @@ PinnedBuf pinned_take(size_t bytes) {
         }
         return b;
     }
-    b.cap = ((bytes > 0 ? bytes : 1) + (1u << 20) - 1) & ~static_cast<size_t>((1u << 20) - 1);
+    b.cap = cap;
     LSPR_HIP(hipHostMalloc(reinterpret_cast<void**>(&b.p), b.cap,
                            hipHostMallocPortable | hipHostMallocCoherent));
     return b;
@@ -240,10 +261,17 @@ void pinned_put(PinnedBuf b) {
         pinned_free.push_back(b);
         size_t total = 0;
         for (const PinnedBuf& f : pinned_free) total += f.cap;
-        while (total > PINNED_KEEP_BYTES && pinned_free.size() > 1) {  // drop the smallest
+        while (total > PINNED_KEEP_BYTES && pinned_free.size() > 1) {
+            // drop the smallest, of those that the device has finished with if there is one
             size_t k = 0;
-            for (size_t i = 1; i < pinned_free.size(); ++i)
-                if (pinned_free[i].cap < pinned_free[k].cap) k = i;
+            bool k_idle = pinned_idle(pinned_free[0]);
+            for (size_t i = 1; i < pinned_free.size(); ++i) {
+                const bool idle = pinned_idle(pinned_free[i]);
+                if (idle != k_idle ? idle : pinned_free[i].cap < pinned_free[k].cap) {
+                    k = i;
+                    k_idle = idle;
+                }
+            }
             total -= pinned_free[k].cap;
             drop.push_back(pinned_free[k]);
             pinned_free.erase(pinned_free.begin() + k);

@@ -232,8 +232,8 @@ struct PinnedBuf {
     size_t cap = 0;
     hipEvent_t busy = nullptr;  // (kept in the pool) its last use on the device
 };
-// A free buffer of at least `bytes` (a new one, a multiple of 1 MiB, if none is free), no longer
-// used by the device.
+// A buffer of at least `bytes` that the device does not use: a free one, or a new one (a multiple of
+// 1 MiB) where none is free and finished with and the pool is not full.
 PinnedBuf pinned_take(size_t bytes);
 // Back to the pool; `s`: a stream whose queued work still uses the buffer (or nothing does).
 void pinned_put(PinnedBuf b);
@@ -251,7 +251,8 @@ void move_blocks(const Move* m, size_t n, hipStream_t s);
 // Batched host-to-device uploads of set-up code.  add() copies host data into one pinned buffer (so
 // temporaries may be passed); flush() queues one kernel that reads the buffer and writes every
 // destination, instead of a transfer, a wait and a copy per destination.  The buffer goes back to
-// the pool behind that kernel, so nothing waits for it.
+// the pool behind that kernel: the host does not wait for it, and a later user takes it only once
+// the kernel has ended (pinned_take).
 class Uploads {
   public:
     explicit Uploads(hipStream_t s) : s_(s) {}
