@@ -324,9 +324,10 @@ __global__ void k_lists_fill(const Box* __restrict__ boxes, const Chunk* __restr
 
 struct NearParams {
     double inv_thr;
-    int n_leaves;
-    const int32_t* leaf;  // [n_leaves] boxes of the leaves, in panel order
-    int32_t* maxcnt;      // largest count of a target (counting walk)
+    int n_leaves, S;
+    const int32_t* leaf;   // [n_leaves] boxes of the leaves, in panel order (k_near)
+    const int32_t* roots;  // [S] (k_near_walk)
+    int32_t* maxcnt;       // largest count of a target (counting walk)
 };
 
 // Near-singular source panels of every target panel, all surfaces, ascending index order.
@@ -339,9 +340,9 @@ struct NearParams {
 // lanes for the test itself.  The waves' counts, in order, are the places of their panels; a wave
 // holds up to NEAR_KEEP panels of a lane from its counting and goes through its share again only
 // where a lane has more.
-// Latency-bound.  A thread going down the trees for its own target took 303 us at 32768 panels and
-// 168 us at 512, a wave going down them for a chunk 266 and 127 us; this, with 1, 4, 8 and 16 waves:
-// 917, 316, 236, 240 and 193, 71, 43, 32 us.
+// Latency-bound.  A thread going down the trees for its own target (k_near_walk) took 303 us at 32768
+// panels and 168 us at 512, a wave going down them for a chunk 266 and 127 us; this, with 1, 4, 8 and
+// 16 waves: 917, 316, 236, 240 and 193, 71, 43, 32 us.  For meshes of few leaves (near_by_chunk).
 constexpr int NEAR_WAVES = 16;
 constexpr int NEAR_KEEP = 12;
 __device__ inline double from_lane(double v, int k) {
@@ -455,6 +456,60 @@ k_near(const Box* __restrict__ boxes, const Chunk* __restrict__ chunks,
         for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o, 64));
         if (lane == 0) atomicMax(np.maxcnt, most);
     }
+}
+
+// The same by a walk down every tree for each target, one thread each (depth-first without a stack: into
+// the first child, or past the box's subtree).  Bound by the latency of the walk, whatever the number of
+// panels: 160 us with one panel per leaf, 300-370 us with about six, 690 us with 21 (up to 65000
+// panels); 384 us at 111392 and 901 us at 492032 panels, where k_near takes 961 us and 8.4 ms.
+__global__ void k_near_walk(const Box* __restrict__ boxes, const double* __restrict__ cen,
+                            const double* __restrict__ area, int N, NearParams np, bool fill,
+                            int64_t* __restrict__ cnt, const int64_t* __restrict__ off,
+                            int32_t* __restrict__ col, int32_t* __restrict__ slot, int cap) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N) return;
+    const double x = cen[3 * i], y = cen[3 * i + 1], z = cen[3 * i + 2];
+    int64_t k = fill ? off[i] : 0;
+    int n = 0;
+    for (int s = 0; s < np.S; ++s) {
+        int bi = np.roots[s];
+        while (bi >= 0) {
+            const Box B = boxes[bi];
+            const double dx = x - B.cx, dy = y - B.cy, dz = z - B.cz;
+            const double d = sqrt(dx * dx + dy * dy + dz * dz);
+            const bool far = d - B.rv > B.lmax * np.inv_thr * (1.0 + 1e-9) + 1e-12;
+            if (!far && B.nchild > 0) {
+                bi = B.child;
+                continue;
+            }
+            if (!far) {
+                for (int j = B.start; j < B.end; ++j) {
+                    if (j == i) continue;
+                    const double ex = x - cen[3 * j], ey = y - cen[3 * j + 1], ez = z - cen[3 * j + 2];
+                    const double dj = sqrt(ex * ex + ey * ey + ez * ez);
+                    if (dj <= sqrt(2.0 * area[j]) * np.inv_thr) {
+                        if (fill) col[k + n] = j;
+                        else if (slot != nullptr && n < cap) slot[static_cast<size_t>(i) * cap + n] = j;
+                        ++n;
+                    }
+                }
+            }
+            bi = B.next;
+        }
+    }
+    if (!fill) {
+        cnt[i] = n;
+        atomicMax(np.maxcnt, n);
+    }
+}
+
+// Which of the two: k_near tries every leaf for every chunk, about 45 us + 0.065 ns per pair of them
+// (256 chunks run at a time), the walk takes about 130 us and 27 us per panel of a leaf.  Measured on
+// either side of the line, k_near and the walk, us: 32768 panels, 4900 leaves 213, 292; 40328, 5528: 285,
+// 294; 48672, 7232: 364, 316; 64800, 3104: 406, 677; 12800, 12800: 225, 164; 16200, 8576: 220, 200.
+bool near_by_chunk(const Geometry& g) {
+    const double tries = double(std::max(g.n_chunks, 256)) * g.n_leaves;
+    return tries <= 1.3e6 + 0.4e6 * g.N / g.n_leaves;
 }
 
 // The counting walk's slots moved into the table: one wave per target, lane e copies entry e.
@@ -783,11 +838,15 @@ void build_lists(Geometry& g) {
 void build_near_table(Geometry& g, const std::function<void()>& meanwhile) {
     hipStream_t s = g.stream;
     const int N = g.N;
-    // one upload: leaves, the fine rule and the Gauss-Legendre nodes of V_ii
+    // one upload: leaves (or the trees' roots), the fine rule and the Gauss-Legendre nodes of V_ii
     const std::vector<double> fine_h = rule_rows(g.Kf);
     std::vector<double> t, w;
     gauss_legendre(g.Nk, t, w);
-    std::vector<int32_t> leaf_h = g.leaf_h;
+    const bool by_chunk = near_by_chunk(g);
+    std::vector<int32_t> leaf_h;
+    if (by_chunk) leaf_h = g.leaf_h;
+    else leaf_h.assign(g.surf_root.begin(), g.surf_root.end());
+    const size_t n_leaf = leaf_h.size();
     leaf_h.push_back(0);  // largest count
     DevBuf<int32_t> leaf(leaf_h.size());
     DevBuf<double> fine(fine_h.size()), t_d(t.size()), w_d(w.size());
@@ -797,7 +856,7 @@ void build_near_table(Geometry& g, const std::function<void()>& meanwhile) {
     up.add(t_d.p, t.data(), t.size());
     up.add(w_d.p, w.data(), w.size());
     up.flush();
-    NearParams np{1.0 / g.threshold, g.n_leaves, leaf.p, leaf.p + g.n_leaves};
+    NearParams np{1.0 / g.threshold, g.n_leaves, g.S, leaf.p, leaf.p, leaf.p + n_leaf};
     DevBuf<int64_t> cnt(N + 1);
     const dim3 grid((N + TPB - 1) / TPB), blk(TPB);
     // The counting walk keeps the first NEAR_CAP panels of each target; when no target has
@@ -806,8 +865,13 @@ void build_near_table(Geometry& g, const std::function<void()>& meanwhile) {
     DevBuf<int32_t> slot;
     if (static_cast<size_t>(N) * NEAR_CAP * 4 <= (size_t(512) << 20)) slot.alloc(static_cast<size_t>(N) * NEAR_CAP);
     auto walk = [&](bool fill, int64_t* count, const int64_t* off, int32_t* col) {
-        hipLaunchKernelGGL(k_near, dim3(g.n_chunks), dim3(64 * NEAR_WAVES), 0, s, g.boxes.p, g.chunks.p,
-                           g.cen.p, g.area.p, np, fill, count, off, col, fill ? nullptr : slot.p, NEAR_CAP);
+        int32_t* keep = fill ? nullptr : slot.p;
+        if (by_chunk)
+            hipLaunchKernelGGL(k_near, dim3(g.n_chunks), dim3(64 * NEAR_WAVES), 0, s, g.boxes.p, g.chunks.p,
+                               g.cen.p, g.area.p, np, fill, count, off, col, keep, NEAR_CAP);
+        else
+            hipLaunchKernelGGL(k_near_walk, grid, blk, 0, s, g.boxes.p, g.cen.p, g.area.p, N, np, fill, count,
+                               off, col, keep, NEAR_CAP);
     };
     walk(false, cnt.p, nullptr, nullptr);
     LSPR_HIP(hipGetLastError());

@@ -178,6 +178,29 @@ def test_near_panels_of_every_target(lib, nu, threshold, ncrit):
     assert _worst(y, ref) < 1e-12
 
 
+# the same search by a walk down the trees for each target (more leaves than trying each for each chunk
+# is worth: here one panel per leaf), with few, dozens and over 64 near panels per target, two meshes
+# beside the sphere; rows of the oracle
+@pytest.mark.parametrize("threshold", [0.5, 0.2, 0.1])
+def test_near_panels_by_tree_walk(lib, threshold):
+    surfs = _surfaces(29, (6, 5))
+    v, t, sid = merge_surfaces(surfs)
+    n = len(t)
+    rows = np.unique(np.r_[0:n:401, n - 350:n:25, n - 1])
+    V, K = oracle.operators.operator_rows(v, t, rows, 4, 19, 9, threshold)
+    rng = np.random.default_rng(29)
+    x = rng.standard_normal((1, 2 * n)) + 1j * rng.standard_normal((1, 2 * n))
+    em, es = np.array([1.7733]), np.array([[-3.38 + 0.2j, 2.5, 2.4]])
+    geo = lib.Geometry(surfs, method="dense", precision="fp64", threshold=threshold, ncrit=1)
+    y = geo.apply(torch.as_tensor(x).cuda(), em, es).cpu().numpy()[0]
+    phi, sig = x[0, :n], x[0, n:]
+    same = sid[rows][:, None] == sid[None, :]
+    top = 0.5 * phi[rows] + np.where(same, K, 0) @ phi - np.where(same, V, 0) @ sig
+    low = 0.5 * phi[rows] - K @ phi + (V * (es[0][sid] / em[0])[None, :]) @ sig
+    for got, ref in ((y[rows], top), (y[n + rows], low)):
+        assert np.abs(got - ref).max() / np.abs(y).max() < 2e-12  # (7500 products per sum)
+
+
 # the right-hand side's columns run through V alone: one and two column groups per operator (3, 6 and
 # 18 columns) and both precisions, at orders whose narrow products have their own kernels; with
 # theta 0.05 every pair is summed directly (tolerances as above), with 0.5 the expansions' relative
