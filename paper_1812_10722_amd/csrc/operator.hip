@@ -549,6 +549,21 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* p, uin
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00020000);
 }
 
+// Waits until at most VM of this wave's vector-memory operations are outstanding, then for the
+// workgroup (vmcnt field split over bits 3:0 and 15:14; expcnt and lgkmcnt not waited for).  The empty
+// statements tell the compiler to move no memory access across the wait or the barrier, which
+// themselves order none.  It may move loads that nothing can alias all the same: that enough of them
+// stay between a request and its wait is checked on the built code (tests/test_lds_waits.py).
+template <int VM>
+__device__ __forceinline__ void wait_then_barrier() {
+    static_assert(VM >= 0 && VM < 64, "vmcnt range");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // One element of a raw buffer load (out-of-range offsets read zero).
 template <class T>
 __device__ __forceinline__ T load_elem(__amdgpu_buffer_rsrc_t rb, uint32_t voff, uint32_t soff);
@@ -1092,17 +1107,10 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
         // this wave's requests of tile e + 1 (made at the start of tile e - 1, or before the
         // first tile) are complete when no more than the loads issued after them are
         // outstanding: the NBS B operands of tile e - 1, this tile's descriptor, requests and
-        // NBS B operands, less one to spare (vmcnt field split over bits 3:0 and 15:14; expcnt
-        // and lgkmcnt not waited for); the barrier then makes every wave's part visible and frees Lc for the
-        // next tile's request
+        // NBS B operands, less one to spare; the barrier then makes every wave's part visible and
+        // frees Lc for the next tile's request
         constexpr int VM = 2 * NBS + NREQ;
-        static_assert(VM < 64, "vmcnt range");
-        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
-        // (the empty statements keep the compiler from moving memory accesses across the
-        // barrier, which itself orders none)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        wait_then_barrier<VM>();
         Te = Tn;
         Tn = Tnn;
         Tnn = to_desc(dn);
@@ -1277,18 +1285,11 @@ k_far_half(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
     };
     // at the end of half i this wave's requests of half i + 1 (made at the start of half i - 1) are
     // complete when no more than the loads issued after them are outstanding: the NH B operands of
-    // half i - 1, then the requests and NH B operands of half i, less one to spare (vmcnt field split over bits 3:0
-    // and 15:14; expcnt and lgkmcnt not waited for); the barrier then makes every wave's part
-    // visible and frees the buffer just read
+    // half i - 1, then the requests and NH B operands of half i, less one to spare; the barrier then
+    // makes every wave's part visible and frees the buffer just read
     auto end_half = [&]() {
         constexpr int VM = 2 * NH + NREQ - 1;
-        static_assert(VM < 64, "vmcnt range");
-        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
-        // (the empty statements keep the compiler from moving memory accesses across the
-        // barrier, which itself orders none)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        wait_then_barrier<VM>();
     };
     // one tile, its halves in buffers P and P + 1 (mod 3)
     auto tile = [&](int e, auto par) {
@@ -1465,17 +1466,11 @@ k_far_wide64(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items
         }
     };
     // this wave's requests of the next half were made before the NH B-operand loads that
-    // followed them, less one to spare (vmcnt field split over bits 3:0 and 15:14; expcnt and lgkmcnt not waited
-    // for); the barrier then makes every wave's part visible and frees the buffer just read
+    // followed them, less one to spare; the barrier then makes every wave's part visible and frees the
+    // buffer just read
     auto end_half = [&]() {
         constexpr int VM = NH - 1;
-        static_assert(VM < 64, "vmcnt range");
-        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
-        // (the empty statements keep the compiler from moving memory accesses across the
-        // barrier, which itself orders none)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        wait_then_barrier<VM>();
     };
     for (int e = t_beg; e < t_end; ++e) {
         const v4u dn = __builtin_amdgcn_raw_buffer_load_b128(
@@ -1657,18 +1652,11 @@ k_far_narrow64(const Chunk* __restrict__ chunks, const FarItem* __restrict__ ite
     };
     // this wave's requests of half u + 1 (made at the start of half u - 1) are complete when no more
     // than the loads issued after them are outstanding: the NHS B operands of half u - 1, half u's
-    // requests and NHS B operands, less one to spare (vmcnt field split over bits 3:0 and 15:14;
-    // expcnt and lgkmcnt not waited for); the barrier then makes every wave's part visible and frees
-    // the buffer just read
+    // requests and NHS B operands, less one to spare; the barrier then makes every wave's part visible
+    // and frees the buffer just read
     auto end_half = [&]() {
         constexpr int VM = 2 * NHS + NREQ - 1;
-        static_assert(VM < 64, "vmcnt range");
-        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
-        // (the empty statements keep the compiler from moving memory accesses across the
-        // barrier, which itself orders none)
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
+        wait_then_barrier<VM>();
     };
     // one tile: its halves are in buffers P and P + 1; the next tile's go to P + 2 and P
     auto tile = [&](int e, auto par) {
