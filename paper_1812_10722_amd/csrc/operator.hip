@@ -1148,8 +1148,14 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
 // 32768 panels, P = 8: 24 wavelengths 0.67 -> 0.58 ms, 32: 0.69 -> 0.64, 40: 1.02 -> 0.93,
 // 48: 1.14 -> 0.93; 31576-panel sensor, P = 10: 24: 0.79 -> 0.70, 48: 1.49 -> 1.10, 64: 1.52 -> 1.36.
 // Requires work items that do not span a chunk's own-surface boundary (plan_items, cut_self).
+// Waves per SIMD asked for: those that the registers and the three buffers leave room for.
+constexpr int far_half_waves(int nsm, int w, int th) {
+    const int lds = 3 * (((nsm > DSTEPS ? nsm : DSTEPS) + 1) / 2) * 1024;
+    const int by_lds = (160 * 1024 / lds * w * th + 3) / 4, by_regs = th == 2 ? 24 / (w * th) : 16 / w;
+    return by_lds < by_regs ? by_lds : by_regs;
+}
 template <int NSM, int W, int TH>
-__global__ void __launch_bounds__(64 * W * TH, TH == 2 ? 24 / (W * TH) : 16 / W)
+__global__ void __launch_bounds__(64 * W * TH, far_half_waves(NSM, W, TH))
 k_far_half(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
            const int32_t* __restrict__ item_order, const int32_t* __restrict__ tile_self,
            const TileDesc* __restrict__ tiles, const float* __restrict__ tileA,
