@@ -402,7 +402,7 @@ static_assert(sizeof(TileDesc) == 16, "tile descriptors are fetched as one 128-b
 // A work item of the one-operator matrix-core far-field kernel: tiles [t0, t1) of a chunk.
 // slot < 0: the whole chunk, whose sums the kernel writes itself; slot >= 0: a piece of a
 // chunk cut into several (never across its own-surface/other-surface boundary), whose FP64
-// partial sums go to scratch block `slot` for k_far_reduce.
+// partial sums go to scratch block `slot` for the row combination (or finish_sums).
 struct FarItem {
     int32_t chunk, t0, t1, slot;
 };
@@ -470,7 +470,7 @@ struct Geometry {
         DevBuf<FarItem> items;
         DevBuf<int32_t> order;  // workgroup -> item (-1: none); a multiple of 8 entries
         DevBuf<FarRed> red;     // [n_chunks] partial sums of each chunk (when some are cut)
-        int n_order = 0, n_red = 0, n_slots = 0;
+        int n_order = 0, n_slots = 0;
         size_t bytes() const { return items.bytes() + order.bytes() + red.bytes(); }
     };
     FarPlan far_plan[3];

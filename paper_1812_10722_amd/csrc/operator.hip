@@ -3033,7 +3033,7 @@ int64_t estimate_tile_elems(const Geometry& g) {
 // ordering puts at the end of the run.  With `cut_self` every chunk that has tiles on both
 // sides of its own-surface boundary is cut there too, so no item spans it.  A chunk of several
 // items has consecutive partial-sum slots in tile order (own-surface pieces first), added in
-// that order by k_far_reduce.
+// that order by the row combination or finish_sums.
 // `fine`: the plan for few chunks, or false (nothing planned) where the first one is as good.  With
 // a few chunks per XCD, pieces of about the mean leave most CUs idle or hold a launch to its
 // longest piece, so the limit is the cost per item of FINE_ITEMS items (they fill the chip: two
@@ -3125,19 +3125,19 @@ bool plan_items(const std::vector<uint8_t>& steps, const std::vector<int32_t>& o
     };
     // the tail of each run cut finer
     if (tail > 0.0 && cap > 0.0) {
-        std::vector<char> fine(pcs.size(), 0);
+        std::vector<char> in_tail(pcs.size(), 0);
         for (int r = 0; r < 8; ++r) {
             const std::vector<int32_t> ix = by_cost(pcs, r);
             double rc = 0.0, acc = 0.0;
             for (int32_t i : ix) rc += pcs[i].cost;
             for (int k = static_cast<int>(ix.size()) - 1; k >= 0 && acc < tail * rc; --k) {
-                fine[ix[k]] = 1;
+                in_tail[ix[k]] = 1;
                 acc += pcs[ix[k]].cost;
             }
         }
         std::vector<Piece> ref;
         for (size_t i = 0; i < pcs.size(); ++i) {
-            if (fine[i])
+            if (in_tail[i])
                 cut_chunk(pcs[i].c, pcs[i].t0, pcs[i].t1, pcs[i].run, tailcap, ref);
             else
                 ref.push_back(pcs[i]);
@@ -3435,7 +3435,6 @@ void build_tiles(Geometry& g, TilePlan& P, TileBuild& b) {
         up.add(fp.items.p, W.items.data(), W.items.size());
         up.add(fp.order.p, W.order.data(), W.order.size());
         fp.n_order = static_cast<int>(W.order.size());
-        fp.n_red = static_cast<int>(W.red.size());
         fp.n_slots = W.n_slots;
         if (!W.red.empty()) {
             std::vector<FarRed> red(nc, FarRed{0, 0, 0, 0});
