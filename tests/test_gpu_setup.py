@@ -22,12 +22,13 @@ def _busy(stream, seconds):
     """Keeps a stream busy for about that long (a bounded spin); an event behind it."""
     t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     with torch.cuda.stream(stream):
+        torch.cuda._sleep(50_000_000)  # the clock rises first
         t0.record()
-        torch.cuda._sleep(1_000_000)
+        torch.cuda._sleep(50_000_000)
         t1.record()
     stream.synchronize()
     with torch.cuda.stream(stream):
-        torch.cuda._sleep(int(1_000_000 * seconds * 1e3 / t0.elapsed_time(t1)))
+        torch.cuda._sleep(int(50_000_000 * seconds * 1e3 / t0.elapsed_time(t1)))
         end = torch.cuda.Event()
         end.record()
     return end
@@ -63,14 +64,16 @@ def test_setup_does_not_wait_for_a_setup_on_another_stream(lib):
     else:
         other.join()
         pytest.skip("no stream runs beside the busy one")
+    assert not end.query()
+    start = time.perf_counter()
     for _ in range(3):
         lib.Geometry(mesh, stream=b, **kw).close()
-    waited = end.query()
+    took, waited = time.perf_counter() - start, end.query()
     other.join()
     torch.cuda.synchronize()
     rhs = [g.rhs(1.7733, np.array([[-3.0 + 0.3j]])) for g in (made[0], lib.Geometry(mesh, **kw))]
     assert torch.equal(*rhs)  # the delayed uploads arrived as they were given
-    assert not waited
+    assert not waited, took
 
 
 # the sort without a scan (up to 262144 panels) and with one: a mesh given in another panel order is the
