@@ -33,12 +33,16 @@ template <class T> constexpr int tile_panels() { return sizeof(T) == 8 ? 16 : 32
 
 template <class T> __device__ __forceinline__ T rsqrt_t(T x);
 template <> __device__ __forceinline__ float rsqrt_t<float>(float x) { return rsqrtf(x); }
-// FP64: the hardware estimate (relative error below 2^-22) and one third-order step,
-// y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2: its truncation, 5 e^3 / 16 < 2^-64, is below the
-// rounding, as after two Newton steps, in five operations instead of eight.
+// FP64: the hardware estimate (relative error 5.3e-8), cut to 26 bits so that its square is exact, and
+// one third-order step, y (1 + e / 2 + 3 e^2 / 8) with e = 1 - x y^2: the truncation, 5 e^3 / 16 <
+// 2^-66, and e's rounding are below that of the result, the only one left.  Over 8.6e9 arguments the
+// largest error is 1.110e-16 and the mean 4.08e-17 (two Newton steps: 1.387e-16, 4.45e-17, in eight
+// operations instead of five; from the whole estimate, where x y rounds: 1.457e-16, 4.45e-17, 2 %
+// faster in k_direct64).
 template <> __device__ __forceinline__ double rsqrt_t<double>(double x) {
-    const double y = __builtin_amdgcn_rsq(x);
-    const double e = fma(-x * y, y, 1.0);
+    const uint2 b = __builtin_bit_cast(uint2, __builtin_amdgcn_rsq(x));
+    const double y = __builtin_bit_cast(double, make_uint2(b.x & 0xf8000000u, b.y));
+    const double e = fma(-x, y * y, 1.0);
     return fma(y * e, fma(0.375, e, 0.5), y);
 }
 
@@ -312,7 +316,7 @@ k_far(const Chunk* __restrict__ chunks, const Box* __restrict__ boxes,
 // ------------------------------------------------------------------------------- direct sums
 // FP64 sums of one or two wavelengths over direct ranges alone, every kernel value formed on the
 // fly: a dense product on a mesh whose factors do not fit the device.  Bound by the FP64 vector
-// units: 16 operations per far-rule node, one of them at quarter rate, and 13 per pair (77 at K = 4).
+// units: 16 FP64 operations per far-rule node, one of them at quarter rate, and 13 per pair (77 at K = 4).
 // One target of a chunk per lane; DW waves take tiles of DT panels of each range in turn.  A panel's
 // record, centroid and densities are the same for the whole wave, so they come by scalar loads and
 // enter the arithmetic from scalar registers: no LDS, barrier or vector load in the loop (k_far,
@@ -320,8 +324,8 @@ k_far(const Chunk* __restrict__ chunks, const Box* __restrict__ boxes,
 // compensated sum; the waves' sums are added (compensated) through LDS after the own-surface ranges
 // and at the end.  For one wavelength a workgroup takes two chunks where their ranges are equal, so
 // that a panel's values serve two targets per lane.
-// 111392 panels, one wavelength, K = 4: 39.1 ms (one chunk per workgroup: 41.0, k_far: 232 ms),
-// 0.32 T pairs/s; the vector units issue 75 % of the time, 29 ms.
+// 111392 panels, one wavelength, K = 4: 40.0 ms (one chunk per workgroup: 2 ms more, k_far: 232 ms),
+// 0.31 T pairs/s; the vector units issue 75 % of the time.
 constexpr int DW = 16;  // waves per workgroup
 constexpr int DT = 16;  // panels per partial
 constexpr int DCUS = 256;  // compute units
@@ -1133,6 +1137,13 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
     write_sums(o_all);
 }
 
+// Waves per SIMD asked for: those that the registers and the three buffers leave room for.
+constexpr int far_half_waves(int nsm, int w, int th) {
+    const int lds = 3 * (((nsm > DSTEPS ? nsm : DSTEPS) + 1) / 2) * 1024;
+    const int by_lds = (160 * 1024 / lds * w * th + 3) / 4, by_regs = th == 2 ? 24 / (w * th) : 16 / w;
+    return by_lds < by_regs ? by_lds : by_regs;
+}
+
 // FP32 products of more than 16 wavelengths, left factors read straight into LDS, in half tiles:
 // workgroups of exactly W column groups (3 .. 8), one operator each, with one wave per group
 // (TH = 1) or two, each on half of the chunk's targets (TH = 2).  Every tile runs as two halves of
@@ -1148,12 +1159,6 @@ k_far_wide(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
 // 32768 panels, P = 8: 24 wavelengths 0.67 -> 0.58 ms, 32: 0.69 -> 0.64, 40: 1.02 -> 0.93,
 // 48: 1.14 -> 0.93; 31576-panel sensor, P = 10: 24: 0.79 -> 0.70, 48: 1.49 -> 1.10, 64: 1.52 -> 1.36.
 // Requires work items that do not span a chunk's own-surface boundary (plan_items, cut_self).
-// Waves per SIMD asked for: those that the registers and the three buffers leave room for.
-constexpr int far_half_waves(int nsm, int w, int th) {
-    const int lds = 3 * (((nsm > DSTEPS ? nsm : DSTEPS) + 1) / 2) * 1024;
-    const int by_lds = (160 * 1024 / lds * w * th + 3) / 4, by_regs = th == 2 ? 24 / (w * th) : 16 / w;
-    return by_lds < by_regs ? by_lds : by_regs;
-}
 template <int NSM, int W, int TH>
 __global__ void __launch_bounds__(64 * W * TH, far_half_waves(NSM, W, TH))
 k_far_half(const Chunk* __restrict__ chunks, const FarItem* __restrict__ items,
