@@ -122,9 +122,9 @@ typedef struct {
  *             registers (more than 32 wavelengths: one column half each) instead of
  *             workgroups that read them straight into LDS buffers (more than 32 wavelengths,
  *             and from P = 6 FP32 from 17 and, but for P = 10, FP64 from 9 wavelengths: all
- *             column groups of an operator, identical sums; FP32 up to 16 wavelengths at P = 8 or 15: 4 or 8 waves per column
- *             group instead of 2 or 4, so the FP32 partial sums are split differently).  A tuning
- *             alternative. */
+ *             column groups of an operator, identical sums; FP32 up to 16 wavelengths at P = 8
+ *             or 15: 4 or 8 waves per column group instead of 2 or 4, so the FP32 partial sums
+ *             are split differently).  A tuning alternative. */
 typedef struct {
     int32_t k_far;
     int32_t k_fine;

@@ -706,8 +706,8 @@ int64_t arnoldi_blocks(int64_t nvec, int B) {
 }
 
 // Pinned, coherent host memory for the residual estimates, which the finishing kernel writes
-// directly, one block per host thread, allocated once and kept for the life of the process (freeing pinned memory can wait for the whole device, which
-// would stall concurrent requests).
+// directly: one block per host thread, allocated once and kept for the life of the process (freeing
+// pinned memory can wait for the whole device, which would stall concurrent requests).
 double* pinned_estimates(int n) {
     constexpr int CAP = 4 * 64;
     LSPR_REQUIRE(n <= CAP, LSPR_E_INVALID, "too many columns for the estimate buffer");

@@ -1,10 +1,10 @@
 // lspr_apply_noalloc: the block matrix-vector product of lspr_apply for callers that cannot
 // allocate device memory (code under stream capture, tight serving loops).  Every temporary of
-// the product (permittivity ratios, the sorted copies of x and y, packed densities, raw layer
-// sums, box moments and partial moments) lives in one file-scope device array of fixed size,
-// reached through the address the runtime reports for it on each device; the call allocates
-// nothing and launches the same kernels as lspr_apply, in the same order, so its results are
-// the same bit for bit.
+// the product (permittivity ratios, a copy of x where y overlaps it, packed densities, raw layer
+// sums, box moments and partial moments, partial sums of the far-field pieces) lives in one
+// file-scope device array of fixed size, reached through the address the runtime reports for it on
+// each device; the call allocates nothing and launches the same kernels as lspr_apply, in the same
+// order, so its results are the same bit for bit.
 #include <algorithm>
 #include <map>
 #include <mutex>

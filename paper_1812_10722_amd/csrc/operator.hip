@@ -600,8 +600,8 @@ __device__ __forceinline__ Quad<T> lds_quad(const float4* ab, int st, int lane) 
     }
 }
 
-// Far field on matrix cores, one operator per workgroup (FP32 or FP64 products).  Workgroups b, b + 8, ... handle one chunk (all on
-// the same XCD, so the later ones read the chunk's left factors from L2): the double-layer (K)
+// Far field on matrix cores, one operator per workgroup (FP32 or FP64 products).  Workgroups b,
+// b + 8, ... handle one chunk (all on the same XCD, so the later ones read the chunk's left factors from L2): the double-layer (K)
 // and single-layer (V) columns, each in 1 or 2 halves of 4 column groups of 16, one group per
 // wave.  Expansion tiles share one left factor between the operators; direct tiles hold the K
 // factor and then the V factor.
@@ -640,7 +640,8 @@ k_far_tiles_op(const Chunk* __restrict__ chunks, const FarItem* __restrict__ ite
     const int c16 = lane & 15, grp = lane >> 4;
     const int ncols = 2 * pad;
     // OPS = 1: 2 * halves workgroups per chunk, at b, b + 8, ...: operator j & 1, column half
-    // j >> 1 (nops = 1, V columns only: halves workgroups, column half j).  OPS = 2: halves workgroups per chunk, column half j, operator wave / 4.
+    // j >> 1 (nops = 1, V columns only: halves workgroups, column half j).  OPS = 2: halves workgroups
+    // per chunk, column half j, operator wave / 4.
     const int b = blockIdx.x;
     const int per = OPS == 2 ? halves : nops * halves;
     const int j = (b >> 3) % per;

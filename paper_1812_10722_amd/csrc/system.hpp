@@ -16,9 +16,9 @@ std::vector<double2> ratio_values(const Geometry& g, const EpsSet& eps, int B);
 // Small sets go as a kernel argument (set_ratios); larger ones by a copy that is waited for.
 void set_ratios(const std::vector<double2>& h, double2* d, hipStream_t s);
 void upload_ratios(Geometry& g, const EpsSet& eps, int B, DevBuf<double2>& d, hipStream_t s);
-// Bytes of scratch one lspr_apply batch of B columns needs in precision prec (ratios, the
-// sorted copies of x and y, packed densities, raw sums, moments, P2M partial sums), counted in
-// the arena's 256-byte pieces.
+// Bytes of scratch one lspr_apply batch of B columns needs in precision prec (ratios, two vectors of
+// which at most one is used, packed densities, raw sums, moments, P2M partial sums, far-field pieces),
+// counted in the arena's 256-byte pieces.
 size_t apply_scratch_bytes(const Geometry& g, int B, int prec);
 
 // y[col] = A(col) x[col] for nslot columns; col = d_cols[slot] (or slot when d_cols is null),
