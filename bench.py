@@ -242,14 +242,15 @@ def serving_main(args):
     print(json.dumps(line), flush=True)
 
 
-def traffic_entry(kernel_file, name):
-    """HBM bytes per launch from rocprofv3 counter runs, valid only for the same kernel source."""
+def traffic_entry(kernel_file, name, workload):
+    """HBM bytes per launch from rocprofv3 counter runs, valid only for the same kernel source and
+    the workload that was counted."""
     path = os.path.join(ROOT, "profiles", f"{name}_traffic.json")  # written from rocprofv3 --pmc runs
     if not os.path.exists(path):
         return None
     rec = json.load(open(path))
     sha = hashlib.sha256(open(kernel_file, "rb").read()).hexdigest()
-    if rec.get("source_sha256") != sha:
+    if rec.get("source_sha256") != sha or rec.get("workload") != workload:
         return None
     return rec
 
@@ -506,7 +507,7 @@ def main():
     # x 2 (packed FP32) x 2.4 GHz
     peak = PEAK_FP32_MFMA_TFLOPS if mfma else PEAK_FP32_VALU_TFLOPS
     trec = traffic_entry(os.path.join(ROOT, "paper_1812_10722_amd", "csrc", "operator.hip"),
-                         "far") if mfma else None
+                         "far", w.name) if mfma else None
     roofline = {"kernel": "k_far_wide and k_far_half (FP32 matrix-core far field: expansion "
                           "and direct far-rule tiles)" if mfma else
                           "k_far (FP32 vector-ALU far field, no tiles kept)",
