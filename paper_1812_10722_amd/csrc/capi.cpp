@@ -662,15 +662,24 @@ int64_t request_footprint(int64_t N, int S, int n_lambda, const lspr_op_params& 
 }  // namespace lspr
 
 size_t lspr::Geometry::device_bytes() const {
-    return tri.bytes() + cen.bytes() + nrm.bytes() + area.bytes() + surf.bytes() + perm.bytes() +
-           iperm.bytes() + morton.bytes() + boxes.bytes() + far_rule.bytes() +
-           mom_slot.bytes() + chunks.bytes() + m2p_off.bytes() + m2p_box.bytes() +
-           m2p_self.bytes() + p2p_off.bytes() + p2p_rng.bytes() + p2p_self.bytes() +
-           near_off64.bytes() + near_col.bytes() + near_dv.bytes() + near_dk.bytes() +
-           vself.bytes() + rhs_u.bytes() + charge_u.bytes() + ws_inv_eps.bytes() + ws_ratio.bytes() + ws_dens.bytes() + ws_mom.bytes() + ws_out.bytes() +
-           ws_part.bytes() + p2m_seg.bytes() + p2m_red.bytes() + p2mA.bytes() + p2mA64.bytes() + p2m_aoff.bytes() + tiles.bytes() +
-           far_plan[0].bytes() + far_plan[1].bytes() + far_plan[2].bytes() + ws_fpart.bytes() +
-           tile_self.bytes() + tileA.bytes() + tileA64.bytes() + src32.bytes() + src64.bytes();
+    std::vector<const Slab*> slabs;  // those that pieces come from, counted in whole
+    size_t total = 0;
+    auto add = [&](const auto&... bufs) {
+        auto one = [&](const auto& b) {
+            if (b.slab == nullptr) total += b.bytes();
+            else if (std::find(slabs.begin(), slabs.end(), b.slab) == slabs.end()) {
+                slabs.push_back(b.slab);
+                total += b.slab->bytes;
+            }
+        };
+        (one(bufs), ...);
+    };
+    add(tri, cen, nrm, area, surf, perm, iperm, morton, boxes, far_rule, mom_slot, chunks, m2p_off,
+        m2p_box, m2p_self, p2p_off, p2p_rng, p2p_self, near_off64, near_col, near_dv, near_dk,
+        vself, rhs_u, charge_u, ws_inv_eps, ws_ratio, ws_dens, ws_mom, ws_out, ws_part, p2m_seg,
+        p2m_red, p2mA, p2mA64, p2m_aoff, tiles, ws_fpart, tile_self, tileA, tileA64, src32, src64);
+    for (const FarPlan& fp : far_plan) add(fp.items, fp.order, fp.red);
+    return total;
 }
 
 extern "C" {

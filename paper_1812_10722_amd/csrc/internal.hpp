@@ -471,7 +471,6 @@ struct Geometry {
         DevBuf<int32_t> order;  // workgroup -> item (-1: none); a multiple of 8 entries
         DevBuf<FarRed> red;     // [n_chunks] partial sums of each chunk (when some are cut)
         int n_order = 0, n_slots = 0;
-        size_t bytes() const { return items.bytes() + order.bytes() + red.bytes(); }
     };
     FarPlan far_plan[3];
     // largest piece, as a fraction of the mean chunk cost, per launch class (0: no pieces), and

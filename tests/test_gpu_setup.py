@@ -91,3 +91,11 @@ def test_setup_does_not_depend_on_the_panels_order(lib, nu):
         rhs.append(geo.rhs(em, es, e).cpu().numpy()[0].reshape(2, -1))
         geo.close()
     assert np.abs(rhs[1] - rhs[0][:, order]).max() < 1e-11 * np.abs(rhs[0]).max()
+
+
+def test_device_bytes_counts_slabs(lib):
+    """Small buffers are pieces of slabs of 1 MiB and more, which a handle holds as long as one piece."""
+    v, t = octasphere(1, 10.0)
+    geo = lib.Geometry([(v, t)], method="dense", precision="fp64")
+    assert 1 << 20 <= geo.info()["device_bytes"] <= 32 << 20
+    geo.close()
